@@ -155,11 +155,15 @@ enum {
     IPC_Q_SPMV_LANES = 13, /* lanes per row the Hessian product uses            */
     IPC_Q_FEM_BLOCKS = 14, /* workgroup sizes of the FEM assembly's kernels:
                               (k_fem << 32) | (k_bsr_assemble << 16) | k_fem_grad_gather */
-    IPC_Q_PCG_FUSED = 15   /* 1 when a PCG iteration applies the coarse correction
+    IPC_Q_PCG_FUSED = 15,  /* 1 when a PCG iteration applies the coarse correction
                               inside its update launch (one scene, correction on;
                               the environment variable IPC_NO_FUSED_PCG = 1, read
                               at ipc_create, keeps it in a launch of its own).
                               Both forms give the same bits.                  */
+    IPC_Q_PCG_RESIDENT = 16 /* PCG solves of this context so far whose iterations
+                              all ran in one launch (one scene that fits the
+                              chip; also the same bits; IPC_NO_GRAPH = 1 and
+                              IPC_NO_FUSED_PCG = 1 keep it off)               */
 };
 
 /* Flags of ipc_energy_grad_hess. */
@@ -370,7 +374,9 @@ int ipc_time_kernel(ipc_ctx *ctx, int kernel, int reps, double *avg_us, double *
  * (nullable) the choice.  The default before any call is 8 lanes; the
  * environment variable IPC_SPMV_LANES (1, 2, 4, 8 or 16), read at
  * ipc_create, fixes the count instead: the autotuner still times every
- * count but keeps that one.  Otherwise the choice is also kept for the
+ * count but keeps that one.  A one-scene context that takes its PCG
+ * solves in one launch (IPC_Q_PCG_RESIDENT) keeps 8 lanes, whose sums that
+ * launch forms, unless the variable fixes another count.  Otherwise the choice is also kept for the
  * process, keyed by the context's size bucket (the powers of two of the
  * static pattern's block count and of the node count, and whether it holds
  * several scenes); a context created later in the same bucket starts with

@@ -562,6 +562,7 @@ extern "C" int ipc_create(const ipc_scene_desc *scenes, int n_scenes, void *hip_
         create_context(c, scenes, n_scenes);
         setup_after_create(c);
         adopt_tuned(c);
+        pcg_resident_setup(c);
     });
     if (rc != IPC_OK) {
         g_create_error = c->err;
@@ -618,6 +619,7 @@ extern "C" int ipc_create_ws(const ipc_scene_desc *scenes, int n_scenes, const i
         setup_after_create(c);
         adopt_tuned(c);
         reserve_capacity(c, cap->max_pairs, cap->max_candidates, cap->max_local_blocks);
+        pcg_resident_setup(c);
         IPC_HIP(hipStreamSynchronize(c->stream));
     });
     if (rc != IPC_OK) {
@@ -658,6 +660,7 @@ extern "C" int ipc_query(const ipc_ctx *c, int what, int64_t *v)
     case IPC_Q_WS_PEAK: *v = (int64_t)c->ws.peak; return IPC_OK;
     case IPC_Q_SPMV_LANES: *v = c->spmv_lanes; return IPC_OK;
     case IPC_Q_FEM_BLOCKS: *v = ((int64_t)c->fem_block << 32) | ((int64_t)c->asm_block << 16) | c->grad_block; return IPC_OK;
+    case IPC_Q_PCG_RESIDENT: *v = c->resident_solves; return IPC_OK;
     case IPC_Q_PCG_FUSED: *v = c->cg_fusable && c->coarse_on && c->pcg_fused && c->n_cdom > 0 ? 1 : 0; return IPC_OK;
     }
     return IPC_E_INVALID;
@@ -1492,7 +1495,8 @@ extern "C" int ipc_autotune(ipc_ctx *c, int reps, double *us_host, int32_t *lane
         c->prof = false;
         int keep = c->spmv_lanes;
         autotune_spmv(c, reps, us_host);
-        if (c->spmv_lanes_forced) c->spmv_lanes = keep;
+        // (the one-launch PCG solve sums as 8 lanes per row do)
+        if (c->spmv_lanes_forced || c->resident_ok) c->spmv_lanes = keep;
         autotune_fem(c, reps);
         {
             std::lock_guard<std::mutex> lk(g_tune_mu);

@@ -691,6 +691,8 @@ void create_context(ipc_ctx *c, const ipc_scene_desc *scenes, int n, const int64
             // half-space entries: list, planes, energies and chunk sums, lag, Hessian blocks, slot entries
             4 * MH, 32 * (int64_t)n, 8 * (MH + 1), 8 * (MH + 1), 8 * (MH / TILE + 1), 8 * (MH / TILE + 1), 8 * MH, 24 * MH,
             72 * MH, 4 * 4 * 16 * MH, 4 * (int64_t)n,
+            // the one-launch solve's exchange words
+            (int64_t)pcg_resident_bytes(n, (int)N, body),
             // sort and scan storage (rocprim: a copy of keys and values plus per-block counts), bounded
             16 * std::max<int64_t>(std::max(std::max(16 * P, 16 * MH), B), std::max(Pp, Q)) + (4 << 20)};
         size_t bytes = 0;

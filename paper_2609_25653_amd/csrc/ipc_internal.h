@@ -344,6 +344,8 @@ struct Dev {
     DBuf<int> cg_ph_ptr, cg_ph_e, cg_ph_n; // one-launch step: per domain its entries that stand for a body (entry, node)
     DBuf<double> cg_inv, cg_part;
     DBuf<int> pcg_act, pcg_it;
+    DBuf<unsigned long long> px_words;     // one-launch solve: the words its workgroups exchange
+    DBuf<int> px_ctl;                      // its abort word and count of workgroups at their end
     DBuf<int> pair_flag, lag_flag;         // 1: the pair's blocks were merged into the matrix
     DBuf<int> tickets;                     // small device counters
     DBuf<double> grav;
@@ -421,6 +423,10 @@ struct ipc_ctx {
     unsigned long long *h_peek = nullptr;       // pinned, coherent host memory: 2 slots of one word per scene
     unsigned long long *h_peek_dev = nullptr;   // its device address
     unsigned int peek_seq = 0;
+    bool resident_ok = false;             // the one-launch solve has its memory (ipc_pcg_resident.hip)
+    int64_t resident_solves = 0;          // solves it has done
+    int resident_skip = 0;                // solves to take in the launch-per-iteration form before it is tried again
+    int device = 0, n_cu = 0;             // the context's device and its compute units
     // pinned host staging: a readback arena (one HostReads at a time) and an upload ring
     char *pin_rd = nullptr, *pin_wr = nullptr;
     size_t pin_wr_off = 0;
@@ -479,6 +485,16 @@ void coarse_build(ipc_ctx *c);
 void coarse_apply(ipc_ctx *c, const int *act, const double *r, double *z, int parity);
 
 void pcg_solve(ipc_ctx *c, const double *b, double *x, double eta, const int *want);
+// The host's progress words: ready for use; the next sequence number; wait
+// for n words of that number in a slot and return the largest value.
+void pcg_peek_ready(ipc_ctx *c);
+unsigned int pcg_next_seq(ipc_ctx *c);
+int pcg_await(ipc_ctx *c, int slot, unsigned int seq, int n);
+// The iterations of a one-scene solve in one launch, after the first r, z,
+// w and partials are formed; false: not taken, nothing of these has changed.
+bool pcg_resident(ipc_ctx *c, double *x);
+void pcg_resident_setup(ipc_ctx *c);
+size_t pcg_resident_bytes(int n_scenes, int N, int NB);   // its memory in a workspace
 // exclusive scan of n ints into out[0..n] (out[n] = total), on the context's stream
 void exclusive_scan_int(ipc_ctx *c, const int *in, int *out, int n);
 void pcg_wginfo(ipc_ctx *c);

@@ -953,6 +953,47 @@ __global__ void __launch_bounds__(BLOCK) k_pcg_peek(int ns, int q, const int *__
 // plus the 3x3 inverse block per FEM vertex; 12x12 blocks per body.
 static double update_bytes(const ipc_ctx *c) { return (264.0 + 72.0) * c->NFEM + (4 * 264.0 + 1152.0) * c->NB; }
 
+// The peek kernel publishes one word per scene into pinned, coherent host
+// memory, which the host polls: no event and no stream synchronisation
+// per batch.  If the words do not appear within a second the host
+// synchronises the stream (which also reports a failed launch) and reads
+// them again.
+void pcg_peek_ready(ipc_ctx *c)
+{
+    if (c->h_peek) return;
+    const size_t n = 2 * (size_t)c->n_scenes;
+    IPC_HIP(hipHostMalloc((void **)&c->h_peek, n * sizeof(unsigned long long), hipHostMallocMapped | hipHostMallocCoherent));
+    IPC_HIP(hipHostGetDevicePointer((void **)&c->h_peek_dev, c->h_peek, 0));
+    for (size_t i = 0; i < n; ++i) c->h_peek[i] = 0;
+}
+
+unsigned int pcg_next_seq(ipc_ctx *c)
+{
+    if (++c->peek_seq == 0) ++c->peek_seq;   // 0 never names a peek
+    return c->peek_seq;
+}
+
+int pcg_await(ipc_ctx *c, int slot, unsigned int seq, int n)
+{
+    volatile unsigned long long *wv = c->h_peek + (size_t)c->n_scenes * slot;
+    auto ready = [&]() {
+        for (int k = 0; k < n; ++k)
+            if ((unsigned int)(wv[k] >> 32) != seq) return false;
+        return true;
+    };
+    auto t0 = std::chrono::steady_clock::now();
+    while (!ready()) {
+        if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(1)) {
+            IPC_HIP(hipStreamSynchronize(c->stream));
+            if (!ready()) throw Error(IPC_E_DEVICE, "PCG progress words did not reach host memory");
+            break;
+        }
+    }
+    int most = 0;
+    for (int k = 0; k < n; ++k) most = std::max(most, (int)(unsigned int)(wv[k] & 0xffffffffull));
+    return most;
+}
+
 void pcg_solve(ipc_ctx *c, const double *b, double *x, double eta, const int *want)
 {
     Dev &D = c->d;
@@ -1003,43 +1044,14 @@ void pcg_solve(ipc_ctx *c, const double *b, double *x, double eta, const int *wa
         if (!fused) coarse_apply(c, act + (q ^ 1) * ns, r, z, q ^ 1);
         hess_apply(c, zb[q ^ 1], w, act + (q ^ 1) * ns, D.part_node3.p);
     };
-    // The peek kernel publishes one word per scene into pinned, coherent host
-    // memory, which the host polls: no event and no stream synchronisation
-    // per batch.  If the words do not appear within a second the host
-    // synchronises the stream (which also reports a failed launch) and reads
-    // them again.
-    if (!c->h_peek) {
-        IPC_HIP(hipHostMalloc((void **)&c->h_peek, 2 * (size_t)ns * sizeof(unsigned long long), hipHostMallocMapped | hipHostMallocCoherent));
-        IPC_HIP(hipHostGetDevicePointer((void **)&c->h_peek_dev, c->h_peek, 0));
-        for (size_t i = 0; i < 2 * (size_t)ns; ++i) c->h_peek[i] = 0;
-    }
+    pcg_peek_ready(c);
+    if (pcg_resident(c, x)) return;
     auto peek = [&](int q, int slot, int n_since) {
-        unsigned int seq = ++c->peek_seq;
-        if (seq == 0) seq = ++c->peek_seq;   // 0 never names a peek
+        const unsigned int seq = pcg_next_seq(c);
         hipLaunchKernelGGL(k_pcg_peek, dim3(ns), dim3(BLOCK), 0, st, ns, q, seg_ptr(c, R_NODEW), D.maxpcg.p, D.pcg_part.p, ntile,
                            D.pcg_st.p, act, D.pcg_it.p, D.pcg_prev.p, n_since, seq, c->h_peek_dev + (size_t)ns * slot,
                            D.pcg_iters.p);
         return seq;
-    };
-    // 0 when no scene iterates any more, else the largest estimate
-    auto await = [&](int slot, unsigned int seq) {
-        volatile unsigned long long *wv = c->h_peek + (size_t)ns * slot;
-        auto ready = [&]() {
-            for (int k = 0; k < ns; ++k)
-                if ((unsigned int)(wv[k] >> 32) != seq) return false;
-            return true;
-        };
-        auto t0 = std::chrono::steady_clock::now();
-        while (!ready()) {
-            if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(1)) {
-                IPC_HIP(hipStreamSynchronize(st));
-                if (!ready()) throw Error(IPC_E_DEVICE, "PCG progress words did not reach host memory");
-                break;
-            }
-        }
-        int left = 0;
-        for (int k = 0; k < ns; ++k) left = std::max(left, (int)(unsigned int)(wv[k] & 0xffffffffull));
-        return left;
     };
     const int KB = 16, KS = 4;   // iterations per batch (even): far from and near convergence
     const int Ks[2] = {KB, KS};
@@ -1110,7 +1122,7 @@ void pcg_solve(ipc_ctx *c, const double *b, double *x, double eta, const int *wa
         if (nb - k_done < 2 && launched < maxit && left > inflight) launch_batch(left - inflight > KB ? 0 : 1);
         if (k_done == nb) break;   // nothing in flight: the iteration cap is reached
         int slot = k_done & 1;
-        left = await(slot, seq_of[slot]);
+        left = pcg_await(c, slot, seq_of[slot], ns);   // 0 when no scene iterates any more, else the largest estimate
         inflight -= size_of[slot];
         ++k_done;
         if (left == 0) break;

@@ -1,0 +1,64 @@
+"""The PCG solve in one launch (ipc_pcg_resident.hip) against the solve of one
+launch per iteration step: the same sums in the same order, so solutions and
+iteration counts are compared bit for bit, at the sizes where its split
+changes (1, 2 or 4 tiles of 64 rows per workgroup, with the coarse correction
+or without) and with affine bodies (rows of their own, coarse groups that
+stand for a body's node)."""
+import numpy as np
+import pytest
+
+import ipcscenes as S
+
+pytestmark = pytest.mark.gpu
+
+
+def _squeeze(c):
+    return S.gripper_squeeze(n_steps=1, pad_cells=c)
+
+
+SCENES = {
+    "one_tet": lambda: S.tiny_scene("tet"),                      # a single tile
+    "block": lambda: S.block_drop(n_steps=1),                    # FEM only, a ragged last tile
+    "free_body": lambda: S.tiny_scene("free_body"),              # bodies only
+    "squeeze_small": lambda: _squeeze((4, 2, 3)),                # long rows, contact with a body
+    "arm": lambda: S.arm_squeeze(n_steps=1),                     # 13 bodies, joint springs
+    "rich_15k": lambda: S.contact_rich(n_steps=1, n_disk=16, n_layers=32),   # about 14.6k nodes
+    "rich_27k": lambda: S.contact_rich(n_steps=1, n_disk=22, n_layers=40),   # about 26.8k nodes
+    "rich_33k": lambda: S.contact_rich(n_steps=1, n_disk=26, n_layers=38),   # about 33.5k nodes
+}
+
+
+@pytest.mark.parametrize("coarse", ["0", "1"])
+@pytest.mark.parametrize("name", list(SCENES))
+def test_one_launch_solve_matches_iteration_launches(name, coarse, monkeypatch):
+    import torch
+
+    from paper_2609_25653_amd import Sim
+    from paper_2609_25653_amd._lib import Q_PCG_RESIDENT
+    sc = SCENES[name]()
+    monkeypatch.setenv("IPC_PCG_COARSE", coarse)
+    got = []
+    for eager in ("1", "0"):
+        monkeypatch.setenv("IPC_NO_GRAPH", eager)
+        sim = Sim(sc)
+        y, _ = sim.state()
+        sim.begin_step(0)
+        b = torch.randn(sim.ndof, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(5))
+        out = []
+        for cap, eta in ((1, 1e-10), (7, 1e-10), (None, 1e-6)):
+            if cap is not None:
+                s2 = dict(sc, max_pcg=np.asarray(float(cap)))
+                one = Sim(s2)
+                one.begin_step(0)
+            else:
+                one = sim
+            x, it = one.pcg(y, b, eta)
+            out.append((x.clone(), int(it[0])))
+            # a right-hand side of zeros ends before the first update
+            x0, it0 = one.pcg(y, torch.zeros_like(b), eta)
+            assert it0[0] == 0 and not x0.any()
+            solves = one._query(Q_PCG_RESIDENT)
+            assert solves == (0 if eager == "1" else 2), (name, solves)
+        got.append(out)
+    for (xa, ia), (xb, ib) in zip(*got):
+        assert ia == ib and torch.equal(xa, xb), (name, ia, ib)
