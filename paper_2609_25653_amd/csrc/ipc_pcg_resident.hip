@@ -39,8 +39,7 @@
 // tiles, lanes, wavefront sums and partials), so both forms give the same
 // iterates bit for bit.
 //
-// Split: T tiles of 64 rows per workgroup of 512 threads (8 lanes per row as
-// in k_spmv<8>).  T = 1 as long as the tiles do not outnumber the compute
+// Split: T tiles of 64 rows per workgroup of 512 threads.  T = 1 as long as the tiles do not outnumber the compute
 // units (more units share the LDS and register traffic), else 2, else 4; the
 // coarse correction takes T = 4, which makes a workgroup one slice of a
 // coarse domain.  T = 4 is what registers hold: 8 blocks per lane are 144 of
@@ -58,11 +57,12 @@ namespace ipc {
 typedef unsigned long long u64;
 constexpr u64 PX_EMPTY = 0xFFF8DEADBEEFCAFEull;
 constexpr int PX_NT = 512;                 // threads: a tile's 64 rows x 8 lanes
-constexpr int PX_HALO = 1280;              // nodes of other workgroups a workgroup's short rows may read
+constexpr int PX_HALO = 1024;              // nodes of other workgroups a workgroup's short rows may read
 constexpr int PX_HASH = 2048;              // their lookup table (set-up)
-constexpr int PX_EXTRA = 2048;             // blocks past the two in registers, over all its short rows
-constexpr int PX_EXTRA_LDS = 512;          // of these, kept in LDS (the others are read from memory)
 constexpr int PX_BODIES = 16;              // affine bodies among a workgroup's nodes
+constexpr int PX_EXTRA = 1536;             // blocks past the two in registers, over all its short rows: the first 512 in
+                                           // registers too, one per thread,
+constexpr int PX_POOL = 128;               // the next ones in LDS, the others read from memory
 constexpr int PX_VROWS = (PX_NT - 192) / 8 / 3;   // of these, with a coarse group: one row of 8 lanes per component
 constexpr int PX_LONG = 512;               // long rows
 constexpr long long PX_WAIT = 5000000;     // 50 ms of the 100 MHz clock
@@ -86,20 +86,20 @@ __device__ __forceinline__ u64 px_ld(const u64 *p) { return __hip_atomic_load(p,
 __device__ __forceinline__ void px_st(u64 *p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void px_put(u64 *p, double v) { px_st(p, (u64)__double_as_longlong(v)); }
 
-// Poll the K words at the given places until none is empty.  Every wait
-// ends: after PX_WAIT, or once any workgroup has given up (ctl[0]), the lane
-// raises *gone and returns.
-template <int K>
-__device__ __forceinline__ void px_poll(const u64 *base, const unsigned (&at)[K], double (&v)[K], int *ctl, int *gone)
+// Poll the words ld(0) .. ld(K - 1) until none that is needed is empty.
+// Every wait ends: after PX_WAIT, or once any workgroup has given up
+// (ctl[0]), the lane raises *gone and returns.
+template <int K, class Ld, class Need>
+__device__ __forceinline__ void px_poll(Ld ld, Need need, double (&v)[K], int *ctl, int *gone)
 {
     u64 u[K];
     long long t0 = 0;
     for (int tries = 0;; ++tries) {
         bool miss = false;
 #pragma unroll
-        for (int i = 0; i < K; ++i) u[i] = px_ld(base + at[i]);
+        for (int i = 0; i < K; ++i) u[i] = px_ld(ld(i));
 #pragma unroll
-        for (int i = 0; i < K; ++i) miss |= u[i] == PX_EMPTY;
+        for (int i = 0; i < K; ++i) miss |= need(i) && u[i] == PX_EMPTY;
         if (!miss) break;
         if ((tries & 31) == 31) {
             const long long t = (long long)wall_clock64();
@@ -112,14 +112,20 @@ __device__ __forceinline__ void px_poll(const u64 *base, const unsigned (&at)[K]
         }
     }
 #pragma unroll
-    for (int i = 0; i < K; ++i) v[i] = __longlong_as_double((long long)u[i]);
+    for (int i = 0; i < K; ++i) v[i] = need(i) ? __longlong_as_double((long long)u[i]) : 0.0;
+}
+__device__ __forceinline__ double px_poll1(const u64 *p, int *ctl, int *gone)
+{
+    double v[1];
+    px_poll<1>([&](int) { return p; }, [](int) { return true; }, v, ctl, gone);
+    return v[0];
 }
 // z of a node
 __device__ __forceinline__ d3 px_poll3(const u64 *z, int node, int *ctl, int *gone)
 {
-    const unsigned o = 3u * (unsigned)node, q[3] = {o, o + 1, o + 2};
+    const u64 *const p = z + 3u * (unsigned)node;
     double v[3];
-    px_poll<3>(z, q, v, ctl, gone);
+    px_poll<3>([&](int i) { return p + i; }, [](int) { return true; }, v, ctl, gone);
     return {v[0], v[1], v[2]};
 }
 
@@ -145,25 +151,127 @@ __device__ __forceinline__ void px_acc(const double *B, d3 w, double &ax, double
 // Shared memory of one workgroup.
 template <int T>
 struct PxLds {
-    double zs[3 * (TILE * T + PX_HALO)];          // z: own nodes, then the halo
+    double zs[3 * (TILE * T + PX_HALO + 1)];      // z: own nodes, then the halo, then a zero
     double wv[3 * TILE * T];                      // A z of the own rows
-    double px[6 * TILE * T];                      // p and x of the own nodes
-    double eval[9 * PX_EXTRA_LDS];                // extra blocks
+    double px[12 * TILE * T];                     // p, x, r and s of the own nodes
+    union {                                       // (by turns, with barriers between)
+        double res[3 * (PX_EXTRA + 1)];           // the extra blocks times z, then a zero
+        double rcb[CG_N * PX_VROWS];              // group sums of the own bodies' domains
+    };
+    double pool[9 * PX_POOL];                     // extra blocks 512 ...
     double body[144 * PX_BODIES];                 // inverse blocks of the own bodies
-    double rc[CG_N], zl[CG_ROWS], rcb[CG_N * PX_VROWS], zlb[3 * PX_VROWS + 1];
+    double rc[CG_N], zl[CG_ROWS], zlb[3 * PX_VROWS + 1];
     double sh[3][8], shd[T][8], shl[3][8];
-    int esrc[PX_EXTRA];                           // extra blocks: index into the matrix, or -1 - index into the pair-local blocks
-    unsigned short eidx[PX_EXTRA];                // and their columns' places in zs
-    int hkey[PX_HASH];
-    unsigned short hslot[PX_HASH];
+    union {
+        double mi[9 * TILE * T];                  // inverse diagonal blocks of the own nodes
+        struct {
+            int key[PX_HASH];
+            unsigned short slot[PX_HASH];
+        } h;                                      // set-up only: columns of other workgroups and their places in zs
+    };
+    int esrc[PX_EXTRA];                               // extra blocks: index into the matrix, or -1 - index into the pair-local blocks
+    unsigned short eidx[PX_EXTRA];                    // and their columns' places in zs (bytes)
     int halo[PX_HALO];
-    int lidx[TILE * T];                           // own node -> its long row, or -1
+    int lidx[TILE * T];                           // own node -> where its A z travels in D (a long row, or the
+                                                  // body node that its slot stands for), or -1
     int vdom[PX_VROWS], vgrp[PX_VROWS];           // own bodies with a coarse group: its domain and group
     short vof[TILE * T];                          // own node -> its entry there, or -1
+    unsigned char kind[TILE * T], bslot[TILE * T];   // own node: 0 FEM, 1 body, 2 none, 3 stands for a body's node; its body's place
     int nhalo, nextra, nbody, nv;
     int fit;                                      // raised in the set-up: the rows do not fit
     int gone[3];                                  // raised by a poll that gave up: phases scalars and long rows, coarse, halo
 };
+
+static_assert(sizeof(PxLds<4>) <= 160 * 1024 && sizeof(PxLds<1>) > 80 * 1024, "one workgroup per compute unit");
+
+// The scalars of iteration k, alike in every thread of every workgroup: the
+// sums of bs_finish (wavefronts 0-3: r.z, 4-7: z.Az and r.r), alpha, beta and
+// the stop.  far: where this lane's node's A z travels in D (-1: nowhere);
+// it is polled with the rest.  Returns whether the wait was given up;
+// afterwards st.a is 0 when the solve has ended.
+struct PxState {
+    int a = 0, it = 0;
+    double eta = 0.0, eta2 = 0.0, gam = 0.0, al = 0.0;
+    bool indef = false;
+};
+template <int T>
+__device__ __forceinline__ bool px_scalars(const PxArgs &A, PxLds<T> &S, PxState &st, int k, int tid, int far, double &al, double &be)
+{
+    const int lane = tid & (TILE - 1), wave = tid / TILE;
+    const int DL = px_dlen(A.ntile, A.nlong, A.ncd, A.nb);
+    const int oRR = A.ntile, oZW = 2 * A.ntile, oZL = 3 * A.ntile, oCG = oZL + A.nlong;
+    const u64 *Dk = A.D + (size_t)(k % 3) * DL;
+    {
+        const int t = tid & (BLOCK - 1);
+        const bool lo = tid < BLOCK;
+        double v0, v1 = 0.0;
+        if (k == 0) {   // from the launches before this one
+            double e[2][4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = t + u * BLOCK;
+                const bool in = i < A.ntile;
+                e[0][u] = in ? (lo ? A.part[i] : A.part_zw[i]) : 0.0;
+                e[1][u] = in && !lo ? A.part[A.ntile + i] : 0.0;
+            }
+            v0 = (e[0][0] + e[0][1]) + (e[0][2] + e[0][3]);
+            v1 = (e[1][0] + e[1][1]) + (e[1][2] + e[1][3]);
+            if (lo) for (int i = t; i < A.ncd; i += BLOCK) v0 += A.cg_part[i];
+            else for (int i = t; i < A.nlong; i += BLOCK) v0 += A.part_long[i];
+        } else if (lo) {
+            // (a word past the end of its list is read from whatever
+            // follows and dropped)
+            double e[T + 4];
+            const u64 *const p = Dk + t, *const pf = Dk + max(far, 0);
+            px_poll<T + 4>([&](int i) { return i < T ? p + i * BLOCK : i == T ? p + oCG : pf + (i - T - 1); },
+                           [&](int i) { return i < T ? t + i * BLOCK < A.ntile : i == T ? t < A.ncd : far >= 0; }, e, A.ctl, &S.gone[0]);
+            if (far >= 0) st3(S.wv, tid, {e[T + 1], e[T + 2], e[T + 3]});
+            double f[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int u = 0; u < T; ++u) f[u] = e[u];
+            v0 = (f[0] + f[1]) + (f[2] + f[3]);
+            v0 += e[T];
+            for (int i = t + BLOCK; i < A.ncd; i += BLOCK) v0 += px_poll1(Dk + oCG + i, A.ctl, &S.gone[0]);
+        } else {
+            double e[2 * T + 1];
+            const u64 *const p = Dk + t;
+            px_poll<2 * T + 1>([&](int i) { return i < T ? p + oZW + i * BLOCK : i < 2 * T ? p + oRR + (i - T) * BLOCK : p + oZL; },
+                               [&](int i) { return i < 2 * T ? t + (i % T) * BLOCK < A.ntile : t < A.nlong; }, e, A.ctl, &S.gone[0]);
+            double f[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+#pragma unroll
+            for (int u = 0; u < T; ++u) { f[0][u] = e[u]; f[1][u] = e[T + u]; }
+            v0 = (f[0][0] + f[0][1]) + (f[0][2] + f[0][3]);
+            v1 = (f[1][0] + f[1][1]) + (f[1][2] + f[1][3]);
+            v0 += e[2 * T];
+            for (int i = t + BLOCK; i < A.nlong; i += BLOCK) v0 += px_poll1(Dk + oZL + i, A.ctl, &S.gone[0]);
+        }
+        v0 = wave_sum(v0);
+        if (!lo) v1 = wave_sum(v1);
+        if (lane == 0) { S.sh[0][wave] = v0; S.sh[1][wave] = v1; }
+    }
+    __syncthreads();
+    if (S.gone[0]) return true;
+    const double gam = (S.sh[0][0] + S.sh[0][1]) + (S.sh[0][2] + S.sh[0][3]);
+    const double rr = (S.sh[1][4] + S.sh[1][5]) + (S.sh[1][6] + S.sh[1][7]);
+    double del = (S.sh[0][4] + S.sh[0][5]) + (S.sh[0][6] + S.sh[0][7]);
+    be = 0.0;
+    bool go = true;
+    if (st.a == 2) {
+        st.eta2 = st.eta * st.eta * rr;
+        go = rr > 0.0;
+    } else if (rr <= st.eta2 || st.it >= A.maxit) {
+        go = false;
+    } else {
+        be = gam / st.gam;
+        del -= be * gam / st.al;
+    }
+    if (go && !(del > 0.0)) { go = false; st.indef = true; }   // not positive definite along p: stop
+    al = go ? gam / del : 0.0;
+    st.gam = gam; st.al = al;
+    st.a = go;
+    st.it += go;
+    return false;
+}
 
 template <int T, bool COARSE>
 __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
@@ -181,42 +289,46 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
 
     int tid = tid0, lane = tid & (TILE - 1), wave = tid / TILE;
     // ---- set-up ---------------------------------------------------------------
+    if (tid < 3) S.zs[3 * (OWN + PX_HALO) + tid] = 0.0;
+    if (tid < 3) S.res[3 * PX_EXTRA + tid] = 0.0;   // (past rcb)
+    static_assert(3 * PX_EXTRA >= CG_N * PX_VROWS, "the zero stays");
     if (tid == 0) { S.nhalo = 0; S.nextra = 0; S.nbody = 0; S.nv = 0; S.fit = 0; S.gone[0] = S.gone[1] = S.gone[2] = 0; }
-    for (int i = tid; i < PX_HASH; i += PX_NT) S.hkey[i] = -1;
-    for (int i = tid; i < OWN; i += PX_NT) { S.lidx[i] = -1; S.vof[i] = -1; }
+    for (int i = tid; i < PX_HASH; i += PX_NT) S.h.key[i] = -1;
     __syncthreads();
     // the own nodes (threads 0 .. OWN - 1): n
-    int n = n0 + tid;
+    const int n = n0 + tid;
     const bool own = tiles && tid < OWN && n < A.N;
-    const int kd = own ? A.kind[n] : 2;
-    const bool fem = kd == 0, bod = kd == 1;
-    d3 rv = {0, 0, 0}, sv = {0, 0, 0};
+    const int kd0 = own ? A.kind[n] : 2;
+    const bool bod = kd0 == 1;
     int ph = -1;          // COARSE: the body translation node that this padding slot stands for
-    int bslot = 0;        // own body's place in S.body
     if (COARSE && cg && tid < OWN)
         for (int u = A.ph_ptr[dom]; u < A.ph_ptr[dom + 1]; ++u)
             if (A.ph_e[u] == sl * OWN + tid) ph = A.ph_n[u];
-    if (own && kd != 2) {
-        rv = ld3(A.r0, n);
-        st3(S.zs, tid, ld3(A.z0, n));
-        st3(S.wv, tid, ld3(A.w0, n));
+    if (tid < OWN) {
+        const int src = kd0 != 2 ? n : ph;
+        S.kind[tid] = kd0 == 2 && ph >= 0 ? 3 : kd0;
+        S.bslot[tid] = 0;
+        st3(S.px, 2 * OWN + tid, src >= 0 ? ld3(A.r0, src) : d3{0, 0, 0});
+        st3(S.px, 3 * OWN + tid, {0, 0, 0});
+        st3(S.wv, tid, src >= 0 ? ld3(A.w0, src) : d3{0, 0, 0});
+        st3(S.zs, tid, kd0 != 2 ? ld3(A.z0, n) : d3{0, 0, 0});
+        S.lidx[tid] = ph >= 0 ? oWB + 3 * ((ph - A.bnode0) / 4) : -1;
+        S.vof[tid] = -1;
     }
-    if (ph >= 0) {
-        rv = ld3(A.r0, ph);
-        st3(S.wv, tid, ld3(A.w0, ph));
-    }
+    __syncthreads();
     if (tid < OWN) {
         st3(S.px, tid, {0, 0, 0});
         st3(S.px, OWN + tid, {0, 0, 0});
-        if (kd == 2) st3(S.zs, tid, {0, 0, 0});
     }
     if (bod) {
         // a body's 4 nodes are 4 lanes of one wavefront; the first takes the place
         const int a = n & 3;
+        int bslot = 0;
         if (a == 0) bslot = atomicAdd(&S.nbody, 1);
         bslot = __shfl(bslot, lane - a);
         if (bslot >= PX_BODIES) S.fit = 2;
         else {
+            S.bslot[tid] = (unsigned char)bslot;
             const double *M = A.dinvB + 144 * (size_t)A.node_body[n - a] + 36 * a;
             for (int q = 0; q < 36; ++q) S.body[144 * bslot + 36 * a + q] = M[q];
         }
@@ -232,99 +344,105 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
     }
     for (int i = tid; i < A.nlong; i += PX_NT) {
         const int q = A.long_rows[i] - n0;
-        if (tiles && q >= 0 && q < OWN) S.lidx[q] = i;
+        if (tiles && q >= 0 && q < OWN) S.lidx[q] = oWL + 3 * i;
     }
-    // the own rows (8 lanes each): collect the columns that other workgroups own
-    int rk0[T], rk1[T], rd0[T], rd1[T];
-    int sub = tid & 7;
-#pragma unroll
+    // the own rows.  A row is 8 sums as in k_spmv<8> (sum s: blocks s, s + 8,
+    // ... of the matrix, then of the pair-local blocks), and a lane takes T of
+    // them: with T < 4 one of a row in each of its tiles; with T = 4 four of
+    // one row, so that a row's sums meet in two exchanges between two lanes
+    // instead of three between eight (the cross-lane sums of 4 tiles took more
+    // issue slots than the products).  Sums 0, 1, 4, 5 in the even lane, 2, 3,
+    // 6, 7 in the odd one: interior rows of the meshes here have 19 blocks, 3
+    // in sums 0 to 2.  First collect the columns that other workgroups own.
+    constexpr bool TWO = T == 4;
+    auto sum_range = [&](int j, int &k0, int &k1, int &d0, int &d1) {   // blocks k0, k0 + 8, ... < k1 of the lane's sum j
+        const int r = n0 + (TWO ? tid >> 1 : TILE * j + tid / 8), sub = TWO ? 2 * (tid & 1) + (j & 1) + 4 * (j >> 1) : tid & 7;
+        k0 = k1 = d0 = d1 = 0;
+        if (!tiles || r >= A.N) return;
+        k0 = A.row_ptr[r]; k1 = A.row_ptr[r + 1]; d0 = A.dptr[r]; d1 = A.dptr[r + 1];
+        if ((k1 - k0) + (d1 - d0) > LONG_ROW) k1 = k0, d1 = d0;
+        k0 += sub; d0 += sub;
+    };
     for (int j = 0; j < T; ++j) {
-        const int r = n0 + TILE * j + tid / 8;
-        rk0[j] = rk1[j] = rd0[j] = rd1[j] = 0;
-        if (!tiles || r >= A.N) continue;
-        const int k0 = A.row_ptr[r], k1 = A.row_ptr[r + 1], d0 = A.dptr[r], d1 = A.dptr[r + 1];
-        if ((k1 - k0) + (d1 - d0) > LONG_ROW) continue;
-        rk0[j] = k0; rk1[j] = k1; rd0[j] = d0; rd1[j] = d1;
         auto insert = [&](int c) {
             if (c >= n0 && c < n0 + OWN) return;
             unsigned h = ((unsigned)c * 2654435761u) >> 21;
             for (int probe = 0; probe < PX_HASH; ++probe, h = (h + 1) & (PX_HASH - 1)) {
-                const int was = atomicCAS(&S.hkey[h], -1, c);
+                const int was = atomicCAS(&S.h.key[h], -1, c);
                 if (was == c) return;
                 if (was == -1) {
                     const int q = atomicAdd(&S.nhalo, 1);
-                    if (q < PX_HALO) { S.hslot[h] = (unsigned short)(OWN + q); S.halo[q] = c; }
+                    if (q < PX_HALO) { S.h.slot[h] = (unsigned short)(OWN + q); S.halo[q] = c; }
                     else S.fit = 2;
                     return;
                 }
             }
             S.fit = 2;
         };
-        for (int k = k0 + sub; k < k1; k += 8) insert(A.col[k]);
-        for (int k = d0 + sub; k < d1; k += 8) insert(A.dcol[k]);
+        int k0, k1, d0, d1;
+        sum_range(j, k0, k1, d0, d1);
+        for (int k = k0; k < k1; k += 8) insert(A.col[k]);
+        for (int k = d0; k < d1; k += 8) insert(A.dcol[k]);
     }
+    static_assert(24 * (OWN + PX_HALO + 1) < 65536, "places in zs are 16 bits");
     static_assert(PX_HASH == 2048, "the hash keeps 11 bits");
     __syncthreads();
-    // blocks into registers (each lane's first two of a row), the others into the extra list
+    // the first two blocks of every sum into registers, the rest into the extra list
     double B[T][2][9];
-    int bi[T], ex[T];   // places of the two columns; extra blocks: first | count << 16
+    int bi[T], ex[T];   // places of the two columns in zs (bytes, 16 bits each); extras: first | count << 16
     {
         auto place = [&](int c) -> int {
-            if (c >= n0 && c < n0 + OWN) return c - n0;
+            if (c >= n0 && c < n0 + OWN) return 24 * (c - n0);
             unsigned h = ((unsigned)c * 2654435761u) >> 21;
             for (int probe = 0; probe < PX_HASH; ++probe, h = (h + 1) & (PX_HASH - 1)) {
-                if (S.hkey[h] == c) return S.hslot[h];
-                if (S.hkey[h] == -1) break;
+                if (S.h.key[h] == c) return 24 * S.h.slot[h];
+                if (S.h.key[h] == -1) break;
             }
             return 0;   // only after an overflow, which has raised S.fit
         };
-        const bool ok = S.fit == 0;
 #pragma unroll
         for (int j = 0; j < T; ++j) {
-            bi[j] = 0;
+            int k0, k1, d0, d1;
+            sum_range(j, k0, k1, d0, d1);
+            bi[j] = ex[j] = 0;
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                const int k = rk0[j] + sub + 8 * u;
-                const bool in = ok && k < rk1[j];
+                const int k = k0 + 8 * u;
+                const bool in = k < k1;
                 if (in) bi[j] |= place(A.col[k]) << (16 * u);
 #pragma unroll
                 for (int q = 0; q < 9; ++q) B[j][u][q] = in ? A.val[9 * (size_t)k + q] : 0.0;
             }
-            const int ks = rk0[j] + sub + 16, ds = rd0[j] + sub;
-            const int m = (ks < rk1[j] ? (rk1[j] - ks + 7) / 8 : 0) + (ds < rd1[j] ? (rd1[j] - ds + 7) / 8 : 0);
-            int e = 0;
-            ex[j] = 0;
-            if (ok && m > 0) {
-                e = atomicAdd(&S.nextra, m);
-                if (e + m > PX_EXTRA) S.fit = 2;
+            const int ks = k0 + 16, ds = d0;
+            const int m = (ks < k1 ? (k1 - ks + 7) / 8 : 0) + (ds < d1 ? (d1 - ds + 7) / 8 : 0);
+            if (m > 0) {
+                int f = atomicAdd(&S.nextra, m);
+                if (f + m > PX_EXTRA) S.fit = 2;
                 else {
-                    ex[j] = e | m << 16;
-                    int f = e;
-                    for (int k = ks; k < rk1[j]; k += 8, ++f) { S.esrc[f] = k; S.eidx[f] = (unsigned short)place(A.col[k]); }
-                    for (int k = ds; k < rd1[j]; k += 8, ++f) { S.esrc[f] = -1 - k; S.eidx[f] = (unsigned short)place(A.dcol[k]); }
+                    ex[j] = f | m << 16;
+                    for (int k = ks; k < k1; k += 8, ++f) { S.esrc[f] = k; S.eidx[f] = (unsigned short)place(A.col[k]); }
+                    for (int k = ds; k < d1; k += 8, ++f) { S.esrc[f] = -1 - k; S.eidx[f] = (unsigned short)place(A.dcol[k]); }
                 }
             }
         }
     }
     __syncthreads();
-    for (int i = tid; i < 9 * min(S.nextra, PX_EXTRA_LDS); i += PX_NT) {
-        const int s = S.esrc[i / 9];
-        S.eval[i] = s >= 0 ? A.val[9 * (size_t)s + i % 9] : A.dval[9 * (size_t)(-1 - s) + i % 9];
-    }
-    // a long-row workgroup: its first row's first blocks, in the registers of the tiles' blocks
-    int lrow = 0, lk = 0, lk1 = 0, ld = 0, ld1 = 0, lc[2] = {-1, -1};
-    if (!tiles) {
-        lrow = A.long_rows[b - A.G];
-        const int k = A.row_ptr[lrow] + tid, d = A.dptr[lrow] + tid;
-        lk1 = A.row_ptr[lrow + 1]; ld1 = A.dptr[lrow + 1];
-        if (k < lk1) lc[0] = A.col[k];
-        if (d < ld1) lc[1] = A.dcol[d];
-        lk = k + PX_NT; ld = d + PX_NT;
+    if (own && kd0 != 2)   // over the lookup table, which no one reads any more
+        for (int q = 0; q < 9; ++q) S.mi[9 * tid + q] = A.dinv[9 * (size_t)n + q];
+    // the extra blocks: this thread's in registers, then those that LDS keeps
+    auto extra_at = [&](int e) { const int c = S.esrc[e]; return c >= 0 ? A.val + 9 * (size_t)c : A.dval + 9 * (size_t)(-1 - c); };
+    double Bx[9];
+    int zx = 0;
 #pragma unroll
-        for (int q = 0; q < 9; ++q) {
-            B[0][0][q] = lc[0] >= 0 ? A.val[9 * (size_t)k + q] : 0.0;
-            B[0][1][q] = lc[1] >= 0 ? A.dval[9 * (size_t)d + q] : 0.0;
+    for (int q = 0; q < 9; ++q) Bx[q] = 0.0;
+    if (!S.fit) {
+        if (tid < S.nextra) {
+            const double *M = extra_at(tid);
+#pragma unroll
+            for (int q = 0; q < 9; ++q) Bx[q] = M[q];
+            zx = S.eidx[tid];
         }
+        for (int i = tid; i < 9 * min(S.nextra - PX_NT, PX_POOL); i += PX_NT) S.pool[i] = extra_at(PX_NT + i / 9)[i % 9];
     }
     __syncthreads();
     if (S.fit) {   // does not fit: everybody leaves
@@ -333,154 +451,46 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
     }
 
     // ---- iterations -------------------------------------------------------------
-    int a = A.act[0], itc = 0;
-    double gam0 = 0.0, al0 = 0.0, eta2 = 0.0;
-    const double eta = A.st[2];
+    PxState st;
+    st.a = A.act[0];
+    st.eta = A.st[2];
     // Why a workgroup's threads leave together: a flag is raised only before
     // its phase's barrier (the long rows' polls share the next scalars') and
     // read only after it.
-    bool indef = false, gone = false;
-    const int li = own && kd != 2 ? S.lidx[tid] : -1;   // this node's row is a long one
-    const int phb = ph >= 0 ? (ph - A.bnode0) / 4 : -1;
-    for (int k = 0; a; ++k) {
+    bool gone = false;
+    for (int k = 0; tiles && st.a; ++k) {
         // the thread's number anew in every iteration: what is derived from it
         // is then formed where it is used instead of being kept in registers
         // that the blocks need
         tid = tid0;
         asm volatile("" : "+v"(tid));
-        lane = tid & (TILE - 1); wave = tid / TILE; n = n0 + tid; sub = tid & 7;
-        const u64 *Dk = A.D + (size_t)(k % 3) * DL;
+        lane = tid & (TILE - 1); wave = tid / TILE;
+        const int n = n0 + tid, kd = tid < OWN ? S.kind[tid] : 2, far = tid < OWN ? S.lidx[tid] : -1;
+        double al, be;
+        gone = px_scalars<T>(A, S, st, k, tid, far, al, be);
+        if (gone || !st.a) break;
         u64 *Dn = A.D + (size_t)((k + 1) % 3) * DL, *Dr = A.D + (size_t)((k + 2) % 3) * DL;
         u64 *Zk = A.Z + (size_t)(k & 1) * 3 * A.N, *Zr = A.Z + (size_t)((k + 1) & 1) * 3 * A.N;
         u64 *RCk = A.RC + (size_t)(k & 1) * CG_N * A.ndom, *RCr = A.RC + (size_t)((k + 1) & 1) * CG_N * A.ndom;
-        d3 zv = {0, 0, 0};
-        double Mi[9];   // read again every iteration (L2), behind the polls: the registers hold the blocks
-        {
-            const double *M = A.dinv + 9 * (size_t)(own ? n : 0);
-#pragma unroll
-            for (int q = 0; q < 9; ++q) Mi[q] = M[q];
-        }
-        // ---- the scalars: wavefronts 0-3 sum r.z and r.r, 4-7 z.Az (the sums of bs_finish) ----
-        {
-            const int t = tid & (BLOCK - 1);
-            double v0 = 0.0, v1 = 0.0;
-            if (k == 0) {   // from the launches before this one
-                double e[2][4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int i = t + u * BLOCK;
-                    const bool in = i < A.ntile;
-                    e[0][u] = in ? (tid < BLOCK ? A.part[i] : A.part_zw[i]) : 0.0;
-                    e[1][u] = in && tid < BLOCK ? A.part[A.ntile + i] : 0.0;
-                }
-                v0 = (e[0][0] + e[0][1]) + (e[0][2] + e[0][3]);
-                v1 = (e[1][0] + e[1][1]) + (e[1][2] + e[1][3]);
-                if (tid >= BLOCK) for (int i = t; i < A.nlong; i += BLOCK) v0 += A.part_long[i];
-                else for (int i = t; i < A.ncd; i += BLOCK) v0 += A.cg_part[i];
-            } else if (tid < BLOCK) {
-                // lanes past the end poll the first tile's word and drop it; a
-                // lane whose A z comes from a long row (or that stands for a
-                // body node) polls it with the rest
-                unsigned p[2 * T + 3];
-                double e[2 * T + 3];
-                const int far = li >= 0 ? oWL + 3 * li : phb >= 0 ? oWB + 3 * phb : -1;
-#pragma unroll
-                for (int u = 0; u < T; ++u) {
-                    const int i = t + u * BLOCK;
-                    p[2 * u] = i < A.ntile ? i : 0;
-                    p[2 * u + 1] = p[2 * u] + oRR;
-                }
-#pragma unroll
-                for (int q = 0; q < 3; ++q) p[2 * T + q] = far >= 0 ? far + q : 0;
-                px_poll<2 * T + 3>(Dk, p, e, A.ctl, &S.gone[0]);
-                if (far >= 0) st3(S.wv, tid, {e[2 * T], e[2 * T + 1], e[2 * T + 2]});
-                double f[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
-#pragma unroll
-                for (int u = 0; u < T; ++u)
-                    if (t + u * BLOCK < A.ntile) { f[0][u] = e[2 * u]; f[1][u] = e[2 * u + 1]; }
-                v0 = (f[0][0] + f[0][1]) + (f[0][2] + f[0][3]);
-                v1 = (f[1][0] + f[1][1]) + (f[1][2] + f[1][3]);
-                if (COARSE)
-                    for (int i = t; i < A.ncd; i += BLOCK) {
-                        const unsigned q[1] = {(unsigned)(oCG + i)};
-                        double c[1];
-                        px_poll<1>(Dk, q, c, A.ctl, &S.gone[0]);
-                        v0 += c[0];
-                    }
-            } else {
-                unsigned p[T];
-                double e[T], f[4] = {0, 0, 0, 0};
-#pragma unroll
-                for (int u = 0; u < T; ++u) p[u] = oZW + (t + u * BLOCK < A.ntile ? t + u * BLOCK : 0);
-                px_poll<T>(Dk, p, e, A.ctl, &S.gone[0]);
-#pragma unroll
-                for (int u = 0; u < T; ++u)
-                    if (t + u * BLOCK < A.ntile) f[u] = e[u];
-                v0 = (f[0] + f[1]) + (f[2] + f[3]);
-                for (int i = t; i < A.nlong; i += BLOCK) {
-                    const unsigned q[1] = {(unsigned)(oZL + i)};
-                    double c[1];
-                    px_poll<1>(Dk, q, c, A.ctl, &S.gone[0]);
-                    v0 += c[0];
-                }
-            }
-            v0 = wave_sum(v0);
-            if (tid < BLOCK) v1 = wave_sum(v1);
-            if (lane == 0) { S.sh[0][wave] = v0; S.sh[1][wave] = v1; }
-        }
-        __syncthreads();
-        if (S.gone[0]) { gone = true; break; }
-        const double gam = (S.sh[0][0] + S.sh[0][1]) + (S.sh[0][2] + S.sh[0][3]);
-        const double rr = (S.sh[1][0] + S.sh[1][1]) + (S.sh[1][2] + S.sh[1][3]);
-        double del = (S.sh[0][4] + S.sh[0][5]) + (S.sh[0][6] + S.sh[0][7]);
-        double be = 0.0;
-        int na = 1;
-        if (a == 2) {
-            eta2 = eta * eta * rr;
-            if (!(rr > 0.0)) na = 0;
-        } else {
-            if (rr <= eta2 || itc >= A.maxit) na = 0;
-            else {
-                be = gam / gam0;
-                del -= be * gam / al0;
-            }
-        }
-        if (na && !(del > 0.0)) { na = 0; indef = true; }
-        if (!na) { a = 0; break; }
-        const double al = gam / del;
-        gam0 = gam; al0 = al; a = 1; ++itc;
-        // ---- empty the words this workgroup writes next time ----
-        if (tiles) {
-            if (tid < T && n0 / TILE + tid < A.ntile) {
-                const int t = n0 / TILE + tid;
-                px_st(Dr + t, PX_EMPTY); px_st(Dr + oRR + t, PX_EMPTY); px_st(Dr + oZW + t, PX_EMPTY);
-            }
-            if (kd != 2)
-#pragma unroll
-                for (int q = 0; q < 3; ++q) px_st(Zr + 3 * (size_t)n + q, PX_EMPTY);
-            if (COARSE) {
-                if (cg && tid == T) px_st(Dr + oCG + CG_SPLIT * dom + sl, PX_EMPTY);
-                if (cg && tid >= TILE && tid < TILE + CG_ROWS) px_st(RCr + (size_t)CG_N * dom + CG_ROWS * sl + tid - TILE, PX_EMPTY);
-                if (bod && (n & 3) == 0 && li < 0)
-#pragma unroll
-                    for (int q = 0; q < 3; ++q) px_st(Dr + oWB + 3 * ((n - A.bnode0) / 4) + q, PX_EMPTY);
-            }
-        } else if (tid == 0) {
-            for (int i = b - A.G; i < A.nlong; i += A.nsp) {
-                px_st(Dr + oZL + i, PX_EMPTY);
-                for (int q = 0; q < 3; ++q) px_st(Dr + oWL + 3 * i + q, PX_EMPTY);
-                const int r = A.long_rows[i] - A.bnode0;
-                if (COARSE && r >= 0 && (r & 3) == 0 && r / 4 < A.nb)
-                    for (int q = 0; q < 3; ++q) px_st(Dr + oWB + 3 * (r / 4) + q, PX_EMPTY);
-            }
-        }
         // ---- the update of the own nodes (k_pcg_step) ----
-        double rz = 0.0, rr1 = 0.0;
-        if (tiles && tid < OWN) {
-            if (kd != 2 || ph >= 0) pcg_sr(ld3(S.wv, tid), al, be, sv, rv);
+        d3 zv = {0, 0, 0};
+        if (tid < OWN) {
+            d3 rv = ld3(S.px, 2 * OWN + tid), sv = ld3(S.px, 3 * OWN + tid);
+            if (kd != 2) {
+                pcg_sr(ld3(S.wv, tid), al, be, sv, rv);
+                st3(S.px, 2 * OWN + tid, rv);
+                st3(S.px, 3 * OWN + tid, sv);
+            }
+            if (COARSE && cg) {
+                const d3 v = cg_group_sum(kd == 0 || kd == 3 ? rv : d3{0, 0, 0});
+                if ((lane & (CG_AGG - 1)) == CG_AGG - 1) {
+                    u64 *p = RCk + (size_t)CG_N * dom + CG_ROWS * sl + 3 * (tid / CG_AGG);
+                    px_put(p, v.x); px_put(p + 1, v.y); px_put(p + 2, v.z);
+                }
+            }
             const d3 zo = ld3(S.zs, tid);
-            if (fem) zv = px_mat3v(Mi, rv);
-            else if (bod) {
+            if (kd == 0) zv = px_mat3v(S.mi + 9 * tid, rv);
+            else if (kd == 1) {
                 const int q4 = n & 3, first = lane - q4;
                 double rb[12];
 #pragma unroll
@@ -490,7 +500,7 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
                     rb[3 * q + 2] = __shfl(rv.z, first + q);
                 }
                 // the sums of body_rows; one row's words in registers at a time
-                const double *M = S.body + 144 * bslot + 36 * q4;
+                const double *M = S.body + 144 * S.bslot[tid] + 36 * q4;
                 double zz[3];
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
@@ -502,34 +512,43 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
                 }
                 zv = {zz[0], zz[1], zz[2]};
             }
-            if (kd != 2) {
-                rr1 = px_dt(rv, rv);
-                rz = px_dt(rv, zv);
+            double rz = 0.0, rr = 0.0;
+            if (kd < 2) {
                 if (!COARSE) {
                     u64 *Zp = Zk + 3 * (size_t)n;
                     px_put(Zp, zv.x); px_put(Zp + 1, zv.y); px_put(Zp + 2, zv.z);
                     st3(S.zs, tid, zv);
                 }
+                rr = px_dt(rv, rv);
+                rz = px_dt(rv, zv);
                 d3 pv = ld3(S.px, tid), xv = ld3(S.px, OWN + tid);
                 pv = {zo.x + be * pv.x, zo.y + be * pv.y, zo.z + be * pv.z};
                 xv = {xv.x + al * pv.x, xv.y + al * pv.y, xv.z + al * pv.z};
                 st3(S.px, tid, pv);
                 st3(S.px, OWN + tid, xv);
             }
-            if (COARSE && cg) {
-                const d3 v = cg_group_sum(fem || ph >= 0 ? rv : d3{0, 0, 0});
-                if ((lane & (CG_AGG - 1)) == CG_AGG - 1) {
-                    u64 *p = RCk + (size_t)CG_N * dom + CG_ROWS * sl + 3 * (tid / CG_AGG);
-                    px_put(p, v.x); px_put(p + 1, v.y); px_put(p + 2, v.z);
-                }
+            // empty the words written next time
+            if (kd < 2)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) px_st(Zr + 3 * (size_t)n + q, PX_EMPTY);
+            if (tid < T && n0 / TILE + tid < A.ntile) {
+                const int t = n0 / TILE + tid;
+                px_st(Dr + t, PX_EMPTY); px_st(Dr + oRR + t, PX_EMPTY); px_st(Dr + oZW + t, PX_EMPTY);
             }
-            rz = wave_sum(rz); rr1 = wave_sum(rr1);
+            if (COARSE) {
+                if (cg && tid == T) px_st(Dr + oCG + CG_SPLIT * dom + sl, PX_EMPTY);
+                if (cg && tid >= TILE && tid < TILE + CG_ROWS) px_st(RCr + (size_t)CG_N * dom + CG_ROWS * sl + tid - TILE, PX_EMPTY);
+                if (kd == 1 && (n & 3) == 0 && far < 0)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) px_st(Dr + oWB + 3 * ((n - A.bnode0) / 4) + q, PX_EMPTY);
+            }
+            rz = wave_sum(rz); rr = wave_sum(rr);
             if (lane == 0 && n0 / TILE + wave < A.ntile) {
                 px_put(Dn + n0 / TILE + wave, rz);
-                px_put(Dn + oRR + n0 / TILE + wave, rr1);
+                px_put(Dn + oRR + n0 / TILE + wave, rr);
             }
         }
-        if (COARSE && tiles) {
+        if (COARSE) {
             // the coarse correction: the rows of the domains' inverses (own
             // groups: threads 0-191; own bodies' groups: the others), from
             // the L2 while the group sums arrive: they would not fit the
@@ -544,11 +563,9 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
             for (int j = 0; j < CG_CPL; ++j) m[j] = M[cl + CG_CLANES * j];
             for (int i = tid; i < (cg ? CG_N : 0) + CG_N * S.nv; i += PX_NT) {
                 const int v = cg ? i / CG_N - 1 : i / CG_N;   // -1: the own domain
-                const unsigned q[1] = {(unsigned)(CG_N * (v < 0 ? dom : S.vdom[v]) + i % CG_N)};
-                double c[1];
-                px_poll<1>(RCk, q, c, A.ctl, &S.gone[1]);
-                if (v < 0) S.rc[i] = c[0];
-                else S.rcb[CG_N * v + i % CG_N] = c[0];
+                const double c = px_poll1(RCk + CG_N * (v < 0 ? dom : S.vdom[v]) + i % CG_N, A.ctl, &S.gone[1]);
+                if (v < 0) S.rc[i] = c;
+                else S.rcb[CG_N * v + i % CG_N] = c;
             }
             __syncthreads();
             if (S.gone[1]) { gone = true; break; }
@@ -560,8 +577,8 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
                 if (cl == 0 && crow < 3 * S.nv) S.zlb[crow] = s;
             }
             __syncthreads();
-            if (own && kd != 2) {
-                if (cg && fem) zv = {zv.x + S.zl[3 * (tid / CG_AGG)], zv.y + S.zl[3 * (tid / CG_AGG) + 1], zv.z + S.zl[3 * (tid / CG_AGG) + 2]};
+            if (kd < 2) {
+                if (cg && kd == 0) zv = {zv.x + S.zl[3 * (tid / CG_AGG)], zv.y + S.zl[3 * (tid / CG_AGG) + 1], zv.z + S.zl[3 * (tid / CG_AGG) + 2]};
                 else if (S.vof[tid] >= 0) {
                     const double *zl = S.zlb + 3 * S.vof[tid];
                     zv = {zv.x + zl[0], zv.y + zl[1], zv.z + zl[2]};
@@ -577,78 +594,147 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
             }
         }
         // ---- w = A z (k_spmv<8>) ----
-        if (tiles) {
-            for (int i = tid; i < S.nhalo; i += PX_NT) st3(S.zs, OWN + i, px_poll3(Zk, S.halo[i], A.ctl, &S.gone[2]));
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the emptying stores have completed
-            __syncthreads();
-            if (S.gone[2]) { gone = true; break; }
+        for (int i = tid; i < S.nhalo; i += PX_NT) st3(S.zs, OWN + i, px_poll3(Zk, S.halo[i], A.ctl, &S.gone[2]));
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the emptying stores have completed
+        __syncthreads();
+        if (S.gone[2]) { gone = true; break; }
+        {
+            auto z_at = [&](int o) -> d3 {
+                const double *q = (const double *)((const char *)S.zs + o);
+                return {q[0], q[1], q[2]};
+            };
+            // the blocks in registers; the extra blocks' products by all
+            // threads alike (rows in contact have dozens), to be added to
+            // their sums in order
+            double p[T][3];
 #pragma unroll
             for (int j = 0; j < T; ++j) {
-                double ax = 0.0, ay = 0.0, az = 0.0;
-                px_acc(B[j][0], ld3(S.zs, bi[j] & 0xffff), ax, ay, az);
-                px_acc(B[j][1], ld3(S.zs, bi[j] >> 16), ax, ay, az);
-                for (int e = ex[j] & 0xffff, e1 = e + (ex[j] >> 16); e < e1; ++e) {
-                    const d3 zc = ld3(S.zs, S.eidx[e]);
-                    if (e < PX_EXTRA_LDS) px_acc(S.eval + 9 * e, zc, ax, ay, az);
-                    else {
-                        const int s = S.esrc[e];
-                        px_acc(s >= 0 ? A.val + 9 * (size_t)s : A.dval + 9 * (size_t)(-1 - s), zc, ax, ay, az);
-                    }
-                }
-                ax = lane_sum<8>(ax); ay = lane_sum<8>(ay); az = lane_sum<8>(az);
-                double dot = 0.0;
-                const int q = TILE * j + tid / 8;
-                if (sub == 0 && n0 + q < A.N && S.lidx[q] < 0) {
-                    st3(S.wv, q, {ax, ay, az});
-                    dot = px_dt(ld3(S.zs, q), {ax, ay, az});
-                    if (COARSE) {
-                        const int r = n0 + q - A.bnode0;
-                        if (r >= 0 && (r & 3) == 0 && r / 4 < A.nb) {
-                            u64 *p = Dn + oWB + 3 * (r / 4);
-                            px_put(p, ax); px_put(p + 1, ay); px_put(p + 2, az);
-                        }
-                    }
-                }
-                dot = wave_sum(dot);
-                if (lane == 0) S.shd[j][wave] = dot;
+                // (opaque: the places' addresses are formed here, not kept)
+                asm volatile("" : "+v"(bi[j]), "+v"(ex[j]));
+                p[j][0] = p[j][1] = p[j][2] = 0.0;
+                px_acc(B[j][0], z_at(bi[j] & 0xffff), p[j][0], p[j][1], p[j][2]);
+                px_acc(B[j][1], z_at((unsigned)bi[j] >> 16), p[j][0], p[j][1], p[j][2]);
+                if (T > 2 && (j & 1)) asm volatile("" ::: "memory");   // four z in flight: more would not fit the registers
             }
+            asm volatile("" : "+v"(zx));
+            if (tid < S.nextra) st3(S.res, tid, px_mat3v(Bx, z_at(zx)));
+            for (int e = tid + PX_NT; e < S.nextra; e += PX_NT)
+                st3(S.res, e, px_mat3v(e < PX_NT + PX_POOL ? S.pool + 9 * (e - PX_NT) : extra_at(e), z_at(S.eidx[e])));
             __syncthreads();
-            if (tid < T && n0 / TILE + tid < A.ntile) {
-                double t = S.shd[tid][0];
-                for (int q = 1; q < 8; ++q) t += S.shd[tid][q];
-                px_put(Dn + oZW + n0 / TILE + tid, t);
+#pragma unroll
+            for (int j0 = 0; j0 < T; j0 += 2) {
+                constexpr int P = T < 2 ? T : 2;
+                int cmax = 0;
+#pragma unroll
+                for (int j = j0; j < j0 + P; ++j) cmax = max(cmax, ex[j] >> 16);
+                // (a lane that has none left adds the zero, so that no branch
+                // keeps the sums' reads from overlapping)
+                for (int x = 0; __any(x < cmax); ++x) {
+#pragma unroll
+                    for (int j = j0; j < j0 + P; ++j) {
+                        const d3 r = ld3(S.res, x < (ex[j] >> 16) ? (ex[j] & 0xffff) + x : PX_EXTRA);
+                        p[j][0] += r.x; p[j][1] += r.y; p[j][2] += r.z;
+                    }
+                }
             }
-        } else {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            // a row's A z (the tree of lane_sum<8>), its z.Az, and the tile's sum over 8 rows (wave_sum)
+            auto finish = [&](int q, bool first, d3 w) -> double {
+                if (!first || n0 + q >= A.N || S.lidx[q] >= 0) return 0.0;
+                st3(S.wv, q, w);
+                if (COARSE) {
+                    const int r = n0 + q - A.bnode0;
+                    if (r >= 0 && (r & 3) == 0 && r / 4 < A.nb) {
+                        u64 *o = Dn + oWB + 3 * (r / 4);
+                        px_put(o, w.x); px_put(o + 1, w.y); px_put(o + 2, w.z);
+                    }
+                }
+                return px_dt(ld3(S.zs, q), w);
+            };
+            if constexpr (TWO) {
+                double w[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    double u = p[0][q] + p[1][q], v = p[2][q] + p[3][q];
+                    u += dpp_d<DPP_XOR1>(u);
+                    v += dpp_d<DPP_XOR1>(v);
+                    w[q] = u + v;
+                }
+                const double dot = sum16(finish(tid >> 1, !(tid & 1), {w[0], w[1], w[2]}));
+                if ((lane & 15) == 0) S.shd[wave >> 1][4 * (wave & 1) + (lane >> 4)] = dot;
+            } else {
+#pragma unroll
+                for (int j = 0; j < T; ++j)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) p[j][q] = lane_sum<8>(p[j][q]);
+                double dot[T];
+#pragma unroll
+                for (int j = 0; j < T; ++j) dot[j] = finish(TILE * j + tid / 8, (tid & 7) == 0, {p[j][0], p[j][1], p[j][2]});
+#pragma unroll
+                for (int j = 0; j < T; ++j) dot[j] = wave_sum(dot[j]);
+#pragma unroll
+                for (int j = 0; j < T; ++j)
+                    if (lane == 0) S.shd[j][wave] = dot[j];
+            }
+        }
+        __syncthreads();
+        if (tid < T && n0 / TILE + tid < A.ntile) {
+            double t = S.shd[tid][0];
+            for (int q = 1; q < 8; ++q) t += S.shd[tid][q];
+            px_put(Dn + oZW + n0 / TILE + tid, t);
+        }
+    }
+    if (!tiles) {
+        // ---- long rows: b - G, b - G + nsp, ...; the first one's first blocks in registers ----
+        const int r0 = A.long_rows[b - A.G], e0 = A.row_ptr[r0] + tid, e1 = A.row_ptr[r0 + 1], f0 = A.dptr[r0] + tid, f1 = A.dptr[r0 + 1];
+        const int c0 = e0 < e1 ? A.col[e0] : r0, c1 = f0 < f1 ? A.dcol[f0] : r0;   // absent ones poll the row's own z
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            B[0][0][q] = e0 < e1 ? A.val[9 * (size_t)e0 + q] : 0.0;
+            B[0][1][q] = f0 < f1 ? A.dval[9 * (size_t)f0 + q] : 0.0;
+        }
+        for (int k = 0; st.a; ++k) {
+            double al, be;
+            gone = px_scalars<T>(A, S, st, k, tid, -1, al, be);
+            if (gone || !st.a) break;
+            u64 *Dn = A.D + (size_t)((k + 1) % 3) * DL, *Dr = A.D + (size_t)((k + 2) % 3) * DL;
+            const u64 *z = A.Z + (size_t)(k & 1) * 3 * A.N;
+            if (tid == 0) {
+                for (int i = b - A.G; i < A.nlong; i += A.nsp) {
+                    px_st(Dr + oZL + i, PX_EMPTY);
+                    for (int q = 0; q < 3; ++q) px_st(Dr + oWL + 3 * i + q, PX_EMPTY);
+                    const int r = A.long_rows[i] - A.bnode0;
+                    if (COARSE && r >= 0 && (r & 3) == 0 && r / 4 < A.nb)
+                        for (int q = 0; q < 3; ++q) px_st(Dr + oWB + 3 * (r / 4) + q, PX_EMPTY);
+                }
+            }
             for (int i = b - A.G; i < A.nlong; i += A.nsp) {
-                int r = lrow, k0 = lk, k1 = lk1, d0 = ld, d1 = ld1;
+                int r = r0;
                 double ax = 0.0, ay = 0.0, az = 0.0;
                 d3 zr;
-                const u64 *const z = Zk;
-                if (i == b - A.G) {   // the first blocks and the row's own z in one poll (absent ones poll the row's z too)
-                    const unsigned p = 3u * (unsigned)(lc[0] >= 0 ? lc[0] : r), pd = 3u * (unsigned)(lc[1] >= 0 ? lc[1] : r),
-                                   pr = 3u * (unsigned)r;
-                    const unsigned q[9] = {p, p + 1, p + 2, pd, pd + 1, pd + 2, pr, pr + 1, pr + 2};
+                auto rest = [&](int q, int end, const int *col, const double *val) {
+                    for (; q < end; q += PX_NT) px_acc(val + 9 * (size_t)q, px_poll3(z, col[q], A.ctl, &S.gone[0]), ax, ay, az);
+                };
+                if (i == b - A.G) {   // the first blocks' z and the row's own in one poll
+                    const u64 *const p = z + 3u * (unsigned)c0, *const pd = z + 3u * (unsigned)c1, *const pr = z + 3u * (unsigned)r;
                     double v[9];
-                    px_poll<9>(z, q, v, A.ctl, &S.gone[0]);
+                    px_poll<9>([&](int i) { return i < 3 ? p + i : i < 6 ? pd + (i - 3) : pr + (i - 6); }, [](int) { return true; }, v, A.ctl, &S.gone[0]);
                     zr = {v[6], v[7], v[8]};
-                    if (lc[0] >= 0) px_acc(B[0][0], {v[0], v[1], v[2]}, ax, ay, az);
-                    for (; k0 < k1; k0 += PX_NT) px_acc(A.val + 9 * (size_t)k0, px_poll3(z, A.col[k0], A.ctl, &S.gone[0]), ax, ay, az);
-                    if (lc[1] >= 0) px_acc(B[0][1], {v[3], v[4], v[5]}, ax, ay, az);
+                    if (e0 < e1) px_acc(B[0][0], {v[0], v[1], v[2]}, ax, ay, az);
+                    rest(e0 + PX_NT, e1, A.col, A.val);
+                    if (f0 < f1) px_acc(B[0][1], {v[3], v[4], v[5]}, ax, ay, az);
+                    rest(f0 + PX_NT, f1, A.dcol, A.dval);
                 } else {
                     r = A.long_rows[i];
-                    k0 = A.row_ptr[r] + tid; k1 = A.row_ptr[r + 1];
-                    d0 = A.dptr[r] + tid; d1 = A.dptr[r + 1];
                     zr = px_poll3(z, r, A.ctl, &S.gone[0]);
-                    for (; k0 < k1; k0 += PX_NT) px_acc(A.val + 9 * (size_t)k0, px_poll3(z, A.col[k0], A.ctl, &S.gone[0]), ax, ay, az);
+                    rest(A.row_ptr[r] + tid, A.row_ptr[r + 1], A.col, A.val);
+                    rest(A.dptr[r] + tid, A.dptr[r + 1], A.dcol, A.dval);
                 }
-                for (; d0 < d1; d0 += PX_NT) px_acc(A.dval + 9 * (size_t)d0, px_poll3(z, A.dcol[d0], A.ctl, &S.gone[0]), ax, ay, az);
                 ax = wave_sum(ax); ay = wave_sum(ay); az = wave_sum(az);
                 if (lane == 0) { S.shl[0][wave] = ax; S.shl[1][wave] = ay; S.shl[2][wave] = az; }
                 __syncthreads();
                 if (tid == 0) {
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the emptying stores have completed
                     for (int q = 1; q < 8; ++q) { ax += S.shl[0][q]; ay += S.shl[1][q]; az += S.shl[2][q]; }
-                    const d3 w = {ax, ay, az};
                     u64 *p = Dn + oWL + 3 * i;
                     px_put(p, ax); px_put(p + 1, ay); px_put(p + 2, az);
                     const int rb = r - A.bnode0;
@@ -656,7 +742,7 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
                         p = Dn + oWB + 3 * (rb / 4);
                         px_put(p, ax); px_put(p + 1, ay); px_put(p + 2, az);
                     }
-                    px_put(Dn + oZL + i, px_dt(zr, w));
+                    px_put(Dn + oZL + i, px_dt(zr, {ax, ay, az}));
                 }
                 __syncthreads();
             }
@@ -664,14 +750,14 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
     }
     // ---- the end: x, and this workgroup's vote that it has reached it ----
     if (gone) {
-        if (tid == 0) __hip_atomic_store(A.ctl, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid0 == 0) __hip_atomic_store(A.ctl, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
-    if (own && kd != 2) st3(A.x, n, ld3(S.px, OWN + tid));
-    if (tid == 0) {
+    if (own && kd0 != 2) st3(A.x, n, ld3(S.px, OWN + tid0));
+    if (tid0 == 0) {
         if (b == 0) {
-            A.iters[0] = itc;
-            if (indef) A.scal[S_INDEF] = 1.0;
+            A.iters[0] = st.it;
+            if (st.indef) A.scal[S_INDEF] = 1.0;
         }
         atomicAdd(A.ctl + 1, 1);
     }
