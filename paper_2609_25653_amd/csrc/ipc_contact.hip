@@ -76,9 +76,9 @@ __device__ __forceinline__ bool overlap(const double *a, const double *b)
     return a[0] <= b[3] && b[0] <= a[3] && a[1] <= b[4] && b[1] <= a[4] && a[2] <= b[5] && b[2] <= a[5];
 }
 
-__device__ __forceinline__ bool allowed(int oa, int ob, const int *okind, const int *excl, int nex)
+// whether objects oa and ob of kinds ka and kb (static: 2) may collide
+__device__ __forceinline__ bool allowed(int oa, int ka, int ob, int kb, const int *excl, int nex)
 {
-    int ka = oa >= 0 ? okind[oa] : 2, kb = ob >= 0 ? okind[ob] : 2;
     if (ka == 2 && kb == 2) return false;
     if (oa == ob && ka == 1) return false;
     for (int i = 0; i < nex; ++i) {
@@ -274,22 +274,56 @@ __global__ void k_node_box(int P, SegLevels L, const double *__restrict__ lev, c
     for (int m = 0; m < 6; ++m) nbox[6 * (size_t)gi + m] = acc[m];
 }
 
+// What a visit of an internal node needs, side by side, so that it costs one
+// trip to memory: both children's boxes (12 doubles) and per child {node,
+// moving} or {-1, primitive}.  Also every primitive's object and its kind
+// (4 (object + 1) + kind).
+__global__ void k_pack_nodes(int P, int kind, const int *__restrict__ left, const int *__restrict__ right, const int2 *__restrict__ range,
+                             const int *__restrict__ sorted_id, const double *__restrict__ pbox, const double *__restrict__ nbox,
+                             const int *__restrict__ nmoving, const int4 *__restrict__ tri, const int2 *__restrict__ edge,
+                             const int *__restrict__ cv_obj, const int *__restrict__ okind, double *__restrict__ cbox, int2 *__restrict__ lnk, int2 *__restrict__ rnk,
+                             int *__restrict__ pobj)
+{
+    const int gi = blockIdx.x * blockDim.x + threadIdx.x;
+    if (gi >= P) return;
+    const int o = cv_obj[kind == 0 ? tri[gi].x : edge[gi].x];
+    pobj[gi] = 4 * (o + 1) + (o >= 0 ? okind[o] : 2);
+    if (range[gi].x < 0) return;   // no internal node of this number
+    for (int c = 0; c < 2; ++c) {
+        const int x = c ? right[gi] : left[gi];
+        const int pid = x < 0 ? sorted_id[-1 - x] : 0;
+        const double *b = x < 0 ? pbox + 6 * (size_t)pid : nbox + 6 * (size_t)x;
+        for (int m = 0; m < 6; ++m) cbox[12 * (size_t)gi + 6 * c + m] = b[m];
+        (c ? rnk : lnk)[gi] = x < 0 ? make_int2(-1, pid) : make_int2(x, nmoving[x]);
+    }
+}
+
 // Queries.  kind 0: surface vertex vs triangle tree; kind 1: edge vs edge tree.
 // Thread t takes query perm[t] (Morton order).  WRITE = false counts and
 // stashes the first TRAV_STASH candidates of each query; WRITE = true writes
 // every candidate at off[q]: from the stash when it held them all, else by
 // traversing again (with stash = nullptr: always traversing).
-constexpr int TRAV_BLOCK = 128, TRAV_DEPTH = 64;
+//
+// A query that has popped TRAV_VISITS nodes gives up and goes to the wide
+// list (wide[q] = 1, its number appended to wlist): a long edge of the ground
+// or of a rigid box meets most of the tree, and one lane that walks 1500
+// nodes kept the launch waiting for 0.7 ms on a 20k-tet scene.  k_wide takes
+// those, a workgroup each.  The limit weighs the last lane's walk (about 1.2
+// us a node) against the workgroups: at 64 / 96 nodes the walk takes 100 /
+// 108 us and the wide queries 35 / 24 us on that scene, 118 / 132 and 135 /
+// 59 us on 200k tets over a fine ground.
+constexpr int TRAV_BLOCK = 128, TRAV_DEPTH = 64, TRAV_VISITS = 96;
 template <bool WRITE>
 __global__ void __launch_bounds__(TRAV_BLOCK) k_traverse(int Q, int kind, const int2 *__restrict__ qedge, const int *__restrict__ cv_scene,
                            const int4 *__restrict__ tri, const int2 *__restrict__ edge, const int *__restrict__ cv_obj,
                            const int *__restrict__ okind, const int *__restrict__ excl, int nex, const double *__restrict__ xw0,
                            const double *__restrict__ xw1, const double *__restrict__ sparam, const int *__restrict__ seg,
-                           const int *__restrict__ sorted_id, const double *__restrict__ pbox, const int *__restrict__ left,
-                           const int *__restrict__ right, const double *__restrict__ nbox, const int *__restrict__ nmoving,
+                           const double *__restrict__ cbox, const int2 *__restrict__ lnk, const int2 *__restrict__ rnk,
+                           const int *__restrict__ pobj, const int *__restrict__ nmoving, const int *__restrict__ rid,
+                           const double *__restrict__ rbox,
                            double grow, const int *__restrict__ perm,
                            int *__restrict__ count, const int *__restrict__ off, int2 *__restrict__ out, int *__restrict__ overflow,
-                           int2 *__restrict__ stash)
+                           int2 *__restrict__ stash, int *__restrict__ wide, int *__restrict__ wlist)
 {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= Q) return;
@@ -301,6 +335,7 @@ __global__ void __launch_bounds__(TRAV_BLOCK) k_traverse(int Q, int kind, const 
             for (int c = 0; c < n; ++c) out[o + c] = stash[(size_t)qi * TRAV_STASH + c];
             return;
         }
+        if (wide && wide[qi]) return;
     }
     int qv[2], nq, s;
     if (kind == 0) { qv[0] = qi; nq = 1; s = cv_scene[qi]; }
@@ -310,53 +345,214 @@ __global__ void __launch_bounds__(TRAV_BLOCK) k_traverse(int Q, int kind, const 
     box_of(xw0, xw1, qv, nq, r, qb);
     int oq = cv_obj[qv[0]];
     // a static query pairs only with moving primitives: subtrees without one are skipped
-    const bool qstatic = (oq >= 0 ? okind[oq] : 2) == 2;
+    const int kq = oq >= 0 ? okind[oq] : 2;
+    const bool qstatic = kq == 2;
     int base = seg[s], n = seg[s + 1] - base;
     int cnt = 0, w = WRITE ? off[qi] : 0;
     // traversal stack in LDS, one column per thread (a private array would
     // live in scratch memory); children are tested before they are pushed
     __shared__ int stk[TRAV_DEPTH * TRAV_BLOCK];
     int *my = stk + threadIdx.x;
-    auto leaf = [&](int pid) {
-        if (!overlap(qb, pbox + 6 * (size_t)pid)) return;
+    auto leaf = [&](int pid) {   // a leaf whose box overlaps the query's
         bool ok;
-        int ob;
+        const int ob = pobj[pid];
         if (kind == 0) {
             int4 t = tri[pid];
             ok = qi != t.x && qi != t.y && qi != t.z;
-            ob = cv_obj[t.x];
         } else {
             int2 f = edge[pid];
             ok = pid > qi && qv[0] != f.x && qv[0] != f.y && qv[1] != f.x && qv[1] != f.y;
-            ob = cv_obj[f.x];
         }
-        if (ok && allowed(oq, ob, okind, excl, nex)) {
+        if (ok && allowed(oq, kq, (ob >> 2) - 1, ob & 3, excl, nex)) {
             if (WRITE) out[w + cnt] = make_int2(qi, pid);
             else if (cnt < TRAV_STASH) stash[(size_t)qi * TRAV_STASH + cnt] = make_int2(qi, pid);
             ++cnt;
         }
     };
-    if (n == 1) leaf(sorted_id[base]);
-    else if (n > 1 && !(qstatic && !nmoving[base]) && overlap(qb, nbox + 6 * (size_t)base)) {
-        int sp = 0;
+    if (n == 1) {
+        if (overlap(qb, rbox + 6 * (size_t)base)) leaf(rid[base]);
+    } else if (n > 1 && !(qstatic && !nmoving[base])) {
+        int sp = 0, pops = 0;
         my[0] = base;
         sp = 1;
         while (sp > 0) {
-            int node = my[TRAV_BLOCK * --sp];
-            int ch[2] = {left[node], right[node]};
+            if (!WRITE && wide && ++pops > TRAV_VISITS) {
+                wide[qi] = 1;
+                wlist[atomicAdd(overflow + 2, 1)] = qi;
+                return;
+            }
+            const int node = my[TRAV_BLOCK * --sp];
+            const int2 ch[2] = {lnk[node], rnk[node]};
+            double cb[12];
+#pragma unroll
+            for (int m = 0; m < 12; ++m) cb[m] = cbox[12 * (size_t)node + m];
+#pragma unroll
             for (int c2 = 0; c2 < 2; ++c2) {
-                int x = ch[c2];
-                if (x < 0) { leaf(sorted_id[-1 - x]); continue; }
-                if (qstatic && !nmoving[x]) continue;
-                if (!overlap(qb, nbox + 6 * (size_t)x)) continue;
+                const int2 x = ch[c2];
+                if (!overlap(qb, cb + 6 * c2)) continue;
+                if (x.x < 0) { leaf(x.y); continue; }
+                if (qstatic && !x.y) continue;
                 if (sp >= TRAV_DEPTH) { atomicOr(overflow, 1); continue; }
-                my[TRAV_BLOCK * sp++] = x;
+                my[TRAV_BLOCK * sp++] = x.x;
             }
         }
     }
     if (!WRITE) {
         count[qi] = cnt;
+        if (wide) wide[qi] = 0;
         if (cnt > TRAV_STASH) atomicOr(overflow + 1, 1);
+    }
+}
+
+// ---- wide queries -----------------------------------------------------------
+// The order in which k_traverse meets a scene's leaves does not depend on
+// the query (a query only leaves subtrees out): below a node first its leaf
+// children, left then right, then the right and then the left subtree.  A
+// leaf's rank in that order, from the root down; the leaves' boxes and
+// primitives in rank order.
+__global__ void k_leaf_rank(int P, const int *__restrict__ scene_sorted, const int *__restrict__ seg, const int *__restrict__ left,
+                            const int *__restrict__ right, const int2 *__restrict__ range, const int *__restrict__ sorted_id,
+                            const double *__restrict__ pbox, int *__restrict__ rid, double *__restrict__ rbox)
+{
+    const int gi = blockIdx.x * blockDim.x + threadIdx.x;
+    if (gi >= P) return;
+    const int s = scene_sorted[gi], base = seg[s], n = seg[s + 1] - base;
+    int rank = 0;
+    for (int node = base; n > 1;) {
+        const int L = left[node], R = right[node], mine = -1 - gi;
+        if (L < 0) {
+            if (L == mine) break;
+            ++rank;
+            if (R == mine) break;
+            node = R;
+        } else if (R < 0) {
+            if (R == mine) break;
+            ++rank;
+            node = L;
+        } else {
+            const int2 rr = range[R];
+            if (gi >= rr.x) node = R;
+            else { rank += rr.y - rr.x + 1; node = L; }
+        }
+    }
+    const int pid = sorted_id[gi];
+    rid[base + rank] = pid;
+    for (int m = 0; m < 6; ++m) rbox[6 * (size_t)(base + rank) + m] = pbox[6 * (size_t)pid + m];
+}
+
+// unions over blocks of 64 consecutive ranks of a scene (one wavefront each);
+// scene s's blocks start at block seg[s] / 64 + s
+__global__ void k_rank_blocks(int ns, const int *__restrict__ seg, const double *__restrict__ rbox, double *__restrict__ bbox)
+{
+    const int w = (blockIdx.x * blockDim.x + threadIdx.x) / TILE, lane = threadIdx.x & (TILE - 1);
+    int lo = 0, hi = ns;   // the scene with seg[s] / 64 + s <= w
+    while (hi - lo > 1) {
+        const int m = (lo + hi) >> 1;
+        if (seg[m] / TILE + m <= w) lo = m; else hi = m;
+    }
+    const int i = seg[lo] + TILE * (w - (seg[lo] / TILE + lo)) + lane;
+    if (i - lane >= seg[lo + 1]) return;   // uniform: past the scene's last block
+    double b[6];
+    box_empty(b);
+    if (i < seg[lo + 1]) box_union(b, rbox + 6 * (size_t)i);
+    for (int o = 32; o > 0; o >>= 1) {
+        double c[6];
+        for (int m = 0; m < 6; ++m) c[m] = __shfl_xor(b[m], o, TILE);
+        box_union(b, c);
+    }
+    if (lane == 0) for (int m = 0; m < 6; ++m) bbox[6 * (size_t)w + m] = b[m];
+}
+
+// One workgroup per wide query: all leaves of its scene in rank order, 256
+// blocks of 64 at a time (a block whose union misses the query's box is
+// skipped), so that its candidates come in the order of the traversal.  The
+// same tests as k_traverse's leaf.  WRITE = false counts and fills the stash.
+constexpr int WIDE_BLOCK = 256, WIDE_GRID = 512;
+template <bool WRITE>
+__global__ void __launch_bounds__(WIDE_BLOCK) k_wide(int kind, const int2 *__restrict__ qedge, const int *__restrict__ cv_scene,
+                           const int4 *__restrict__ tri, const int2 *__restrict__ edge, const int *__restrict__ cv_obj,
+                           const int *__restrict__ okind, const int *__restrict__ excl, int nex, const double *__restrict__ xw0,
+                           const double *__restrict__ xw1, const double *__restrict__ sparam, const int *__restrict__ seg,
+                           const int *__restrict__ rid, const double *__restrict__ rbox, const double *__restrict__ bbox,
+                           const int *__restrict__ pobj, double grow,
+                           const int *__restrict__ nwide, const int *__restrict__ wlist, int *__restrict__ count,
+                           const int *__restrict__ off, int2 *__restrict__ out, int *__restrict__ overflow, int2 *__restrict__ stash)
+{
+    __shared__ int blk[WIDE_BLOCK], wsum[WIDE_BLOCK / TILE];
+    __shared__ unsigned long long mask[WIDE_BLOCK];
+    const int tid = threadIdx.x, lane = tid & (TILE - 1), wave = tid / TILE;
+    // exclusive sum over the workgroup's threads; every thread gets the total
+    auto scan = [&](int v, int &total) -> int {
+        int x = v;
+        for (int o = 1; o < TILE; o <<= 1) {
+            const int y = __shfl_up(x, o, TILE);
+            if (lane >= o) x += y;
+        }
+        if (lane == TILE - 1) wsum[wave] = x;
+        __syncthreads();
+        int before = 0;
+        total = 0;
+        for (int w = 0; w < WIDE_BLOCK / TILE; ++w) {
+            if (w < wave) before += wsum[w];
+            total += wsum[w];
+        }
+        __syncthreads();
+        return before + x - v;
+    };
+    for (int u = blockIdx.x; u < nwide[0]; u += gridDim.x) {
+        const int qi = wlist[u];
+        if (WRITE && count[qi] <= TRAV_STASH) continue;   // uniform: copied from the stash
+        int qv[2], nq, s;
+        if (kind == 0) { qv[0] = qi; nq = 1; s = cv_scene[qi]; }
+        else { const int2 e = qedge[qi]; qv[0] = e.x; qv[1] = e.y; nq = 2; s = cv_scene[e.x]; }
+        const double r = 1.01 * sparam[8 * s + 2] * (kind == 0 ? 1.0 : 0.5) + grow * sparam[8 * s + 2];
+        double qb[6];
+        box_of(xw0, xw1, qv, nq, r, qb);
+        const int oq = cv_obj[qv[0]], kq = oq >= 0 ? okind[oq] : 2;
+        const int base = seg[s], n = seg[s + 1] - base, b0 = base / TILE + s, nb = (n + TILE - 1) / TILE;
+        int done = 0;   // candidates so far
+        for (int c0 = 0; c0 < nb; c0 += WIDE_BLOCK) {
+            const bool hit = c0 + tid < nb && overlap(qb, bbox + 6 * (size_t)(b0 + c0 + tid));
+            int nhit;
+            const int at = scan(hit, nhit);
+            if (hit) blk[at] = c0 + tid;
+            __syncthreads();
+            for (int h = wave; h < nhit; h += WIDE_BLOCK / TILE) {
+                const int i = TILE * blk[h] + lane;
+                bool ok = i < n && overlap(qb, rbox + 6 * (size_t)(base + min(i, n - 1)));
+                if (ok) {
+                    const int pid = rid[base + i];
+                    const int ob = pobj[pid];
+                    if (kind == 0) {
+                        const int4 t = tri[pid];
+                        ok = qi != t.x && qi != t.y && qi != t.z;
+                    } else {
+                        const int2 f = edge[pid];
+                        ok = pid > qi && qv[0] != f.x && qv[0] != f.y && qv[1] != f.x && qv[1] != f.y;
+                    }
+                    ok = ok && allowed(oq, kq, (ob >> 2) - 1, ob & 3, excl, nex);
+                }
+                const unsigned long long m = __ballot(ok);
+                if (lane == 0) mask[h] = m;
+            }
+            __syncthreads();
+            int found;
+            const int first = scan(tid < nhit ? __popcll(mask[tid]) : 0, found);
+            if (tid < nhit) {
+                int o = done + first;
+                for (unsigned long long m = mask[tid]; m; m &= m - 1, ++o) {
+                    const int2 c = make_int2(qi, rid[base + TILE * blk[tid] + __ffsll((long long)m) - 1]);
+                    if (WRITE) out[off[qi] + o] = c;
+                    else if (o < TRAV_STASH) stash[(size_t)qi * TRAV_STASH + o] = c;
+                }
+            }
+            done += found;
+            __syncthreads();
+        }
+        if (!WRITE && tid == 0) {
+            count[qi] = done;
+            if (done > TRAV_STASH) atomicOr(overflow + 1, 1);
+        }
     }
 }
 
@@ -477,9 +673,27 @@ static void bvh_query(ipc_ctx *c, int kind, const double *xw0, const double *xw1
         hipLaunchKernelGGL(k_seg_up, dim3(blocks_for(SL.size[j0], 256)), dim3(256), 0, st, SL, j0, D.bvh_lev.p);
     hipLaunchKernelGGL(k_node_box, dim3(blocks_for(P)), dim3(BLOCK), 0, st, P, SL, D.bvh_lev.p, D.bvh_range.p, D.bvh_mscan.p,
                        D.bvh_box.p, D.bvh_nmoving.p);
-    DBuf<int> &ovf = D.woff;
-    ovf.alloc(2);
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, 2, ovf.p, 0);
+    DBuf<int> &ovf = D.woff;   // stack overflow, stash overflow, number of wide queries
+    ovf.alloc(3);
+    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, 3, ovf.p, 0);
+    // For the traversal, over buffers that are free by now: the nodes'
+    // children (the union tree's memory, the keys'), the primitives' objects
+    // (the flags' scan); for the wide queries the leaves in traversal order
+    // (the node boxes, the unsorted ids) and their blocks (the primitive
+    // boxes, unless many tiny scenes need more blocks than they have room).
+    const int nblk = P / TILE + ns + 1;
+    D.qkey.alloc(Q); D.qid.alloc(Q);
+    double *cbox = D.bvh_lev.p, *rbox = D.bvh_box.p, *bbox = D.box.p;
+    int2 *lnk = (int2 *)D.mkey.p, *rnk = (int2 *)D.mkey2.p;
+    const bool wide_ok = nblk <= P;
+    int *pobj = D.bvh_mscan.p, *rid = D.mid.p, *wide = wide_ok ? D.qid.p : nullptr, *wlist = (int *)D.qkey.p;
+    hipLaunchKernelGGL(k_pack_nodes, dim3(blocks_for(P)), dim3(BLOCK), 0, st, P, kind, D.bvh_left.p, D.bvh_right.p, D.bvh_range.p, D.mid2.p,
+                       D.box.p, D.bvh_box.p, D.bvh_nmoving.p, D.tri.p, D.edge.p, D.cv_obj.p, D.obj_kind.p,
+                       cbox, lnk, rnk, pobj);
+    hipLaunchKernelGGL(k_leaf_rank, dim3(blocks_for(P)), dim3(BLOCK), 0, st, P, scene_sorted, pseg_d, D.bvh_left.p, D.bvh_right.p,
+                       D.bvh_range.p, D.mid2.p, D.box.p, rid, rbox);
+    if (wide_ok)
+        hipLaunchKernelGGL(k_rank_blocks, dim3(blocks_for((int64_t)nblk * TILE)), dim3(BLOCK), 0, st, ns, pseg_d, rbox, bbox);
     const int2 *qedge = D.edge.p;
     // query order: edges in their own tree's sorted order; surface vertices by their own Morton keys
     const int *perm = D.mid2.p;
@@ -493,8 +707,12 @@ static void bvh_query(ipc_ctx *c, int kind, const double *xw0, const double *xw1
         perm = D.qperm.p;
     }
     hipLaunchKernelGGL(k_traverse<false>, dim3(blocks_for(Q, TRAV_BLOCK)), dim3(TRAV_BLOCK), 0, st, Q, kind, qedge, D.cv_scene.p, D.tri.p, D.edge.p,
-                       D.cv_obj.p, D.obj_kind.p, D.excl.p, c->NEX, xw0, xw1, D.sparam.p, pseg_d, D.mid2.p, D.box.p, D.bvh_left.p,
-                       D.bvh_right.p, D.bvh_box.p, D.bvh_nmoving.p, grow, perm, D.qcount.p, nullptr, nullptr, ovf.p, D.qstash.p);
+                       D.cv_obj.p, D.obj_kind.p, D.excl.p, c->NEX, xw0, xw1, D.sparam.p, pseg_d, cbox, lnk, rnk, pobj, D.bvh_nmoving.p,
+                       rid, rbox, grow, perm, D.qcount.p, nullptr, nullptr, ovf.p, D.qstash.p, wide, wlist);
+    if (wide)
+        hipLaunchKernelGGL(k_wide<false>, dim3(std::min(Q, WIDE_GRID)), dim3(WIDE_BLOCK), 0, st, kind, qedge, D.cv_scene.p, D.tri.p,
+                           D.edge.p, D.cv_obj.p, D.obj_kind.p, D.excl.p, c->NEX, xw0, xw1, D.sparam.p, pseg_d, rid, rbox, bbox, pobj, grow,
+                           ovf.p + 2, wlist, D.qcount.p, nullptr, nullptr, ovf.p, D.qstash.p);
     hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, 1, D.qcount.p + Q, 0);
     exclusive_scan(c, D.qcount.p, D.qoff.p, Q);
     // the candidates' per-scene segments go straight to the device table
@@ -518,10 +736,16 @@ static void bvh_query(ipc_ctx *c, int kind, const double *xw0, const double *xw1
     count = total;
     if (!of[1])
         hipLaunchKernelGGL(k_unstash, dim3(blocks_for(Q)), dim3(BLOCK), 0, st, Q, D.qcount.p, D.qoff.p, D.qstash.p, outbuf.p);
-    else   // queries whose candidates did not fit the stash traverse again
+    else {   // queries whose candidates did not fit the stash traverse again
         hipLaunchKernelGGL(k_traverse<true>, dim3(blocks_for(Q, TRAV_BLOCK)), dim3(TRAV_BLOCK), 0, st, Q, kind, qedge, D.cv_scene.p,
-                           D.tri.p, D.edge.p, D.cv_obj.p, D.obj_kind.p, D.excl.p, c->NEX, xw0, xw1, D.sparam.p, pseg_d, D.mid2.p,
-                           D.box.p, D.bvh_left.p, D.bvh_right.p, D.bvh_box.p, D.bvh_nmoving.p, grow, perm, D.qcount.p, D.qoff.p, outbuf.p, ovf.p, D.qstash.p);
+                           D.tri.p, D.edge.p, D.cv_obj.p, D.obj_kind.p, D.excl.p, c->NEX, xw0, xw1, D.sparam.p, pseg_d, cbox, lnk, rnk,
+                           pobj, D.bvh_nmoving.p, rid, rbox, grow, perm, D.qcount.p, D.qoff.p, outbuf.p, ovf.p, D.qstash.p,
+                           wide, wlist);
+        if (wide)
+            hipLaunchKernelGGL(k_wide<true>, dim3(std::min(Q, WIDE_GRID)), dim3(WIDE_BLOCK), 0, st, kind, qedge, D.cv_scene.p, D.tri.p,
+                               D.edge.p, D.cv_obj.p, D.obj_kind.p, D.excl.p, c->NEX, xw0, xw1, D.sparam.p, pseg_d, rid, rbox, bbox, pobj, grow,
+                               ovf.p + 2, wlist, D.qcount.p, D.qoff.p, outbuf.p, ovf.p, D.qstash.p);
+    }
 }
 
 void broad_phase(ipc_ctx *c, const double *xw0, const double *xw1, double grow)
