@@ -161,9 +161,10 @@ enum {
                               at ipc_create, keeps it in a launch of its own).
                               Both forms give the same bits.                  */
     IPC_Q_PCG_RESIDENT = 16 /* PCG solves of this context so far whose iterations
-                              all ran in one launch (one scene that fits the
-                              chip; also the same bits; IPC_NO_GRAPH = 1 and
-                              IPC_NO_FUSED_PCG = 1 keep it off)               */
+                              all ran inside one launch per group of scenes
+                              (every scene fits the chip; also the same bits;
+                              IPC_NO_GRAPH = 1 and IPC_NO_FUSED_PCG = 1 keep
+                              it off)                                         */
 };
 
 /* Flags of ipc_energy_grad_hess. */
@@ -374,7 +375,7 @@ int ipc_time_kernel(ipc_ctx *ctx, int kernel, int reps, double *avg_us, double *
  * (nullable) the choice.  The default before any call is 8 lanes; the
  * environment variable IPC_SPMV_LANES (1, 2, 4, 8 or 16), read at
  * ipc_create, fixes the count instead: the autotuner still times every
- * count but keeps that one.  A one-scene context that takes its PCG
+ * count but keeps that one.  A context that takes its PCG
  * solves in one launch (IPC_Q_PCG_RESIDENT) keeps 8 lanes, whose sums that
  * launch forms, unless the variable fixes another count.  Otherwise the choice is also kept for the
  * process, keyed by the context's size bucket (the powers of two of the

@@ -1193,7 +1193,7 @@ void newton_step(ipc_ctx *c, const double *targets_dev, ipc_stats *stats)
             build_preconditioner(c);
         }
         hipLaunchKernelGGL(k_negate, dim3(blocks_for(3 * (int64_t)c->N)), dim3(BLOCK), 0, st, 3 * (int64_t)c->N, D.g.p, D.v1.p);
-        pcg_solve(c, D.v1.p, D.x.p, -1.0, D.newton_on.p);
+        pcg_solve(c, D.v1.p, D.x.p, -1.0, D.newton_on.p, on.data());
         std::vector<int> it(ns);
         // the trial point y + p (step 1) and world positions at both ends,
         // and whether the kept candidates still cover that sweep; read

@@ -41,7 +41,7 @@ void coarse_setup(ipc_ctx *c)
     c->seg_cdom.assign(ns + 1, 0);
     std::vector<int> ent, nodes, dom_scene, grp, node_da(c->N, -1);
     int ndom = 0;
-    bool windows = ns == 1;
+    bool windows = ns == 1;   // one scene at node 0 (the one-launch PCG step)
     for (int s = 0; s < ns; ++s) {
         c->seg_cdom[s] = ndom;
         if (!c->coarse) continue;
@@ -83,19 +83,20 @@ void coarse_setup(ipc_ctx *c)
             for (int e = ent[d]; e < ent[d + 1]; ++e) pn[(size_t)d * CG_AGG * CG_DOM + (e - ent[d])] = nodes[e];
         D.cg_pnodes.upload(pn, c->stream);
     }
-    {   // one scene: per domain the entries whose slot stands for a body's translation node
+    {   // per domain the entries whose slot stands for a body's translation node
         std::vector<int> ph_ptr(ndom + 1, 0), ph_e, ph_n;
-        if (c->cg_fusable) {
-            const SceneInfo &S = c->sc[0];
-            c->cg_nfr = (int)S.entry.size();
-            for (int m = 0; m < c->cg_nfr; ++m)
+        if (c->cg_fusable) c->cg_nfr = (int)c->sc[0].entry.size();
+        c->cg_windows = ndom > 0;
+        for (int s = 0; s < ns && ndom > 0; ++s) {
+            const SceneInfo &S = c->sc[s];
+            for (int m = 0; m < (int)S.entry.size(); ++m)
                 if (S.entry[m] < 0) {
-                    ph_ptr[m / (CG_AGG * CG_DOM) + 1]++;
+                    ph_ptr[c->seg_cdom[s] + m / (CG_AGG * CG_DOM) + 1]++;
                     ph_e.push_back(m % (CG_AGG * CG_DOM));
                     ph_n.push_back(S.bnode0 + 4 * (-1 - S.entry[m]));
                 }
-            for (int d = 0; d < ndom; ++d) ph_ptr[d + 1] += ph_ptr[d];
         }
+        for (int d = 0; d < ndom; ++d) ph_ptr[d + 1] += ph_ptr[d];
         D.cg_ph_ptr.upload(ph_ptr, c->stream);
         D.cg_ph_e.upload(ph_e.empty() ? std::vector<int>(1, 0) : ph_e, c->stream);
         D.cg_ph_n.upload(ph_n.empty() ? std::vector<int>(1, 0) : ph_n, c->stream);

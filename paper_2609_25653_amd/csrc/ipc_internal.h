@@ -346,6 +346,7 @@ struct Dev {
     DBuf<int> pcg_act, pcg_it;
     DBuf<unsigned long long> px_words;     // one-launch solve: the words its workgroups exchange
     DBuf<int> px_ctl;                      // its abort word and count of workgroups at their end
+    DBuf<int> px_scene, px_wg;             // its scenes' ranges; its workgroups' parts
     DBuf<int> pair_flag, lag_flag;         // 1: the pair's blocks were merged into the matrix
     DBuf<int> tickets;                     // small device counters
     DBuf<double> grav;
@@ -386,6 +387,7 @@ struct ipc_ctx {
     bool coarse = true;                   // coarse domains built (the PCG preconditioner's correction)
     bool coarse_on = false;               // the PCG applies the coarse correction
     bool coarse_forced = false;           // on by request, whatever the size
+    bool cg_windows = false;              // every scene's domains are runs of its nodes (the one-launch solve's slices)
     bool cg_fusable = false;              // one scene whose domains match the step's workgroups (see coarse_setup)
     int cg_nfr = 0;                       // its entries (FEM vertices and body translations)
     bool pcg_fused = true;                // IPC_NO_FUSED_PCG unset: a fusable context applies its coarse
@@ -484,15 +486,19 @@ void coarse_setup(ipc_ctx *c);
 void coarse_build(ipc_ctx *c);
 void coarse_apply(ipc_ctx *c, const int *act, const double *r, double *z, int parity);
 
-void pcg_solve(ipc_ctx *c, const double *b, double *x, double eta, const int *want);
+// want (device) and on (host): the scenes to solve for (null: all)
+void pcg_solve(ipc_ctx *c, const double *b, double *x, double eta, const int *want, const int *on = nullptr);
 // The host's progress words: ready for use; the next sequence number; wait
 // for n words of that number in a slot and return the largest value.
 void pcg_peek_ready(ipc_ctx *c);
 unsigned int pcg_next_seq(ipc_ctx *c);
 int pcg_await(ipc_ctx *c, int slot, unsigned int seq, int n);
-// The iterations of a one-scene solve in one launch, after the first r, z,
-// w and partials are formed; false: not taken, nothing of these has changed.
-bool pcg_resident(ipc_ctx *c, double *x);
+// The iterations of a solve in one launch per group of scenes, after the
+// first r, z, w and partials are formed.  on (host, nullable): the scenes
+// that are solved for.  NO: not taken, nothing has changed; FAILED: x and the
+// scenes' counts may have, start again.
+enum PcgResident { PCG_RESIDENT_NO, PCG_RESIDENT_DONE, PCG_RESIDENT_FAILED };
+PcgResident pcg_resident(ipc_ctx *c, double *x, const int *on);
 void pcg_resident_setup(ipc_ctx *c);
 size_t pcg_resident_bytes(int n_scenes, int N, int NB);   // its memory in a workspace
 // exclusive scan of n ints into out[0..n] (out[n] = total), on the context's stream

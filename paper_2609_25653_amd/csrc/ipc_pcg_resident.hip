@@ -64,14 +64,24 @@ constexpr int PX_EXTRA = 1536;             // blocks past the two in registers, 
                                            // registers too, one per thread,
 constexpr int PX_POOL = 128;               // the next ones in LDS, the others read from memory
 constexpr int PX_VROWS = (PX_NT - 192) / 8 / 3;   // of these, with a coarse group: one row of 8 lanes per component
-constexpr int PX_LONG = 512;               // long rows
+constexpr int PX_LONG = 512;               // long rows per scene (on average)
+constexpr int PX_SPARE = 16;               // workgroups kept free of tiles for them
+constexpr int PX_WGMAX = 256;              // workgroups per launch (compute units)
 constexpr long long PX_WAIT = 5000000;     // 50 ms of the 100 MHz clock
 
+// A scene's ranges: nodes, tiles, coarse domains, bodies, first body node
+struct PxScene { int node0, ntile, tile0, dom0, ndom, body0, nb, bnode0, maxit; };
+// A workgroup's part: its scene; tiles T tile .. T tile + T - 1 of it, or
+// (tile < 0) long rows spare, spare + nsp, ... of it
+struct PxPart { int scene, tile, spare, nsp; };
+// All scenes' arrays; the kernel moves them to its scene's part first.
 struct PxArgs {
-    int N, ntile, G, nsp, nlong, nb, ncd, ndom, nfr, bnode0, maxit;
-    const int *kind, *node_body, *row_ptr, *col, *dptr, *dcol, *long_rows, *node_da;
+    int N, ntile, nlong, nb, ncd, ndom, ndom_all, bnode0, maxit;
+    const PxScene *scene;
+    const PxPart *wg;
+    const int *seg_long, *kind, *node_body, *row_ptr, *col, *dptr, *dcol, *long_rows, *node_da;
     const double *val, *dval, *dinv, *dinvB, *inv, *r0, *z0, *w0;
-    const double *part, *part_zw, *part_long, *cg_part, *st;
+    const double *part, *part_rr, *part_zw, *part_long, *cg_part, *st;
     const int *act, *ph_ptr, *ph_e, *ph_n;
     double *x, *scal;
     int *iters, *ctl;
@@ -212,7 +222,7 @@ __device__ __forceinline__ bool px_scalars(const PxArgs &A, PxLds<T> &S, PxState
                 const int i = t + u * BLOCK;
                 const bool in = i < A.ntile;
                 e[0][u] = in ? (lo ? A.part[i] : A.part_zw[i]) : 0.0;
-                e[1][u] = in && !lo ? A.part[A.ntile + i] : 0.0;
+                e[1][u] = in && !lo ? A.part_rr[i] : 0.0;
             }
             v0 = (e[0][0] + e[0][1]) + (e[0][2] + e[0][3]);
             v1 = (e[1][0] + e[1][1]) + (e[1][2] + e[1][3]);
@@ -279,9 +289,26 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
     extern __shared__ double px_smem[];
     PxLds<T> &S = *reinterpret_cast<PxLds<T> *>(px_smem);
     constexpr int OWN = TILE * T;
-    const int tid0 = threadIdx.x, b = blockIdx.x;
-    const bool tiles = b < A.G;                 // a workgroup of tiles, else one of long rows
-    const int n0 = tiles ? b * OWN : 0;         // first own node
+    const int tid0 = threadIdx.x;
+    const PxPart me = A.wg[blockIdx.x];
+    const PxScene Q = A.scene[me.scene];
+    {
+        const int l0 = A.seg_long[me.scene];
+        A.nlong = A.seg_long[me.scene + 1] - l0;
+        A.ntile = Q.ntile; A.nb = Q.nb; A.bnode0 = Q.bnode0; A.maxit = Q.maxit;
+        A.ndom = COARSE ? Q.ndom : 0; A.ncd = CG_SPLIT * A.ndom;
+        A.D += 3 * (size_t)px_dlen(Q.tile0, l0, COARSE ? CG_SPLIT * Q.dom0 : 0, Q.body0);
+        A.part += Q.tile0; A.part_rr += Q.tile0; A.part_zw += Q.tile0; A.part_long += l0; A.long_rows += l0;
+        A.st += 4 * (size_t)me.scene; A.act += me.scene; A.iters += me.scene; A.scal += (size_t)me.scene * NSLOT;
+        if (COARSE) {
+            A.cg_part += CG_SPLIT * Q.dom0; A.ph_ptr += Q.dom0; A.RC += (size_t)CG_N * Q.dom0;
+            A.inv += (size_t)Q.dom0 * CG_N * CG_N;
+        }
+    }
+    const bool tiles = me.tile >= 0;            // a workgroup of tiles, else one of long rows
+    const int b = me.tile;
+    const int n0 = tiles ? Q.node0 + b * OWN : 0, nend = Q.node0 + TILE * Q.ntile;   // own nodes from n0, before the scene's end
+    const int lt0 = b * T;                      // the first own tile among the scene's
     const int dom = b / CG_SPLIT, sl = b % CG_SPLIT;
     const bool cg = COARSE && tiles && dom < A.ndom;
     const int DL = px_dlen(A.ntile, A.nlong, A.ncd, A.nb);
@@ -297,7 +324,7 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
     __syncthreads();
     // the own nodes (threads 0 .. OWN - 1): n
     const int n = n0 + tid;
-    const bool own = tiles && tid < OWN && n < A.N;
+    const bool own = tiles && tid < OWN && n < nend;
     const int kd0 = own ? A.kind[n] : 2;
     const bool bod = kd0 == 1;
     int ph = -1;          // COARSE: the body translation node that this padding slot stands for
@@ -337,7 +364,7 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
             if (v >= PX_VROWS) S.fit = 2;
             else {
                 S.vof[tid] = (short)v;
-                S.vdom[v] = A.node_da[n] / CG_DOM;
+                S.vdom[v] = A.node_da[n] / CG_DOM - Q.dom0;
                 S.vgrp[v] = A.node_da[n] % CG_DOM;
             }
         }
@@ -358,7 +385,7 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
     auto sum_range = [&](int j, int &k0, int &k1, int &d0, int &d1) {   // blocks k0, k0 + 8, ... < k1 of the lane's sum j
         const int r = n0 + (TWO ? tid >> 1 : TILE * j + tid / 8), sub = TWO ? 2 * (tid & 1) + (j & 1) + 4 * (j >> 1) : tid & 7;
         k0 = k1 = d0 = d1 = 0;
-        if (!tiles || r >= A.N) return;
+        if (!tiles || r >= nend) return;
         k0 = A.row_ptr[r]; k1 = A.row_ptr[r + 1]; d0 = A.dptr[r]; d1 = A.dptr[r + 1];
         if ((k1 - k0) + (d1 - d0) > LONG_ROW) k1 = k0, d1 = d0;
         k0 += sub; d0 += sub;
@@ -471,7 +498,7 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
         if (gone || !st.a) break;
         u64 *Dn = A.D + (size_t)((k + 1) % 3) * DL, *Dr = A.D + (size_t)((k + 2) % 3) * DL;
         u64 *Zk = A.Z + (size_t)(k & 1) * 3 * A.N, *Zr = A.Z + (size_t)((k + 1) & 1) * 3 * A.N;
-        u64 *RCk = A.RC + (size_t)(k & 1) * CG_N * A.ndom, *RCr = A.RC + (size_t)((k + 1) & 1) * CG_N * A.ndom;
+        u64 *RCk = A.RC + (size_t)(k & 1) * CG_N * A.ndom_all, *RCr = A.RC + (size_t)((k + 1) & 1) * CG_N * A.ndom_all;
         // ---- the update of the own nodes (k_pcg_step) ----
         d3 zv = {0, 0, 0};
         if (tid < OWN) {
@@ -531,8 +558,8 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
             if (kd < 2)
 #pragma unroll
                 for (int q = 0; q < 3; ++q) px_st(Zr + 3 * (size_t)n + q, PX_EMPTY);
-            if (tid < T && n0 / TILE + tid < A.ntile) {
-                const int t = n0 / TILE + tid;
+            if (tid < T && lt0 + tid < A.ntile) {
+                const int t = lt0 + tid;
                 px_st(Dr + t, PX_EMPTY); px_st(Dr + oRR + t, PX_EMPTY); px_st(Dr + oZW + t, PX_EMPTY);
             }
             if (COARSE) {
@@ -543,9 +570,9 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
                     for (int q = 0; q < 3; ++q) px_st(Dr + oWB + 3 * ((n - A.bnode0) / 4) + q, PX_EMPTY);
             }
             rz = wave_sum(rz); rr = wave_sum(rr);
-            if (lane == 0 && n0 / TILE + wave < A.ntile) {
-                px_put(Dn + n0 / TILE + wave, rz);
-                px_put(Dn + oRR + n0 / TILE + wave, rr);
+            if (lane == 0 && lt0 + wave < A.ntile) {
+                px_put(Dn + lt0 + wave, rz);
+                px_put(Dn + oRR + lt0 + wave, rr);
             }
         }
         if (COARSE) {
@@ -639,7 +666,7 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
             }
             // a row's A z (the tree of lane_sum<8>), its z.Az, and the tile's sum over 8 rows (wave_sum)
             auto finish = [&](int q, bool first, d3 w) -> double {
-                if (!first || n0 + q >= A.N || S.lidx[q] >= 0) return 0.0;
+                if (!first || n0 + q >= nend || S.lidx[q] >= 0) return 0.0;
                 st3(S.wv, q, w);
                 if (COARSE) {
                     const int r = n0 + q - A.bnode0;
@@ -677,15 +704,15 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
             }
         }
         __syncthreads();
-        if (tid < T && n0 / TILE + tid < A.ntile) {
+        if (tid < T && lt0 + tid < A.ntile) {
             double t = S.shd[tid][0];
             for (int q = 1; q < 8; ++q) t += S.shd[tid][q];
-            px_put(Dn + oZW + n0 / TILE + tid, t);
+            px_put(Dn + oZW + lt0 + tid, t);
         }
     }
-    if (!tiles) {
-        // ---- long rows: b - G, b - G + nsp, ...; the first one's first blocks in registers ----
-        const int r0 = A.long_rows[b - A.G], e0 = A.row_ptr[r0] + tid, e1 = A.row_ptr[r0 + 1], f0 = A.dptr[r0] + tid, f1 = A.dptr[r0 + 1];
+    if (!tiles && me.spare < A.nlong) {
+        // ---- long rows spare, spare + nsp, ...; the first one's first blocks in registers ----
+        const int r0 = A.long_rows[me.spare], e0 = A.row_ptr[r0] + tid, e1 = A.row_ptr[r0 + 1], f0 = A.dptr[r0] + tid, f1 = A.dptr[r0 + 1];
         const int c0 = e0 < e1 ? A.col[e0] : r0, c1 = f0 < f1 ? A.dcol[f0] : r0;   // absent ones poll the row's own z
 #pragma unroll
         for (int q = 0; q < 9; ++q) {
@@ -699,7 +726,7 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
             u64 *Dn = A.D + (size_t)((k + 1) % 3) * DL, *Dr = A.D + (size_t)((k + 2) % 3) * DL;
             const u64 *z = A.Z + (size_t)(k & 1) * 3 * A.N;
             if (tid == 0) {
-                for (int i = b - A.G; i < A.nlong; i += A.nsp) {
+                for (int i = me.spare; i < A.nlong; i += me.nsp) {
                     px_st(Dr + oZL + i, PX_EMPTY);
                     for (int q = 0; q < 3; ++q) px_st(Dr + oWL + 3 * i + q, PX_EMPTY);
                     const int r = A.long_rows[i] - A.bnode0;
@@ -707,14 +734,14 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
                         for (int q = 0; q < 3; ++q) px_st(Dr + oWB + 3 * (r / 4) + q, PX_EMPTY);
                 }
             }
-            for (int i = b - A.G; i < A.nlong; i += A.nsp) {
+            for (int i = me.spare; i < A.nlong; i += me.nsp) {
                 int r = r0;
                 double ax = 0.0, ay = 0.0, az = 0.0;
                 d3 zr;
                 auto rest = [&](int q, int end, const int *col, const double *val) {
                     for (; q < end; q += PX_NT) px_acc(val + 9 * (size_t)q, px_poll3(z, col[q], A.ctl, &S.gone[0]), ax, ay, az);
                 };
-                if (i == b - A.G) {   // the first blocks' z and the row's own in one poll
+                if (i == me.spare) {   // the first blocks' z and the row's own in one poll
                     const u64 *const p = z + 3u * (unsigned)c0, *const pd = z + 3u * (unsigned)c1, *const pr = z + 3u * (unsigned)r;
                     double v[9];
                     px_poll<9>([&](int i) { return i < 3 ? p + i : i < 6 ? pd + (i - 3) : pr + (i - 6); }, [](int) { return true; }, v, A.ctl, &S.gone[0]);
@@ -784,43 +811,6 @@ static void px_launch(const PxArgs &A, int wgs, hipStream_t st)
     hipLaunchKernelGGL((k_pcg_resident<T, COARSE>), dim3(wgs), dim3(PX_NT), sizeof(PxLds<T>), st, A);
 }
 
-// tiles per workgroup and workgroups, or T = 0: not for this context
-struct PxShape { int T = 0, G = 0, nsp = 0; };
-static PxShape px_shape(const ipc_ctx *c)
-{
-    PxShape s;
-    const int ntile = c->N / TILE, cu = c->n_cu;
-    const bool coarse = c->coarse_on && c->n_cdom > 0;
-    if (c->n_scenes != 1 || c->spmv_lanes != 8 || !c->use_graphs || c->prof || !c->pcg_fused || c->n_long > PX_LONG || !c->resident_ok) return s;
-    if (coarse && (!c->cg_fusable || c->n_cdom * CG_SPLIT > BLOCK * 4)) return s;
-    const int room = cu - std::min(c->n_long, 16);   // units left for tiles
-    int T, G;
-    if (coarse) {
-        T = 4;
-        G = std::max(CG_SPLIT * c->n_cdom, (ntile + T - 1) / T);
-    } else {
-        T = ntile <= std::min(room, BLOCK) ? 1 : ntile <= 2 * std::min(room, BLOCK) ? 2 : 4;
-        G = (ntile + T - 1) / T;
-    }
-    if (G > room || ntile > T * BLOCK || G <= 0) return s;
-    s.T = T; s.G = G; s.nsp = std::min(c->n_long, cu - G);
-    return s;
-}
-
-// exchange words of a one-scene context of N nodes and NB bodies (0: none)
-static size_t px_words(int n_scenes, int N, int NB)
-{
-    if (n_scenes != 1 || N / TILE > 4 * BLOCK) return 0;
-    const int ndom = N / (CG_AGG * CG_DOM) + 1;
-    return 3 * (size_t)px_dlen(N / TILE, PX_LONG, CG_SPLIT * ndom, NB) + 6 * (size_t)N + 2 * (size_t)CG_N * ndom;
-}
-
-size_t pcg_resident_bytes(int n_scenes, int N, int NB)
-{
-    const size_t w = px_words(n_scenes, N, NB);
-    return w ? Arena::round(8 * w) + Arena::round(2 * sizeof(int)) : 0;
-}
-
 template <int T, bool COARSE>
 static bool px_allow()
 {
@@ -828,79 +818,167 @@ static bool px_allow()
                                (int)sizeof(PxLds<T>)) == hipSuccess;
 }
 
+static bool px_coarse(const ipc_ctx *c) { return c->coarse_on && c->n_cdom > 0; }
+// a scene's workgroups of T tiles: all its tiles and every slice of its coarse domains
+static int px_wgs(const ipc_ctx *c, int s, int T)
+{
+    const int w = (c->sc[s].nnode_pad / TILE + T - 1) / T;
+    return px_coarse(c) ? std::max(w, CG_SPLIT * (c->seg_cdom[s + 1] - c->seg_cdom[s])) : w;
+}
+
+// Tiles per workgroup for this context, 0: not for this context.  Several
+// scenes take one launch after the other, each as many scenes as the compute
+// units hold: a scene's solve then costs its own iterations once, where the
+// launch-per-iteration form streams all scenes' matrices until the last has
+// converged (16 scenes of 1k-40k tets: 23 us an iteration).
+static int px_tiles(const ipc_ctx *c)
+{
+    if (c->spmv_lanes != 8 || !c->use_graphs || c->prof || !c->pcg_fused || c->n_long > PX_LONG * c->n_scenes || !c->resident_ok) return 0;
+    if (px_coarse(c) && !c->cg_windows) return 0;
+    int total = 0, largest[3] = {0, 0, 0};
+    const int Ts[3] = {1, 2, 4}, room = c->n_cu - PX_SPARE;   // units for one scene's tiles
+    for (int s = 0; s < c->n_scenes; ++s) {
+        if (c->sc[s].nnode_pad / TILE > 4 * BLOCK) return 0;
+        for (int i = 0; i < 3; ++i) largest[i] = std::max(largest[i], px_wgs(c, s, Ts[i]));
+        total += c->sc[s].nnode_pad / TILE;
+    }
+    for (int i = px_coarse(c) ? 2 : 0; i < 3; ++i)
+        if (largest[i] <= std::min(room, BLOCK) && (i == 2 || total + c->n_scenes <= Ts[i] * room)) return Ts[i];
+    return 0;
+}
+
+// exchange words of a context of N nodes and NB bodies
+static size_t px_words(int n_scenes, int N, int NB)
+{
+    const int ndom = N / (CG_AGG * CG_DOM) + n_scenes;
+    return 3 * (size_t)px_dlen(N / TILE, PX_LONG * std::min(n_scenes, 64), CG_SPLIT * ndom, NB) + 6 * (size_t)N + 2 * (size_t)CG_N * ndom;
+}
+
+size_t pcg_resident_bytes(int n_scenes, int N, int NB)
+{
+    return Arena::round(8 * px_words(n_scenes, N, NB)) + Arena::round(2 * sizeof(int)) + Arena::round(n_scenes * sizeof(PxScene)) +
+           Arena::round(n_scenes * (size_t)PX_WGMAX * sizeof(PxPart));
+}
+
 // The exchange memory of a new context.  A workspace context takes it only
 // when the plan's slack stays free for the requests of later calls, so that
 // a workspace sized by an earlier plan serves as it did.
 void pcg_resident_setup(ipc_ctx *c)
 {
-    const size_t w = px_words(c->n_scenes, c->N, c->NB);
-    if (!w) return;
+    const int ns = c->n_scenes;
     if (c->ws.base) {
-        const size_t need = pcg_resident_bytes(c->n_scenes, c->N, c->NB);
+        const size_t need = pcg_resident_bytes(ns, c->N, c->NB);
         if (c->ws.used + need + c->ws.size / 17 + (1 << 20) > c->ws.size) return;
     }
     int cu = 0;
     if (hipGetDevice(&c->device) != hipSuccess || hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess)
         return;
-    c->n_cu = cu;
+    c->n_cu = std::min(cu, PX_WGMAX);
     if (!px_allow<1, false>() || !px_allow<2, false>() || !px_allow<4, false>() || !px_allow<4, true>()) return;
     // its sums are those of 8 lanes per row: the lanes stay at 8 unless a count is forced
     const int lanes = c->spmv_lanes;
     if (!c->spmv_lanes_forced) c->spmv_lanes = 8;
     c->resident_ok = true;
-    c->resident_ok = px_shape(c).T > 0;
+    c->resident_ok = px_tiles(c) > 0;
     if (!c->resident_ok) {
         c->spmv_lanes = lanes;
         return;
     }
-    c->d.px_words.alloc(w);
+    std::vector<int> tab;
+    for (int s = 0; s < ns; ++s) {
+        const SceneInfo &S = c->sc[s];
+        const PxScene q = {S.node0, S.nnode_pad / TILE, S.node0 / TILE, c->seg_cdom[s], c->seg_cdom[s + 1] - c->seg_cdom[s], S.body0, S.nb, S.bnode0, S.max_pcg};
+        const int *w = (const int *)&q;
+        tab.insert(tab.end(), w, w + sizeof(q) / sizeof(int));
+    }
+    c->d.px_scene.alloc(tab.size());
+    upload_async(c, c->d.px_scene.p, tab.data(), tab.size() * sizeof(int));
+    c->d.px_wg.alloc(ns * (size_t)PX_WGMAX * sizeof(PxPart) / sizeof(int));
+    c->d.px_words.alloc(px_words(ns, c->N, c->NB));
     c->d.px_ctl.alloc(2);
 }
 
 static std::mutex g_resident_mu[64];   // one resident solve per device at a time
 
-bool pcg_resident(ipc_ctx *c, double *x)
+PcgResident pcg_resident(ipc_ctx *c, double *x, const int *on)
 {
-    const PxShape s = px_shape(c);
-    if (!s.T) return false;
-    if (c->resident_skip > 0) { --c->resident_skip; return false; }
+    const int T = px_tiles(c);
+    if (!T) return PCG_RESIDENT_NO;
     Dev &D = c->d;
-    if (!D.px_words.p) return false;
+    if (!D.px_words.p) return PCG_RESIDENT_NO;
+    if (c->resident_skip > 0) { --c->resident_skip; return PCG_RESIDENT_NO; }
     // workgroups of two resident launches could each hold compute units the
     // other waits for; the lock is kept until this one's end is known
     std::unique_lock<std::mutex> lock(g_resident_mu[c->device & 63], std::try_to_lock);
-    if (!lock.owns_lock()) return false;
+    if (!lock.owns_lock()) return PCG_RESIDENT_NO;
     hipStream_t st = c->stream;
+    const bool coarse = px_coarse(c);
+    // the launches: scenes in order, as many as fit; units left over take
+    // long rows, alike for each of the launch's scenes
+    std::vector<PxPart> wg;
+    std::vector<int> round;   // first workgroup of every launch
+    const int spare_min = c->n_long > 0 ? 1 : 0;
+    for (int s = 0; s < c->n_scenes;) {
+        int s1 = s, used = 0, cnt = 0;
+        for (; s1 < c->n_scenes; ++s1) {
+            if (on && !on[s1]) continue;
+            const int w = px_wgs(c, s1, T) + spare_min;
+            if (used + w > c->n_cu) break;
+            used += w;
+            ++cnt;
+        }
+        if (cnt) {
+            const int most = std::min(c->n_long, c->n_scenes == 1 ? PX_LONG : PX_SPARE);
+            const int nsp = spare_min ? std::max(1, std::min(most, 1 + (c->n_cu - used) / cnt)) : 0;
+            round.push_back((int)wg.size());
+            for (int q = s; q < s1; ++q) {
+                if (on && !on[q]) continue;
+                const int w = px_wgs(c, q, T);
+                for (int k = 0; k < w; ++k) wg.push_back({q, k, 0, 0});
+                for (int k = 0; k < nsp; ++k) wg.push_back({q, -1, k, nsp});
+            }
+        }
+        if (s1 == s) return PCG_RESIDENT_NO;   // a scene alone does not fit
+        s = s1;
+    }
+    const int wgs = (int)wg.size();
+    round.push_back(wgs);
+    if (D.px_wg.n < wgs * sizeof(PxPart) / sizeof(int)) return PCG_RESIDENT_NO;
     PxArgs A{};
-    const bool coarse = c->coarse_on && c->n_cdom > 0;
-    A.N = c->N; A.ntile = c->N / TILE; A.G = s.G; A.nsp = s.nsp; A.nlong = c->n_long; A.nb = c->NB;
-    A.ncd = coarse ? CG_SPLIT * c->n_cdom : 0;
-    A.ndom = coarse ? c->n_cdom : 0; A.nfr = c->cg_nfr; A.bnode0 = c->sc[0].bnode0; A.maxit = c->sc[0].max_pcg;
+    A.N = c->N;
+    A.ntile = c->N / TILE; A.nlong = c->n_long; A.nb = c->NB; A.ncd = coarse ? CG_SPLIT * c->n_cdom : 0; A.ndom = A.ndom_all = coarse ? c->n_cdom : 0;
+    const int64_t nd = 3 * (int64_t)px_dlen(A.ntile, A.nlong, A.ncd, A.nb), nz = 6 * (int64_t)A.N, nr = 2 * (int64_t)CG_N * A.ndom;
+    if ((size_t)(nd + nz + nr) > D.px_words.n) return PCG_RESIDENT_NO;
+    A.scene = (const PxScene *)D.px_scene.p; A.wg = (const PxPart *)D.px_wg.p; A.seg_long = seg_ptr(c, R_LONG);
     A.kind = D.node_kind.p; A.node_body = D.node_body.p; A.row_ptr = D.row_ptr.p; A.col = D.col.p; A.dptr = D.dyn_ptr.p; A.dcol = D.dyn_col.p;
     A.long_rows = D.long_rows.p; A.node_da = D.cg_node_da.p;
     A.val = D.val.p; A.dval = D.dyn_val.p; A.dinv = D.dinv.p; A.dinvB = D.dinvB.p; A.inv = D.cg_inv.p;
     A.r0 = D.r.p; A.z0 = D.z.p; A.w0 = D.w.p;
-    A.part = D.pcg_part.p; A.part_zw = D.part_node3.p; A.part_long = D.part_long.p; A.cg_part = D.cg_part.p; A.st = D.pcg_st.p; A.act = D.pcg_act.p;
+    A.part = D.pcg_part.p; A.part_rr = A.part + A.ntile; A.part_zw = D.part_node3.p; A.part_long = D.part_long.p; A.cg_part = D.cg_part.p;
+    A.st = D.pcg_st.p; A.act = D.pcg_act.p;
     A.ph_ptr = D.cg_ph_ptr.p; A.ph_e = D.cg_ph_e.p; A.ph_n = D.cg_ph_n.p;
     A.x = x; A.scal = D.scal.p; A.iters = D.pcg_iters.p; A.ctl = D.px_ctl.p;
-    const int64_t nd = 3 * (int64_t)px_dlen(A.ntile, A.nlong, A.ncd, A.nb), nz = 6 * (int64_t)A.N, nr = 2 * (int64_t)CG_N * A.ndom;
     A.D = D.px_words.p; A.Z = A.D + nd; A.RC = A.Z + nz;
-    const int wgs = s.G + s.nsp;
+    upload_async(c, D.px_wg.p, wg.data(), wgs * sizeof(PxPart));
     hipLaunchKernelGGL(k_pcgx_fill, dim3(std::min(blocks_for(nd + nz + nr), 1024)), dim3(BLOCK), 0, st, nd + nz + nr, A.D, A.ctl);
-    switch (s.T) {
-    case 1: px_launch<1, false>(A, wgs, st); break;
-    case 2: px_launch<2, false>(A, wgs, st); break;
-    default:
-        if (coarse) px_launch<4, true>(A, wgs, st);
-        else px_launch<4, false>(A, wgs, st);
+    for (size_t k = 0; k + 1 < round.size(); ++k) {
+        const int w = round[k + 1] - round[k];
+        A.wg = (const PxPart *)D.px_wg.p + round[k];
+        switch (T) {
+        case 1: px_launch<1, false>(A, w, st); break;
+        case 2: px_launch<2, false>(A, w, st); break;
+        default:
+            if (coarse) px_launch<4, true>(A, w, st);
+            else px_launch<4, false>(A, w, st);
+        }
     }
     IPC_HIP(hipGetLastError());
     const unsigned int seq = pcg_next_seq(c);
     hipLaunchKernelGGL(k_pcgx_end, dim3(1), dim3(1), 0, st, wgs, D.px_ctl.p, seq, c->h_peek_dev);
     const int status = pcg_await(c, 0, seq, 1);
-    if (status == 1) { ++c->resident_solves; return true; }
+    if (status == 1) { ++c->resident_solves; return PCG_RESIDENT_DONE; }
     c->resident_skip = status == 3 ? 256 : 64;   // the launch-per-iteration form for a while
-    return false;
+    return PCG_RESIDENT_FAILED;
 }
 
 } // namespace ipc

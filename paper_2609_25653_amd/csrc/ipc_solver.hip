@@ -994,7 +994,7 @@ int pcg_await(ipc_ctx *c, int slot, unsigned int seq, int n)
     return most;
 }
 
-void pcg_solve(ipc_ctx *c, const double *b, double *x, double eta, const int *want)
+void pcg_solve(ipc_ctx *c, const double *b, double *x, double eta, const int *want, const int *on)
 {
     Dev &D = c->d;
     hipStream_t st = c->stream;
@@ -1013,11 +1013,20 @@ void pcg_solve(ipc_ctx *c, const double *b, double *x, double eta, const int *wa
     D.pcg_it.alloc(2 * (size_t)ns);
     D.pcg_prev.alloc(ns);
     int *act = D.pcg_act.p;
-    hipLaunchKernelGGL(k_pcg_init, dim3(blocks_for(c->N)), dim3(BLOCK), 0, st, c->N, ns, D.node_kind.p, D.node_body.p,
-                       D.tile_scene_node.p, seg_ptr(c, R_NODEW), b, D.dinv.p, D.dinvB.p, x, r, z, p, s, D.pcg_part.p, ntile, want, eta,
-                       D.sparam.p, D.pcg_st.p, D.pcg_prev.p, act, D.pcg_it.p, D.pcg_iters.p, D.scal.p);
-    coarse_apply(c, act, r, z, 0);              // z += the coarse correction of r, its r . z partials
-    hess_apply(c, z, w, act, D.part_node3.p);   // w = A z and z . w for the first step
+    auto start = [&]() {
+        hipLaunchKernelGGL(k_pcg_init, dim3(blocks_for(c->N)), dim3(BLOCK), 0, st, c->N, ns, D.node_kind.p, D.node_body.p,
+                           D.tile_scene_node.p, seg_ptr(c, R_NODEW), b, D.dinv.p, D.dinvB.p, x, r, z, p, s, D.pcg_part.p, ntile, want, eta,
+                           D.sparam.p, D.pcg_st.p, D.pcg_prev.p, act, D.pcg_it.p, D.pcg_iters.p, D.scal.p);
+        coarse_apply(c, act, r, z, 0);              // z += the coarse correction of r, its r . z partials
+        hess_apply(c, z, w, act, D.part_node3.p);   // w = A z and z . w for the first step
+    };
+    start();
+    pcg_peek_ready(c);
+    switch (pcg_resident(c, x, on)) {
+    case PCG_RESIDENT_DONE: return;
+    case PCG_RESIDENT_FAILED: start(); break;
+    default: break;
+    }
     int maxit = 0;
     for (auto &S : c->sc) maxit = std::max(maxit, S.max_pcg);
     // one iteration of parity q; every kernel skips scenes that stopped, so
@@ -1044,8 +1053,6 @@ void pcg_solve(ipc_ctx *c, const double *b, double *x, double eta, const int *wa
         if (!fused) coarse_apply(c, act + (q ^ 1) * ns, r, z, q ^ 1);
         hess_apply(c, zb[q ^ 1], w, act + (q ^ 1) * ns, D.part_node3.p);
     };
-    pcg_peek_ready(c);
-    if (pcg_resident(c, x)) return;
     auto peek = [&](int q, int slot, int n_since) {
         const unsigned int seq = pcg_next_seq(c);
         hipLaunchKernelGGL(k_pcg_peek, dim3(ns), dim3(BLOCK), 0, st, ns, q, seg_ptr(c, R_NODEW), D.maxpcg.p, D.pcg_part.p, ntile,

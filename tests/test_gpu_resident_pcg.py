@@ -62,3 +62,30 @@ def test_one_launch_solve_matches_iteration_launches(name, coarse, monkeypatch):
         got.append(out)
     for (xa, ia), (xb, ib) in zip(*got):
         assert ia == ib and torch.equal(xa, xb), (name, ia, ib)
+
+
+@pytest.mark.parametrize("coarse", ["0", "1"])
+def test_scenes_of_a_batch_match_iteration_launches(coarse, monkeypatch):
+    """Uneven scenes, more than one launch holds with the coarse correction (4
+    workgroups at least per scene), with and without bodies and contact: steps
+    (each Newton iteration solves for the scenes still iterating) and counts."""
+    import torch
+
+    from paper_2609_25653_amd import Sim
+    from paper_2609_25653_amd._lib import Q_PCG_RESIDENT
+    cells = [(2, 2, 2), (6, 3, 3), (12, 6, 6), (3, 2, 2)]
+    scenes = [S.gripper_squeeze(seed=i, n_steps=2, pad_cells=cells[i % 4]) for i in range(34)]
+    scenes[3:3] = [S.block_drop(n_steps=2), S.tiny_scene("free_body", h=0.005, n_steps=2), S.tiny_scene("cube", h=0.005, n_steps=2)]
+    monkeypatch.setenv("IPC_PCG_COARSE", coarse)
+    got = []
+    for eager in ("1", "0"):
+        monkeypatch.setenv("IPC_NO_GRAPH", eager)
+        sim = Sim(scenes)
+        out = []
+        for _ in range(2):
+            _, st = sim.step(allow_status=(3,))
+            out.append((sim.state(), [(q["newton_iters"], q["pcg_iters_total"], q["status"]) for q in st]))
+        assert (sim._query(Q_PCG_RESIDENT) > 0) == (eager == "0")
+        got.append(out)
+    for ((ya, va), sa), ((yb, vb), sb) in zip(*got):
+        assert sa == sb and torch.equal(ya, yb) and torch.equal(va, vb)
