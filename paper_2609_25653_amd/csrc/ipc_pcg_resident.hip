@@ -826,11 +826,7 @@ static int px_wgs(const ipc_ctx *c, int s, int T)
     return px_coarse(c) ? std::max(w, CG_SPLIT * (c->seg_cdom[s + 1] - c->seg_cdom[s])) : w;
 }
 
-// Tiles per workgroup for this context, 0: not for this context.  Several
-// scenes take one launch after the other, each as many scenes as the compute
-// units hold: a scene's solve then costs its own iterations once, where the
-// launch-per-iteration form streams all scenes' matrices until the last has
-// converged (16 scenes of 1k-40k tets: 23 us an iteration).
+// Tiles per workgroup for this context, 0: not for this context.
 static int px_tiles(const ipc_ctx *c)
 {
     if (c->spmv_lanes != 8 || !c->use_graphs || c->prof || !c->pcg_fused || c->n_long > PX_LONG * c->n_scenes || !c->resident_ok) return 0;
@@ -847,6 +843,47 @@ static int px_tiles(const ipc_ctx *c)
     return 0;
 }
 
+// The launches of a solve for the scenes on[] (null: all): scenes in order, as
+// many as the compute units hold, units left over for long rows, alike for
+// each of a launch's scenes.  first: the launches' first workgroups.
+//
+// At most PX_ROUNDS launches: one after the other each takes its scenes'
+// iterations, where the launch-per-iteration form streams all scenes'
+// matrices at once (uneven scenes of 1k-40k tets, ms a step, that form and
+// this one: 16 scenes, one launch, 48 and 36; 32, two, 44 and 40; 64, four,
+// 63 and 71; 256, 13 of them, 236 and 273).
+constexpr int PX_ROUNDS = 2;
+static bool px_plan(const ipc_ctx *c, int T, const int *on, std::vector<PxPart> &wg, std::vector<int> &first)
+{
+    const int spare_min = c->n_long > 0 ? 1 : 0;
+    for (int s = 0; s < c->n_scenes;) {
+        int s1 = s, used = 0, cnt = 0;
+        for (; s1 < c->n_scenes; ++s1) {
+            if (on && !on[s1]) continue;
+            const int w = px_wgs(c, s1, T) + spare_min;
+            if (used + w > c->n_cu) break;
+            used += w;
+            ++cnt;
+        }
+        if (cnt) {
+            if (first.size() == PX_ROUNDS) return false;
+            const int most = std::min(c->n_long, c->n_scenes == 1 ? PX_LONG : PX_SPARE);
+            const int nsp = spare_min ? std::max(1, std::min(most, 1 + (c->n_cu - used) / cnt)) : 0;
+            first.push_back((int)wg.size());
+            for (int q = s; q < s1; ++q) {
+                if (on && !on[q]) continue;
+                const int w = px_wgs(c, q, T);
+                for (int k = 0; k < w; ++k) wg.push_back({q, k, 0, 0});
+                for (int k = 0; k < nsp; ++k) wg.push_back({q, -1, k, nsp});
+            }
+        }
+        if (s1 == s) return false;   // a scene alone does not fit
+        s = s1;
+    }
+    first.push_back((int)wg.size());
+    return true;
+}
+
 // exchange words of a context of N nodes and NB bodies
 static size_t px_words(int n_scenes, int N, int NB)
 {
@@ -857,7 +894,7 @@ static size_t px_words(int n_scenes, int N, int NB)
 size_t pcg_resident_bytes(int n_scenes, int N, int NB)
 {
     return Arena::round(8 * px_words(n_scenes, N, NB)) + Arena::round(2 * sizeof(int)) + Arena::round(n_scenes * sizeof(PxScene)) +
-           Arena::round(n_scenes * (size_t)PX_WGMAX * sizeof(PxPart));
+           Arena::round(PX_ROUNDS * (size_t)PX_WGMAX * sizeof(PxPart));
 }
 
 // The exchange memory of a new context.  A workspace context takes it only
@@ -875,15 +912,19 @@ void pcg_resident_setup(ipc_ctx *c)
         return;
     c->n_cu = std::min(cu, PX_WGMAX);
     if (!px_allow<1, false>() || !px_allow<2, false>() || !px_allow<4, false>() || !px_allow<4, true>()) return;
-    // its sums are those of 8 lanes per row: the lanes stay at 8 unless a count is forced
+    // Its sums are those of 8 lanes per row: the lanes stay at 8, unless a
+    // count is forced or the scenes take too many launches together (then it
+    // serves a Newton iteration's last scenes while the lanes are 8).
     const int lanes = c->spmv_lanes;
-    if (!c->spmv_lanes_forced) c->spmv_lanes = 8;
+    c->spmv_lanes = 8;
     c->resident_ok = true;
-    c->resident_ok = px_tiles(c) > 0;
-    if (!c->resident_ok) {
-        c->spmv_lanes = lanes;
-        return;
-    }
+    const int T = px_tiles(c);
+    c->resident_ok = T > 0;
+    std::vector<PxPart> wg;
+    std::vector<int> first;
+    c->resident_lanes = c->resident_ok && !c->spmv_lanes_forced && px_plan(c, T, nullptr, wg, first);
+    if (!c->resident_lanes) c->spmv_lanes = lanes;
+    if (!c->resident_ok) return;
     std::vector<int> tab;
     for (int s = 0; s < ns; ++s) {
         const SceneInfo &S = c->sc[s];
@@ -893,7 +934,7 @@ void pcg_resident_setup(ipc_ctx *c)
     }
     c->d.px_scene.alloc(tab.size());
     upload_async(c, c->d.px_scene.p, tab.data(), tab.size() * sizeof(int));
-    c->d.px_wg.alloc(ns * (size_t)PX_WGMAX * sizeof(PxPart) / sizeof(int));
+    c->d.px_wg.alloc(PX_ROUNDS * (size_t)PX_WGMAX * sizeof(PxPart) / sizeof(int));
     c->d.px_words.alloc(px_words(ns, c->N, c->NB));
     c->d.px_ctl.alloc(2);
 }
@@ -913,37 +954,11 @@ PcgResident pcg_resident(ipc_ctx *c, double *x, const int *on)
     if (!lock.owns_lock()) return PCG_RESIDENT_NO;
     hipStream_t st = c->stream;
     const bool coarse = px_coarse(c);
-    // the launches: scenes in order, as many as fit; units left over take
-    // long rows, alike for each of the launch's scenes
     std::vector<PxPart> wg;
-    std::vector<int> round;   // first workgroup of every launch
-    const int spare_min = c->n_long > 0 ? 1 : 0;
-    for (int s = 0; s < c->n_scenes;) {
-        int s1 = s, used = 0, cnt = 0;
-        for (; s1 < c->n_scenes; ++s1) {
-            if (on && !on[s1]) continue;
-            const int w = px_wgs(c, s1, T) + spare_min;
-            if (used + w > c->n_cu) break;
-            used += w;
-            ++cnt;
-        }
-        if (cnt) {
-            const int most = std::min(c->n_long, c->n_scenes == 1 ? PX_LONG : PX_SPARE);
-            const int nsp = spare_min ? std::max(1, std::min(most, 1 + (c->n_cu - used) / cnt)) : 0;
-            round.push_back((int)wg.size());
-            for (int q = s; q < s1; ++q) {
-                if (on && !on[q]) continue;
-                const int w = px_wgs(c, q, T);
-                for (int k = 0; k < w; ++k) wg.push_back({q, k, 0, 0});
-                for (int k = 0; k < nsp; ++k) wg.push_back({q, -1, k, nsp});
-            }
-        }
-        if (s1 == s) return PCG_RESIDENT_NO;   // a scene alone does not fit
-        s = s1;
-    }
+    std::vector<int> round;
+    if (!px_plan(c, T, on, wg, round)) return PCG_RESIDENT_NO;
     const int wgs = (int)wg.size();
-    round.push_back(wgs);
-    if (D.px_wg.n < wgs * sizeof(PxPart) / sizeof(int)) return PCG_RESIDENT_NO;
+    if (wgs == 0 || D.px_wg.n < wgs * sizeof(PxPart) / sizeof(int)) return PCG_RESIDENT_NO;
     PxArgs A{};
     A.N = c->N;
     A.ntile = c->N / TILE; A.nlong = c->n_long; A.nb = c->NB; A.ncd = coarse ? CG_SPLIT * c->n_cdom : 0; A.ndom = A.ndom_all = coarse ? c->n_cdom : 0;

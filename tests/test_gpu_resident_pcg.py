@@ -74,7 +74,7 @@ def test_scenes_of_a_batch_match_iteration_launches(coarse, monkeypatch):
     from paper_2609_25653_amd import Sim
     from paper_2609_25653_amd._lib import Q_PCG_RESIDENT
     cells = [(2, 2, 2), (6, 3, 3), (12, 6, 6), (3, 2, 2)]
-    scenes = [S.gripper_squeeze(seed=i, n_steps=2, pad_cells=cells[i % 4]) for i in range(34)]
+    scenes = [S.gripper_squeeze(seed=i, n_steps=2, pad_cells=cells[i % 4]) for i in range(40)]
     scenes[3:3] = [S.block_drop(n_steps=2), S.tiny_scene("free_body", h=0.005, n_steps=2), S.tiny_scene("cube", h=0.005, n_steps=2)]
     monkeypatch.setenv("IPC_PCG_COARSE", coarse)
     got = []
