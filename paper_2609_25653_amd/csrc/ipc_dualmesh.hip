@@ -2,16 +2,17 @@
 // Loop subdivision of the coarse simulation mesh as one sparse matrix, built
 // on the host at creation; X^f = W X^c for many frames per launch.
 //
-// The application is HBM-bound: W is read once per launch (12 B per
-// nonzero) and every frame writes 24 B per fine vertex, while the coarse
-// frames (24 B per coarse vertex) stay in L2.  One thread per fine vertex
-// keeps its row of W in registers and loops over the frames, so consecutive
-// threads write consecutive fine vertices of a frame.
+// The application is HBM-bound: W is read once per launch and every frame
+// writes 24 B per fine vertex, while the coarse frames (24 B per coarse
+// vertex) stay in L2.  A thread keeps its rows of W in registers and loops
+// over the frames (k_dm_pairs; k_dm_apply for long rows).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <iterator>
+#include <memory>
 #include <mutex>
 #include <stdexcept>
 #include <string>
@@ -27,22 +28,28 @@ struct ipc_dualmesh {
     int64_t nnz = 0;
     std::vector<int> row_ptr, col, tri_fine;
     std::vector<double> val;
-    // per block of DM_ROWS rows: its distinct columns (blk_cols from
-    // blk_off[b]) and, per nonzero, the column's place in its block's list
-    std::vector<int> blk_off, blk_cols, lcol;
-    int max_block = 0;
+    // W for k_dm_pairs (empty if a row has more than DM_K columns): groups of
+    // one or two rows (rows of group g: grp_row[g] .. grp_row[g + 1]), blocks
+    // of at most DM_T groups, each with the list of its distinct columns
+    // (in blk_cols) and, by [k][group of the block], the group's k-th
+    // column's place in that list (times 3) and, by [k][row of the group][group], its
+    // weights (grp_col, grp_val)
+    struct Block {
+        int u0, nu;    // its columns: blk_cols[u0 .. u0 + nu)
+        int g0, ng;    // its groups
+        int w0, nk;    // its part of grp_col from w0 on, of grp_val from 2 w0 on; columns of its widest group
+        int pad[2];
+    };
+    std::vector<int> grp_row, blk_cols;
+    std::vector<Block> blk;
+    std::vector<uint16_t> grp_col;
+    std::vector<double> grp_val;
     uint64_t id = 0;   // unique per handle: names the W that the no-alloc path last staged
-    int *d_row = nullptr, *d_col = nullptr, *d_lcol = nullptr, *d_boff = nullptr, *d_bcols = nullptr;
-    double *d_val = nullptr;
+    unsigned char *d_w = nullptr;   // the arrays of W, at layout()'s offsets
     std::string err;
     ~ipc_dualmesh()
     {
-        if (d_row) (void)hipFree(d_row);
-        if (d_col) (void)hipFree(d_col);
-        if (d_lcol) (void)hipFree(d_lcol);
-        if (d_boff) (void)hipFree(d_boff);
-        if (d_bcols) (void)hipFree(d_bcols);
-        if (d_val) (void)hipFree(d_val);
+        if (d_w) (void)hipFree(d_w);
     }
 };
 
@@ -50,8 +57,10 @@ namespace {
 
 std::string g_dm_create_error;
 
-constexpr int DM_ROWS = 256;     // fine rows per workgroup of the staged kernel
-constexpr int DM_STAGE = 1024;   // coarse vertices a block may stage in LDS (24 KiB)
+constexpr int DM_T = 256;        // groups of rows per workgroup of k_dm_pairs, at most
+constexpr int DM_STAGE = 512;    // coarse vertices a block stages in LDS, at most (12 KiB)
+constexpr int DM_K = 16;         // columns of a group, at most
+constexpr int DM_CUS = 256;
 
 struct Invalid : std::runtime_error {
     using std::runtime_error::runtime_error;
@@ -235,38 +244,72 @@ __global__ void __launch_bounds__(256) k_dm_apply(int nf, int nc, int frames, co
     }
 }
 
-// Workgroup b takes rows [DM_ROWS b, DM_ROWS b + DM_ROWS): per frame it
-// first copies the positions of the block's distinct coarse vertices into
-// LDS (each fetched once per block instead of once per use: a block of 256
-// consecutive fine rows touches ~100 coarse vertices), then every thread
-// sums its row (kept in registers with columns renumbered into the block's
-// list) from LDS and writes its fine vertex.
-template <int K>
-__global__ void __launch_bounds__(DM_ROWS) k_dm_apply_lds(int nf, int nc, int frames, const int *__restrict__ rp,
-                                                          const int *__restrict__ lcol, const double *__restrict__ val,
-                                                          const int *__restrict__ boff, const int *__restrict__ bcols,
-                                                          const double *__restrict__ xc, double *__restrict__ xf)
+// Workgroup b takes a block of up to 256 groups of rows, a group (one or two
+// consecutive rows with at most KMAX columns between them) per thread, and
+// the frames [per blockIdx.y, per (blockIdx.y + 1)).  Per frame it first
+// copies the positions of the block's distinct coarse vertices into LDS (each
+// fetched once per block: 512 consecutive fine rows touch ~180 coarse
+// vertices), then every thread reads its group's columns once for both rows -
+// neighbouring fine vertices lie in one coarse triangle and share nearly all
+// of their columns, 12.5 for two rows of 11.2 - and the wavefront's rows,
+// which are consecutive, go out through LDS as 16 B per lane and whole lines.
+//
+// What bounds it: the output (24 B per fine vertex and frame), then LDS
+// reads.  422402 fine vertices, 100 frames (1014 MB written): 351 us with a
+// row per thread, its own CSR row and 8 B stores 24 B apart; 291 with the
+// frames in two parts (1650 blocks on 1280 places left the second round
+// nearly empty); 258 with two rows per thread (283 with 8 B stores); stores
+// straight from two-row threads, 48 B apart,
+// 633-1270; three or four rows per thread 289-305 (registers).  One frame
+// (118786 fine vertices): 8.4 us with CSR rows, which each thread reads for
+// itself, 5.1 with the weights side by side.
+//
+// The sums run over a row's own columns in ascending order; the other row's
+// columns add 0 * x, which changes nothing unless x is infinite or NaN: a
+// block that stages such a position takes the sums with those terms left out.
+template <int KMAX>
+__global__ void __launch_bounds__(DM_T) k_dm_pairs(int nf, int nc, int frames, int per, const int *__restrict__ grp_row,
+                                                   const ipc_dualmesh::Block *__restrict__ blk,
+                                                   const int *__restrict__ blk_cols, const uint16_t *__restrict__ grp_col,
+                                                   const double *__restrict__ grp_val, const double *__restrict__ xc,
+                                                   double *__restrict__ xf)
 {
-    constexpr int PER = DM_STAGE / DM_ROWS;   // staged vertices per thread, at most
+    typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+    constexpr int PER = DM_STAGE / DM_T;   // staged vertices per thread, at most
     __shared__ double sx[3 * DM_STAGE];
-    const int t = threadIdx.x, r = blockIdx.x * DM_ROWS + t;
-    const int u0 = boff[blockIdx.x], U = boff[blockIdx.x + 1] - u0;
+    __shared__ double so[6 * DM_T];
+    __shared__ int bad[3];                 // a staged position of frame f is not finite: [f mod 3]
+    const int t = threadIdx.x, b = blockIdx.x, lane = t & 63;
+    const int f0 = blockIdx.y * per, f1 = min(frames, f0 + per);
+    const ipc_dualmesh::Block B = blk[b];
+    const int ng = B.ng, nk = B.nk;
     int src[PER];
 #pragma unroll
-    for (int q = 0; q < PER; ++q) src[q] = t + q * DM_ROWS < U ? bcols[u0 + t + q * DM_ROWS] : -1;
-    int c[K];
-    double w[K];
-    int n = 0;
-    if (r < nf) {
-        const int k0 = rp[r];
-        n = rp[r + 1] - k0;
+    for (int q = 0; q < PER; ++q) src[q] = t + q * DM_T < B.nu ? blk_cols[B.u0 + t + q * DM_T] : -1;
+    const bool on = t < ng;
+    const int ti = min(t, ng - 1);
+    int c[KMAX];
+    double w[2][KMAX];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const bool in = k < n;
-            c[k] = in ? lcol[k0 + k] : 0;
-            w[k] = in ? val[k0 + k] : 0.0;
-        }
+    for (int k = 0; k < KMAX; ++k) {
+        c[k] = 0;
+        w[0][k] = w[1][k] = 0.0;
     }
+    auto load = [&](int k0, int k1) {      // nothing looks at them before the last loads are out
+#pragma unroll
+        for (int k = k0; k < k1; ++k) {
+            const size_t o = (size_t)B.w0 + (size_t)min(k, nk - 1) * ng + ti;
+            const size_t v = 2 * o - ti;
+            c[k] = grp_col[o];
+            w[0][k] = grp_val[v];
+            w[1][k] = grp_val[v + ng];
+        }
+    };
+    load(0, 2);
+    if (nk > 2) load(2, 6);
+    if (nk > 6) load(6, 10);
+    if (nk > 10) load(10, 14);
+    if (nk > 14) load(14, KMAX);
     // the next frame's staged positions are loaded into registers while this
     // frame is summed and stored, so the gather's latency overlaps the work
     double pf[PER][3];
@@ -280,85 +323,226 @@ __global__ void __launch_bounds__(DM_ROWS) k_dm_apply_lds(int nf, int nc, int fr
                 pf[q][2] = x[3 * (size_t)src[q] + 2];
             }
     };
-    if (frames > 0) fetch(0);
-    for (int f = 0; f < frames; ++f) {
+    if (f0 < f1) fetch(f0);
+    const int r0 = grp_row[B.g0 + ti], r1 = grp_row[B.g0 + ti + 1], rows = on ? r1 - r0 : 0;
+    int words = 0;                         // of the wavefront's rows, which start at wr0
+    const int wr0 = __builtin_amdgcn_readfirstlane(r0), first = __builtin_amdgcn_readfirstlane(t);
+    if (first < ng) words = 3 * (__builtin_amdgcn_readlane(r1, min(63, ng - 1 - first)) - wr0);
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k) {
+        const bool in = k < nk && on;
+        c[k] = in ? c[k] : 0;
+        w[0][k] = in ? w[0][k] : 0.0;
+        w[1][k] = in ? w[1][k] : 0.0;
+    }
+    int wide = 0;                          // columns of the wavefront's widest group
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k)
+        if (__any(w[0][k] != 0.0 || w[1][k] != 0.0)) wide = k + 1;
+    if (t < 3) bad[t] = 0;
+    for (int f = f0, slot = 0; f < f1; ++f, slot = slot == 2 ? 0 : slot + 1) {
         __syncthreads();   // the previous frame's reads of sx are done
 #pragma unroll
-        for (int q = 0; q < PER; ++q) {
+        for (int q = 0; q < PER; ++q)
             if (src[q] >= 0) {
-                const int u = t + q * DM_ROWS;
-                sx[3 * u] = pf[q][0];
-                sx[3 * u + 1] = pf[q][1];
-                sx[3 * u + 2] = pf[q][2];
+                const int u = 3 * (t + q * DM_T);
+                sx[u] = pf[q][0];
+                sx[u + 1] = pf[q][1];
+                sx[u + 2] = pf[q][2];
+                if (!(pf[q][0] * 0.0 + pf[q][1] * 0.0 + pf[q][2] * 0.0 == 0.0)) bad[slot] = 1;
             }
-        }
-        if (f + 1 < frames) fetch(f + 1);
         __syncthreads();
-        if (r < nf) {
-            double ax = 0.0, ay = 0.0, az = 0.0;
+        if (t == 0) bad[slot == 0 ? 2 : slot - 1] = 0;   // the previous frame's: read before the barrier above, next set two frames on
+        if (f + 1 < f1) fetch(f + 1);
+        double a[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
+        if (!bad[slot]) {
+            auto sum = [&](int k0, int k1) {
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                if (k < n) {
-                    ax += w[k] * sx[3 * c[k]];
-                    ay += w[k] * sx[3 * c[k] + 1];
-                    az += w[k] * sx[3 * c[k] + 2];
+                for (int k = k0; k < k1; ++k) {
+                    const double px = sx[c[k]], py = sx[c[k] + 1], pz = sx[c[k] + 2];
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        a[j][0] += w[j][k] * px;
+                        a[j][1] += w[j][k] * py;
+                        a[j][2] += w[j][k] * pz;
+                    }
                 }
+            };
+            sum(0, 6);
+            if (wide > 6) sum(6, 10);
+            if (wide > 10) sum(10, 14);
+            if (wide > 14) sum(14, KMAX);
+        } else {
+#pragma unroll
+            for (int k = 0; k < KMAX; ++k) {
+                const double px = sx[c[k]], py = sx[c[k] + 1], pz = sx[c[k] + 2];
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    if (w[j][k] != 0.0) {   // the weights of a row are all positive
+                        a[j][0] += w[j][k] * px;
+                        a[j][1] += w[j][k] * py;
+                        a[j][2] += w[j][k] * pz;
+                    }
             }
-            double *o = xf + ((size_t)f * nf + r) * 3;
-            st_stream(o, ax, ay, az);
         }
+        // the wavefront's own part of so: no barrier
+        double *const out = so + 6 * (t - lane);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            if (j < rows) {
+                double *o = out + 3 * (r0 - wr0 + j);
+                o[0] = a[j][0];
+                o[1] = a[j][1];
+                o[2] = a[j][2];
+            }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        double *const o = xf + ((size_t)f * nf + wr0) * 3;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const int e = 2 * (64 * q + lane);
+            if (e + 1 < words) __builtin_nontemporal_store((d2u){out[e], out[e + 1]}, (d2u *)(o + e));
+            else if (e < words) __builtin_nontemporal_store(out[e], o + e);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
-// the staged kernel serves every W whose blocks fit in LDS and rows in 16 registers
-bool staged(const ipc_dualmesh *m) { return m->max_block <= DM_STAGE && m->max_row <= 16; }
+// Groups and blocks of k_dm_pairs (host side of its layout).
+void group_rows(ipc_dualmesh *m)
+{
+    if (m->max_row > DM_K) return;
+    const int kmax = m->max_row > 14 ? 16 : 14, n = m->n_fine;
+    const int *rp = m->row_ptr.data(), *col = m->col.data();
+    std::vector<int> place(m->n_coarse, -1), cols;      // of the block being filled
+    std::vector<int> ucol, uptr{0};                     // each group's columns, ascending
+    int g0 = 0, nk = 1;
+    auto close = [&](int g1) {
+        std::sort(cols.begin(), cols.end());
+        for (size_t u = 0; u < cols.size(); ++u) place[cols[u]] = (int)u;
+        m->blk_cols.insert(m->blk_cols.end(), cols.begin(), cols.end());
+        const int ng = g1 - g0;
+        const size_t w0 = m->grp_col.size(), size = w0 + (size_t)nk * ng;
+        if (size > (size_t)INT32_MAX) throw Invalid("too many nonzeros");
+        m->grp_col.resize(size, 0);
+        m->grp_val.resize(2 * size, 0.0);
+        for (int g = g0; g < g1; ++g) {
+            const int *u = ucol.data() + uptr[g], nu = uptr[g + 1] - uptr[g];
+            for (int k = 0; k < nu; ++k) m->grp_col[w0 + (size_t)k * ng + g - g0] = (uint16_t)(3 * place[u[k]]);
+            for (int r = m->grp_row[g]; r < m->grp_row[g + 1]; ++r)
+                for (int q = rp[r], k = 0; q < rp[r + 1]; ++q) {
+                    while (u[k] != col[q]) ++k;
+                    m->grp_val[2 * (w0 + (size_t)k * ng) + (size_t)(r - m->grp_row[g]) * ng + g - g0] = m->val[q];
+                }
+        }
+        for (int j : cols) place[j] = -1;
+        m->blk.push_back({(int)(m->blk_cols.size() - cols.size()), (int)cols.size(), g0, ng, (int)w0, nk, {0, 0}});
+        cols.clear();
+        g0 = g1;
+        nk = 1;
+    };
+    m->grp_row.push_back(0);
+    for (int r = 0; r < n;) {
+        std::vector<int> u;
+        int end = r + 1;
+        if (end < n) std::set_union(col + rp[r], col + rp[r + 1], col + rp[r + 1], col + rp[r + 2], std::back_inserter(u));
+        if (end < n && (int)u.size() <= kmax) ++end;
+        else u.assign(col + rp[r], col + rp[r + 1]);
+        const int g = (int)m->grp_row.size() - 1;
+        int fresh = 0;
+        for (int j : u) fresh += place[j] < 0;
+        if (g - g0 == DM_T || (int)cols.size() + fresh > DM_STAGE) close(g);
+        for (int j : u)
+            if (place[j] < 0) { place[j] = 0; cols.push_back(j); }
+        nk = std::max(nk, (int)u.size());
+        ucol.insert(ucol.end(), u.begin(), u.end());
+        uptr.push_back((int)ucol.size());
+        m->grp_row.push_back(end);
+        r = end;
+    }
+    close((int)m->grp_row.size() - 1);
+}
+
+size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// byte offsets of W's arrays on the device, of k_dm_pairs (pairs) or k_dm_apply; the total
+struct Layout {
+    bool pairs = false;
+    size_t row = 0, col = 0, val = 0, blk = 0, cols = 0, total = 0;
+};
+Layout layout(const ipc_dualmesh *m, bool pairs)
+{
+    Layout L;
+    auto put = [&](size_t bytes) { const size_t o = L.total; L.total += align256(std::max<size_t>(bytes, 1)); return o; };
+    L.pairs = pairs;
+    L.row = put(sizeof(int) * (pairs ? m->grp_row : m->row_ptr).size());
+    L.val = put(sizeof(double) * (pairs ? m->grp_val : m->val).size());
+    L.col = put(pairs ? sizeof(uint16_t) * m->grp_col.size() : sizeof(int) * m->col.size());
+    if (pairs) {
+        L.blk = put(sizeof(ipc_dualmesh::Block) * m->blk.size());
+        L.cols = put(sizeof(int) * m->blk_cols.size());
+    }
+    return L;
+}
+
+hipError_t copy_in(const ipc_dualmesh *m, const Layout &L, unsigned char *base)
+{
+    hipError_t e = hipSuccess;
+    auto put = [&](size_t off, const auto &v) {
+        if (e == hipSuccess && !v.empty()) e = hipMemcpyAsync(base + off, v.data(), sizeof(v[0]) * v.size(), hipMemcpyHostToDevice, m->stream);
+    };
+    if (L.pairs) {
+        put(L.row, m->grp_row); put(L.val, m->grp_val); put(L.col, m->grp_col);
+        put(L.blk, m->blk); put(L.cols, m->blk_cols);
+    } else {
+        put(L.row, m->row_ptr); put(L.val, m->val); put(L.col, m->col);
+    }
+    return e;
+}
+
+Layout owned(const ipc_dualmesh *m) { return layout(m, !m->grp_row.empty()); }
 
 hipError_t upload(ipc_dualmesh *m)
 {
-    if (m->d_row) return hipSuccess;
-    hipError_t e = hipMalloc(&m->d_row, sizeof(int) * m->row_ptr.size());
-    if (e == hipSuccess) e = hipMalloc(&m->d_col, sizeof(int) * std::max<size_t>(m->col.size(), 1));
-    if (e == hipSuccess) e = hipMalloc(&m->d_val, sizeof(double) * std::max<size_t>(m->val.size(), 1));
-    if (e == hipSuccess) e = hipMemcpyAsync(m->d_row, m->row_ptr.data(), sizeof(int) * m->row_ptr.size(), hipMemcpyHostToDevice, m->stream);
-    if (e == hipSuccess && !m->col.empty())
-        e = hipMemcpyAsync(m->d_col, m->col.data(), sizeof(int) * m->col.size(), hipMemcpyHostToDevice, m->stream);
-    if (e == hipSuccess && !m->val.empty())
-        e = hipMemcpyAsync(m->d_val, m->val.data(), sizeof(double) * m->val.size(), hipMemcpyHostToDevice, m->stream);
-    if (e == hipSuccess && staged(m)) {
-        e = hipMalloc(&m->d_lcol, sizeof(int) * std::max<size_t>(m->lcol.size(), 1));
-        if (e == hipSuccess) e = hipMalloc(&m->d_boff, sizeof(int) * m->blk_off.size());
-        if (e == hipSuccess) e = hipMalloc(&m->d_bcols, sizeof(int) * std::max<size_t>(m->blk_cols.size(), 1));
-        if (e == hipSuccess && !m->lcol.empty())
-            e = hipMemcpyAsync(m->d_lcol, m->lcol.data(), sizeof(int) * m->lcol.size(), hipMemcpyHostToDevice, m->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(m->d_boff, m->blk_off.data(), sizeof(int) * m->blk_off.size(), hipMemcpyHostToDevice, m->stream);
-        if (e == hipSuccess && !m->blk_cols.empty())
-            e = hipMemcpyAsync(m->d_bcols, m->blk_cols.data(), sizeof(int) * m->blk_cols.size(), hipMemcpyHostToDevice, m->stream);
-    }
+    if (m->d_w) return hipSuccess;
+    const Layout L = owned(m);
+    hipError_t e = hipMalloc(&m->d_w, L.total);
+    if (e == hipSuccess) e = copy_in(m, L, m->d_w);
     if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
     return e;
 }
 
-// W on the device: CSR arrays, and for the staged kernel the renumbered
-// columns and the per-block coarse-vertex lists
-struct DevW {
-    const int *row, *col, *lcol, *boff, *bcols;
-    const double *val;
-};
-
-hipError_t launch(ipc_dualmesh *m, const DevW &w, const double *xc, double *xf, int frames)
+hipError_t launch(ipc_dualmesh *m, const Layout &L, const unsigned char *base, const double *xc, double *xf, int frames)
 {
-    const dim3 grid((m->n_fine + 255) / 256), blk(256);
+    const int *row = (const int *)(base + L.row);
+    const double *val = (const double *)(base + L.val);
     const int R = m->max_row;
-    if (w.lcol) {
-        hipLaunchKernelGGL(k_dm_apply_lds<16>, dim3((m->n_fine + DM_ROWS - 1) / DM_ROWS), dim3(DM_ROWS), 0, m->stream, m->n_fine,
-                           m->n_coarse, frames, w.row, w.lcol, w.val, w.boff, w.bcols, xc, xf);
+    if (L.pairs) {
+        // Frames are split over blocks: as long as all of the blocks run at
+        // once (four per CU), to single frames, which then take as long as
+        // one; beyond, to about four rounds of blocks, so that the last,
+        // partly empty one weighs little, and at least 16 frames each: a
+        // block's set-up reads the weights, as many bytes as five frames
+        // write.  885 blocks by 100 frames: one part 304 us, two 270, three
+        // 264, four 259, six 255.  13 blocks
+        // by 20: one part 28 us, twenty 6.
+        const int nb = (int)m->blk.size();
+        const int parts = std::max({1, std::min(4 * DM_CUS / nb, frames), std::min((16 * DM_CUS + nb - 1) / nb, frames / 16)});
+        const int per = (frames + parts - 1) / parts;
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(nb, (frames + per - 1) / per), dim3(DM_T), 0, m->stream, m->n_fine, m->n_coarse, frames, per, row,
+                               (const ipc_dualmesh::Block *)(base + L.blk), (const int *)(base + L.cols),
+                               (const uint16_t *)(base + L.col), val, xc, xf);
+        };
+        if (R <= 14) go(k_dm_pairs<14>);   // 128 registers: four blocks per CU; regular meshes have rows of at most 14
+        else go(k_dm_pairs<16>);
         return hipGetLastError();
     }
-#define IPC_DM(KK) hipLaunchKernelGGL(k_dm_apply<KK>, grid, blk, 0, m->stream, m->n_fine, m->n_coarse, frames, w.row, w.col, \
-                                      w.val, xc, xf)
-    if (R <= 8) IPC_DM(8);
-    else if (R <= 16) IPC_DM(16);
+    const dim3 grid((m->n_fine + 255) / 256), blk(256);
+    const int *col = (const int *)(base + L.col);
+#define IPC_DM(KK) hipLaunchKernelGGL(k_dm_apply<KK>, grid, blk, 0, m->stream, m->n_fine, m->n_coarse, frames, row, col, val, xc, xf)
+    if (R <= 16) IPC_DM(16);
     else if (R <= 32) IPC_DM(32);
     else if (R <= 48) IPC_DM(48);
     else if (R <= 64) IPC_DM(64);
@@ -366,8 +550,6 @@ hipError_t launch(ipc_dualmesh *m, const DevW &w, const double *xc, double *xf, 
 #undef IPC_DM
     return hipGetLastError();
 }
-
-DevW owned(const ipc_dualmesh *m) { return {m->d_row, m->d_col, m->d_lcol, m->d_boff, m->d_bcols, m->d_val}; }
 
 // ---- the variant that allocates nothing ------------------------------------
 // W is staged in a file-scope device array of fixed size instead of memory
@@ -387,27 +569,11 @@ std::mutex g_scratch_mu;
 ScratchSlot g_scratch[DM_MAX_DEVICES];
 uint64_t g_dm_next_id = 1;
 
-size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
-
-// byte offsets of W's arrays in the array (0 for an unused one); the total
-struct ScratchLayout {
-    size_t row = 0, col = 0, lcol = 0, val = 0, boff = 0, bcols = 0, total = 0;
-};
-ScratchLayout scratch_layout(const ipc_dualmesh *m)
+// W as the array holds it: for k_dm_pairs if that fits, else in its own rows
+Layout scratch_layout(const ipc_dualmesh *m)
 {
-    ScratchLayout L;
-    size_t o = 0;
-    L.row = o; o += align256(sizeof(int) * m->row_ptr.size());
-    L.val = o; o += align256(sizeof(double) * std::max<size_t>(m->val.size(), 1));
-    if (staged(m)) {
-        L.lcol = o; o += align256(sizeof(int) * std::max<size_t>(m->lcol.size(), 1));
-        L.boff = o; o += align256(sizeof(int) * m->blk_off.size());
-        L.bcols = o; o += align256(sizeof(int) * std::max<size_t>(m->blk_cols.size(), 1));
-    } else {
-        L.col = o; o += align256(sizeof(int) * std::max<size_t>(m->col.size(), 1));
-    }
-    L.total = o;
-    return L;
+    const Layout L = owned(m);
+    return L.total <= DM_SCRATCH_BYTES ? L : layout(m, false);
 }
 
 } // namespace
@@ -427,7 +593,8 @@ extern "C" int ipc_dualmesh_create(const int32_t *tri_host, int32_t n_tri, int32
             if (a < 0 || b < 0 || c < 0 || a >= n_vert || b >= n_vert || c >= n_vert) throw Invalid("vertex index out of range");
             if (a == b || b == c || c == a) throw Invalid("a triangle repeats a vertex");
         }
-        auto *m = new ipc_dualmesh;
+        auto own = std::make_unique<ipc_dualmesh>();
+        ipc_dualmesh *m = own.get();
         m->stream = (hipStream_t)hip_stream;
         {
             std::lock_guard<std::mutex> lock(g_scratch_mu);
@@ -437,18 +604,13 @@ extern "C" int ipc_dualmesh_create(const int32_t *tri_host, int32_t n_tri, int32
         Csr W;
         for (int i = 0; i < n_vert; ++i) { W.col.push_back(i); W.val.push_back(1.0); W.ptr.push_back(i + 1); }
         int n = n_vert;
-        try {
-            for (int l = 0; l < levels; ++l) {
-                Csr S;
-                std::vector<int> tri_next;
-                loop_level(n, tri, S, tri_next);
-                W = multiply(S, W, n_vert);
-                n = S.rows();
-                tri.swap(tri_next);
-            }
-        } catch (...) {
-            delete m;
-            throw;
+        for (int l = 0; l < levels; ++l) {
+            Csr S;
+            std::vector<int> tri_next;
+            loop_level(n, tri, S, tri_next);
+            W = multiply(S, W, n_vert);
+            n = S.rows();
+            tri.swap(tri_next);
         }
         m->n_coarse = n_vert;
         m->n_fine = n;
@@ -458,23 +620,8 @@ extern "C" int ipc_dualmesh_create(const int32_t *tri_host, int32_t n_tri, int32
         m->nnz = (int64_t)m->col.size();
         for (int r = 0; r < n; ++r) m->max_row = std::max(m->max_row, m->row_ptr[r + 1] - m->row_ptr[r]);
         m->tri_fine = std::move(tri);
-        // per block of rows: distinct columns and the nonzeros' places among them
-        m->lcol.resize(m->col.size());
-        m->blk_off.push_back(0);
-        std::vector<int> place(n_vert, -1);
-        for (int b0 = 0; b0 < n; b0 += DM_ROWS) {
-            const int b1 = std::min(n, b0 + DM_ROWS), first = (int)m->blk_cols.size();
-            std::vector<int> cols(m->col.begin() + m->row_ptr[b0], m->col.begin() + m->row_ptr[b1]);
-            std::sort(cols.begin(), cols.end());
-            cols.erase(std::unique(cols.begin(), cols.end()), cols.end());
-            for (size_t u = 0; u < cols.size(); ++u) { place[cols[u]] = (int)u; m->blk_cols.push_back(cols[u]); }
-            for (int k = m->row_ptr[b0]; k < m->row_ptr[b1]; ++k) m->lcol[k] = place[m->col[k]];
-            for (int j : cols) place[j] = -1;
-            m->max_block = std::max(m->max_block, (int)cols.size());
-            m->blk_off.push_back((int)m->blk_cols.size());
-            (void)first;
-        }
-        *out = m;
+        group_rows(m);
+        *out = own.release();
         return IPC_OK;
     } catch (const Invalid &e) {
         g_dm_create_error = e.what();
@@ -523,7 +670,7 @@ extern "C" int ipc_dualmesh_apply(ipc_dualmesh *m, const double *xc_dev, double 
     if (!m) return IPC_E_INVALID;
     if (!xc_dev || !xf_dev || n_frames < 1) { m->err = "need device arrays and at least one frame"; return IPC_E_INVALID; }
     hipError_t e = upload(m);
-    if (e == hipSuccess) e = launch(m, owned(m), xc_dev, xf_dev, n_frames);
+    if (e == hipSuccess) e = launch(m, owned(m), m->d_w, xc_dev, xf_dev, n_frames);
     if (e != hipSuccess) { m->err = std::string("HIP: ") + hipGetErrorString(e); return IPC_E_DEVICE; }
     return IPC_OK;
 }
@@ -532,7 +679,7 @@ extern "C" int ipc_dualmesh_apply_noalloc(ipc_dualmesh *m, const double *xc_dev,
 {
     if (!m) return IPC_E_INVALID;
     if (!xc_dev || !xf_dev || n_frames < 1) { m->err = "need device arrays and at least one frame"; return IPC_E_INVALID; }
-    const ScratchLayout L = scratch_layout(m);
+    const Layout L = scratch_layout(m);
     if (L.total > DM_SCRATCH_BYTES) {
         m->err = "W needs " + std::to_string(L.total) + " bytes of staging; the no-alloc path holds at most " +
                  std::to_string(DM_SCRATCH_BYTES);
@@ -545,27 +692,11 @@ extern "C" int ipc_dualmesh_apply_noalloc(ipc_dualmesh *m, const double *xc_dev,
     ScratchSlot &S = g_scratch[dev];
     if (e == hipSuccess && !S.ptr) e = hipGetSymbolAddress((void **)&S.ptr, HIP_SYMBOL(scratch));   // once per device
     if (e == hipSuccess && S.holds != m->id) {
-        auto put = [&](size_t off, const void *src, size_t bytes) {
-            if (e == hipSuccess && bytes) e = hipMemcpyAsync(S.ptr + off, src, bytes, hipMemcpyHostToDevice, m->stream);
-        };
         S.holds = 0;
-        put(L.row, m->row_ptr.data(), sizeof(int) * m->row_ptr.size());
-        put(L.val, m->val.data(), sizeof(double) * m->val.size());
-        if (staged(m)) {
-            put(L.lcol, m->lcol.data(), sizeof(int) * m->lcol.size());
-            put(L.boff, m->blk_off.data(), sizeof(int) * m->blk_off.size());
-            put(L.bcols, m->blk_cols.data(), sizeof(int) * m->blk_cols.size());
-        } else {
-            put(L.col, m->col.data(), sizeof(int) * m->col.size());
-        }
+        e = copy_in(m, L, S.ptr);
         if (e == hipSuccess) S.holds = m->id;
     }
-    if (e == hipSuccess) {
-        const bool st = staged(m);
-        DevW w{(const int *)(S.ptr + L.row), st ? nullptr : (const int *)(S.ptr + L.col), st ? (const int *)(S.ptr + L.lcol) : nullptr,
-               st ? (const int *)(S.ptr + L.boff) : nullptr, st ? (const int *)(S.ptr + L.bcols) : nullptr, (const double *)(S.ptr + L.val)};
-        e = launch(m, w, xc_dev, xf_dev, n_frames);
-    }
+    if (e == hipSuccess) e = launch(m, L, S.ptr, xc_dev, xf_dev, n_frames);
     if (e != hipSuccess) { m->err = std::string("HIP: ") + hipGetErrorString(e); return IPC_E_DEVICE; }
     return IPC_OK;
 }
@@ -577,11 +708,11 @@ extern "C" int ipc_dualmesh_time(ipc_dualmesh *m, const double *xc_dev, double *
     if (!xc_dev || !xf_dev || n_frames < 1 || reps < 1 || !avg_us) { m->err = "invalid timing arguments"; return IPC_E_INVALID; }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = upload(m);
-    if (e == hipSuccess) e = launch(m, owned(m), xc_dev, xf_dev, n_frames);   // warm
+    if (e == hipSuccess) e = launch(m, owned(m), m->d_w, xc_dev, xf_dev, n_frames);   // warm
     if (e == hipSuccess) e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
     if (e == hipSuccess) e = hipEventRecord(e0, m->stream);
-    for (int k = 0; k < reps && e == hipSuccess; ++k) e = launch(m, owned(m), xc_dev, xf_dev, n_frames);
+    for (int k = 0; k < reps && e == hipSuccess; ++k) e = launch(m, owned(m), m->d_w, xc_dev, xf_dev, n_frames);
     if (e == hipSuccess) e = hipEventRecord(e1, m->stream);
     if (e == hipSuccess) e = hipEventSynchronize(e1);
     float ms = 0.0f;
