@@ -398,35 +398,42 @@ __global__ void k_prec_fem(int N, const int *__restrict__ kind, const int *__res
     o[6] = c2 * id; o[7] = (a[1] * a[6] - a[0] * a[7]) * id; o[8] = (a[0] * a[4] - a[1] * a[3]) * id;
 }
 
-// 12x12 SPD inverse by Cholesky (one thread per body)
-// One thread per body (launched with 64 threads, so the register file holds
-// the 12x12 factor); every loop is unrolled, so no array needs scratch memory.
+// 12x12 SPD inverse by Cholesky, 16 lanes per body.  What bounds it is a
+// chain of divisions and dependent loads, as few bodies as a scene has: each
+// lane finds and loads one of the 16 node blocks (one search each instead of
+// 16 in a row), every lane factors the whole matrix in registers (all
+// loops unrolled: no array needs scratch memory), and lane j < 12 solves for
+// column j of the inverse: 10-12 us per assembly; a thread per body took 38-47.
+constexpr int PB_LANES = 16;
 __global__ void __launch_bounds__(64) k_prec_body(int NB, const int *__restrict__ bslot, const int *__restrict__ node0,
                                                   const double *__restrict__ val, const int *__restrict__ dptr,
                                                   const int *__restrict__ dcol, const double *__restrict__ dval,
                                                   double *__restrict__ dinvB, const int *__restrict__ body_scene,
                                                   const int *__restrict__ active)
 {
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= NB) return;
-    if (active && !active[body_scene[b]]) return;
+    __shared__ double A[64 / PB_LANES][144];
+    const int g = threadIdx.x / PB_LANES, lane = threadIdx.x % PB_LANES, b = blockIdx.x * (64 / PB_LANES) + g;
+    const bool on = b < NB && !(active && !active[body_scene[b]]);
+    if (on) {
+        const int n0 = node0[b], ca = lane / 4, cb = lane % 4;
+        const double *B = val + 9 * (size_t)bslot[16 * (size_t)b + lane];
+        const int k = dyn_find(dptr, dcol, n0 + ca, n0 + cb);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                double v = B[3 * i + j];
+                if (k >= 0) v += dval[9 * (size_t)k + 3 * i + j];
+                A[g][12 * (3 * ca + i) + 3 * cb + j] = v;
+            }
+    }
+    __syncthreads();
+    if (!on || lane >= 12) return;
     double L[144];
-    int n0 = node0[b];
 #pragma unroll
-    for (int ca = 0; ca < 4; ++ca)
+    for (int i = 0; i < 12; ++i)
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-            const double *B = val + 9 * (size_t)bslot[16 * (size_t)b + 4 * ca + cb];
-            int k = dyn_find(dptr, dcol, n0 + ca, n0 + cb);
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    double v = B[3 * i + j];
-                    if (k >= 0) v += dval[9 * (size_t)k + 3 * i + j];
-                    L[12 * (3 * ca + i) + 3 * cb + j] = v;
-                }
-        }
+        for (int j = 0; j <= i; ++j) L[12 * i + j] = A[g][12 * i + j];
     // Cholesky factor L L^T (lower triangle of L)
 #pragma unroll
     for (int j = 0; j < 12; ++j) {
@@ -443,28 +450,25 @@ __global__ void __launch_bounds__(64) k_prec_body(int NB, const int *__restrict_
             L[12 * i + j] = t / dj;
         }
     }
-    // the inverse, one column at a time by forward and back substitution
+    // the lane's column of the inverse by forward and back substitution
     double *o = dinvB + 144 * (size_t)b;
+    double y[12];
 #pragma unroll
-    for (int cidx = 0; cidx < 12; ++cidx) {
-        double y[12];
+    for (int i = 0; i < 12; ++i) {
+        double t = (i == lane) ? 1.0 : 0.0;
 #pragma unroll
-        for (int i = 0; i < 12; ++i) {
-            double t = (i == cidx) ? 1.0 : 0.0;
-#pragma unroll
-            for (int k = 0; k < i; ++k) t -= L[12 * i + k] * y[k];
-            y[i] = t / L[12 * i + i];
-        }
-#pragma unroll
-        for (int i = 11; i >= 0; --i) {
-            double t = y[i];
-#pragma unroll
-            for (int k = i + 1; k < 12; ++k) t -= L[12 * k + i] * y[k];
-            y[i] = t / L[12 * i + i];
-        }
-#pragma unroll
-        for (int i = 0; i < 12; ++i) o[12 * i + cidx] = y[i];
+        for (int k = 0; k < i; ++k) t -= L[12 * i + k] * y[k];
+        y[i] = t / L[12 * i + i];
     }
+#pragma unroll
+    for (int i = 11; i >= 0; --i) {
+        double t = y[i];
+#pragma unroll
+        for (int k = i + 1; k < 12; ++k) t -= L[12 * k + i] * y[k];
+        y[i] = t / L[12 * i + i];
+    }
+#pragma unroll
+    for (int i = 0; i < 12; ++i) o[12 * i + lane] = y[i];
 }
 
 void build_preconditioner(ipc_ctx *c)
@@ -473,7 +477,7 @@ void build_preconditioner(ipc_ctx *c)
     hipLaunchKernelGGL(k_prec_fem, dim3(blocks_for(c->N)), dim3(BLOCK), 0, c->stream, c->N, D.node_kind.p, D.diag_slot.p, D.val.p,
                        D.dyn_ptr.p, D.dyn_col.p, D.dyn_val.p, D.dinv.p, D.node_scene.p, c->assemble_only);
     if (c->NB)
-        hipLaunchKernelGGL(k_prec_body, dim3(blocks_for(c->NB, 64)), dim3(64), 0, c->stream, c->NB, D.bslot.p, D.body_node0.p, D.val.p,
+        hipLaunchKernelGGL(k_prec_body, dim3(blocks_for((int64_t)c->NB * PB_LANES, 64)), dim3(64), 0, c->stream, c->NB, D.bslot.p, D.body_node0.p, D.val.p,
                            D.dyn_ptr.p, D.dyn_col.p, D.dyn_val.p, D.dinvB.p, D.body_scene.p, c->assemble_only);
     coarse_build(c);
 }
