@@ -1742,46 +1742,96 @@ __global__ void k_dyn_count(int nb, int nf, const int *__restrict__ pflag, const
     cnt[i] = n;
 }
 
-// DYN_LANES lanes per pair entry: lane j writes output blocks j, j +
-// DYN_LANES, ... of the entry, block b at row node b / total and column node
-// b % total in the owner groups' order (a pair touches at most two bodies, so
-// at most 8 nodes and 64 blocks; one between FEM vertices at most 16).  A
-// thread per entry walked up to 64 blocks one after another, which took
-// 0.26 ms per assembly where a body met the pads; a wavefront per entry left
-// most lanes idle on FEM pairs (40 -> 72 us on the 200k-tet squeeze).
+// DYN_LANES lanes per pair entry.  First lane 4 k + l forms the world-vertex
+// block (k, l) and lane 4 k + q the weight of node q of vertex k's owner, into
+// LDS; then lane j writes output blocks j, j + DYN_LANES, ... of the entry,
+// block b at row node b / total and column node b % total in the owner groups'
+// order (a pair touches at most two bodies, so at most 8 nodes and 64
+// blocks; one between FEM vertices at most 16), the weighted sum of up to 9
+// world blocks.  A thread per entry walked up to 64 blocks one after another
+// (0.26 ms per assembly where a body met the pads), a wavefront per entry
+// left most lanes idle on FEM pairs (40 -> 72 us on the 200k-tet squeeze),
+// and with the world blocks formed anew for every output block that they
+// enter, up to 9 x 81 operations each and 304 B of scratch per lane, the
+// launch took 46 us on the 20k-tet squeeze and 105 on a batch of eight scenes;
+// now 10 and 25.
 constexpr int DYN_LANES = 16;
-__global__ void k_dyn_write(int nb, int nf, const int *__restrict__ off, const int4 *__restrict__ pcv, const int4 *__restrict__ lcv,
+__global__ void __launch_bounds__(BLOCK) k_dyn_write(int nb, int nf, const int *__restrict__ off, const int4 *__restrict__ pcv,
+                            const int4 *__restrict__ lcv,
                             const double *__restrict__ pH, const double *__restrict__ lbeta, const double *__restrict__ lM,
                             const int *__restrict__ cv_node, const int *__restrict__ cv_body, const double *__restrict__ cv_x,
                             const int *__restrict__ body_node0, unsigned long long *__restrict__ key, int *__restrict__ idx,
                             double *__restrict__ valc)
 {
+    struct Entry {
+        double B[16][9], w[16];
+        int first[4], nn[4], node[16], own[16], q[16];   // owners; the local nodes: number, owner, place in it
+    };
+    __shared__ Entry entry[BLOCK / DYN_LANES];
     const int i = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / DYN_LANES), lane = threadIdx.x & (DYN_LANES - 1);
-    if (i >= nb + nf) return;
-    const int o0 = off[i], n = off[i + 1] - o0;
-    if (n == 0) return;
-    Map mp[4];
-    pair_maps(i, nb, pcv, lcv, cv_node, cv_body, cv_x, body_node0, mp);
-    const PairNodes P = pair_nodes(mp);
+    const int o0 = i < nb + nf ? off[i] : 0, n = i < nb + nf ? off[i + 1] - o0 : 0;
+    if (n == 0) return;   // all of the entry's lanes; the others of the wavefront go on without them
+    Entry &E = entry[threadIdx.x / DYN_LANES];
+    const int4 cv = i < nb ? pcv[i] : lcv[i - nb];
+    const Map mp[4] = {cv_map(cv.x, cv_node, cv_body, cv_x, body_node0), cv_map(cv.y, cv_node, cv_body, cv_x, body_node0),
+                       cv_map(cv.z, cv_node, cv_body, cv_x, body_node0), cv_map(cv.w, cv_node, cv_body, cv_x, body_node0)};
+    int f[4], g[4], ng = 0, total = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {   // pair_nodes, with constant indices
+        f[k] = mp[k].node >= 0 ? mp[k].node : mp[k].body;
+        g[k] = -1;
+        if (f[k] < 0) continue;
+#pragma unroll
+        for (int q = 0; q < k; ++q)
+            if (f[q] == f[k]) g[k] = g[q];
+        if (g[k] < 0) {
+            g[k] = ng++;
+            const int nn = mp[k].node >= 0 ? 1 : 4;
+            total += nn;
+            if (lane == 0) { E.first[g[k]] = f[k]; E.nn[g[k]] = nn; }
+        }
+    }
+    {
+        const int k = lane >> 2, l = lane & 3;
+        pair_block(i, nb, pH, lbeta, lM, k, l, E.B[lane]);
+        double w = 0.0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (k == v) w = map_weight(mp[v], l);
+        E.w[lane] = w;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (lane < total) {
+        int a = 0, q = lane;
+        while (q >= E.nn[a]) q -= E.nn[a++];
+        E.node[lane] = E.first[a] + q;
+        E.own[lane] = a;
+        E.q[lane] = q;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     for (int j = lane; j < n; j += DYN_LANES) {
-        int ga = 0, qa = j / P.total, gb = 0, qb = j % P.total;
-        while (qa >= P.nn[ga]) qa -= P.nn[ga++];
-        while (qb >= P.nn[gb]) qb -= P.nn[gb++];
-        double B[9], S[9];
+        const int la = j / total, lb = j % total, ga = E.own[la], qa = E.q[la], gb = E.own[lb], qb = E.q[lb];
+        double S[9];
+#pragma unroll
         for (int q = 0; q < 9; ++q) S[q] = 0.0;
+#pragma unroll
         for (int k = 0; k < 4; ++k) {
-            if (P.g[k] != ga) continue;
-            double wk = map_weight(mp[k], qa);
+            if (g[k] != ga) continue;
+            const double wk = E.w[4 * k + qa];
+#pragma unroll
             for (int l = 0; l < 4; ++l) {
-                if (P.g[l] != gb) continue;
-                double w = wk * map_weight(mp[l], qb);
-                pair_block(i, nb, pH, lbeta, lM, k, l, B);
-                for (int q = 0; q < 9; ++q) S[q] += w * B[q];
+                if (g[l] != gb) continue;
+                const double w = wk * E.w[4 * l + qb];
+#pragma unroll
+                for (int q = 0; q < 9; ++q) S[q] += w * E.B[4 * k + l][q];
             }
         }
         const int o = o0 + j;
-        key[o] = ((unsigned long long)(P.first[ga] + qa) << 32) | (unsigned)(P.first[gb] + qb);
+        key[o] = ((unsigned long long)E.node[la] << 32) | (unsigned)E.node[lb];
         idx[o] = o;
+#pragma unroll
         for (int q = 0; q < 9; ++q) valc[9 * (size_t)o + q] = S[q];
     }
 }
