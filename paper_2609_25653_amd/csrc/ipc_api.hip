@@ -287,8 +287,7 @@ void eval_energy(ipc_ctx *c, const double *y, bool from_candidates)
     Dev &D = c->d;
     hipStream_t st = c->stream;
     launch_world(c, y, D.xw.p);
-    hipLaunchKernelGGL(k_fill_int_api, dim3(blocks_for(c->n_scenes)), dim3(BLOCK), 0, st, c->n_scenes, D.inf_flag.p, 0);
-    launch_node_inertia(c, y, nullptr, D.part_node.p);
+    launch_node_inertia(c, y, nullptr, D.part_node.p);   // clears inf_flag too
     launch_fem(c, 0, y, nullptr, false, D.part_tet.p, D.h2s.p);
     launch_body(c, 0, y, nullptr, false, D.body_part.p, D.h2s.p);
     launch_spring(c, 0, y, nullptr, D.sp_part.p, D.h2s.p);
@@ -343,13 +342,12 @@ void eval_grad_hess(ipc_ctx *c, const double *y, double *g, bool hess, bool proj
     Dev &D = c->d;
     hipStream_t st = c->stream;
     launch_world(c, y, D.xw.p);
-    hipLaunchKernelGGL(k_fill_int_api, dim3(blocks_for(c->n_scenes)), dim3(BLOCK), 0, st, c->n_scenes, D.inf_flag.p, 0);
     // inertia writes g; the FEM gathers then write the matrix values (constant
     // part + tets) and add the tets' gradients; the bodies add their own
     // nodes; springs, barrier and friction pairs add through sorted run sums
     // (one writer per destination, in an order fixed by the inputs), so the
     // gradient and the matrix are the same bit for bit on every run
-    launch_node_inertia(c, y, g, D.part_node.p);
+    launch_node_inertia(c, y, g, D.part_node.p);   // clears inf_flag too
     launch_fem(c, hess ? 2 : 1, y, g, project, D.part_tet.p, D.h2s.p);
     launch_body(c, hess ? 2 : 1, y, g, project, D.body_part.p, D.h2s.p);
     launch_spring(c, 1, y, g, D.sp_part.p, D.h2s.p);
@@ -399,12 +397,27 @@ constexpr size_t PIN_RD_BYTES = 1 << 20, PIN_WR_BYTES = 1 << 20;
 static void ensure_pinned(ipc_ctx *c)
 {
     if (c->pin_rd) return;
-    IPC_HIP(hipHostMalloc((void **)&c->pin_rd, PIN_RD_BYTES, hipHostMallocDefault));
+    IPC_HIP(hipHostMalloc((void **)&c->pin_rd, PIN_RD_BYTES, hipHostMallocMapped | hipHostMallocCoherent));
     IPC_HIP(hipHostMalloc((void **)&c->pin_wr, PIN_WR_BYTES, hipHostMallocDefault));
     c->pin_wr_off = 0;
 }
 
 HostReads::HostReads(ipc_ctx *cc) : c(cc) { ensure_pinned(c); }
+
+// A group of small reads is one launch that writes the pinned area itself:
+// a copy call per array took the stream and the host some 8 us each (17 of
+// them per Newton iteration).
+constexpr int READS = 8;
+constexpr size_t READ_BYTES = 1 << 16;   // a larger array is a copy call
+struct ReadArgs {
+    const unsigned *src[READS];
+    unsigned *dst[READS];
+    int words[READS];
+};
+__global__ void __launch_bounds__(256) k_host_reads(ReadArgs a)
+{
+    for (int i = threadIdx.x; i < a.words[blockIdx.x]; i += 256) a.dst[blockIdx.x][i] = a.src[blockIdx.x][i];
+}
 
 void HostReads::add(void *dst, const void *src, size_t bytes)
 {
@@ -414,13 +427,27 @@ void HostReads::add(void *dst, const void *src, size_t bytes)
         IPC_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, c->stream));
         return;
     }
-    IPC_HIP(hipMemcpyAsync(c->pin_rd + off, src, bytes, hipMemcpyDeviceToHost, c->stream));
-    items.push_back({dst, off, bytes});
+    const bool small = bytes <= READ_BYTES && bytes % 4 == 0;
+    if (!small) IPC_HIP(hipMemcpyAsync(c->pin_rd + off, src, bytes, hipMemcpyDeviceToHost, c->stream));
+    items.push_back({dst, off, bytes, small ? src : nullptr});
     used = off + bytes;
 }
 
 void HostReads::wait()
 {
+    ReadArgs a;
+    int n = 0;
+    for (size_t k = 0; k < items.size(); ++k) {
+        if (items[k].src) {
+            a.src[n] = (const unsigned *)items[k].src;
+            a.dst[n] = (unsigned *)(c->pin_rd + items[k].off);
+            a.words[n++] = (int)(items[k].bytes / 4);
+        }
+        if (n == READS || (n && k + 1 == items.size())) {
+            hipLaunchKernelGGL(k_host_reads, dim3(n), dim3(256), 0, c->stream, a);
+            n = 0;
+        }
+    }
     IPC_HIP(hipStreamSynchronize(c->stream));
     for (auto &it : items) std::memcpy(it.dst, c->pin_rd + it.off, it.bytes);
     items.clear();
@@ -880,7 +907,6 @@ extern "C" int ipc_hessian_bsr(ipc_ctx *c, const double *y_dev, uint32_t flags, 
         D.bsr_cnt.alloc(NE + 1);
         hipLaunchKernelGGL(k_bsr_export<false>, dim3(blocks_for(NE)), dim3(BLOCK), 0, st, NE, D.ext2node.p, D.int2ext.p, D.row_ptr.p,
                            D.col.p, D.val.p, D.dyn_ptr.p, D.dyn_col.p, D.dyn_val.p, D.bsr_cnt.p, nullptr, nullptr, nullptr);
-        hipLaunchKernelGGL(k_fill_int_api, dim3(1), dim3(64), 0, st, 1, D.bsr_cnt.p + NE, 0);
         exclusive_scan_int(c, D.bsr_cnt.p, row_ptr_dev, (int)NE);
         int total = 0;
         std::vector<int> inf(c->n_scenes);

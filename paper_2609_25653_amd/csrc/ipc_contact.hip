@@ -587,30 +587,78 @@ __global__ void k_seg_from_scan(int n_scenes, const int *__restrict__ qseg, cons
     seg[s] = off[qseg[s]];
 }
 
-// per-scene segments of a ballot-compacted list: survivors before each
-// scene's first candidate (cseg), from the wavefront masks and their scan
-__global__ void k_compact_seg(int n_scenes, int ncand, const int *__restrict__ cseg, const unsigned long long *__restrict__ mask,
-                              const int *__restrict__ woff, int nw, int *__restrict__ seg)
+// per-scene segments of the narrow phase's two ballot-compacted lists (thread
+// s: scene s of the first, n_scenes + 1 + s of the second): survivors before
+// each scene's first candidate (cseg), from the wavefront masks and their scan
+__global__ void k_compact_seg(int n_scenes, int n0, int n1, const int *__restrict__ cseg0, const int *__restrict__ cseg1,
+                              const unsigned long long *__restrict__ mask, const int *__restrict__ woff, int *__restrict__ seg0,
+                              int *__restrict__ seg1)
 {
     int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s > n_scenes) return;
-    int q = cseg[s];
-    if (q >= ncand) { seg[s] = woff[nw]; return; }
-    int w = q / TILE, l = q % TILE;
-    seg[s] = woff[w] + (l ? __popcll(mask[w] & ((1ull << l) - 1ull)) : 0);
+    if (s >= 2 * (n_scenes + 1)) return;
+    const int second = s > n_scenes;
+    if (second) s -= n_scenes + 1;
+    const int nw0 = (n0 + TILE - 1) / TILE, nw1 = (n1 + TILE - 1) / TILE, w0 = second ? nw0 : 0, first = second ? woff[nw0] : 0;
+    const int q = (second ? cseg1 : cseg0)[s];
+    int v;
+    if (q >= (second ? n1 : n0)) v = woff[second ? nw0 + nw1 : nw0];
+    else {
+        const int w = w0 + q / TILE, l = q % TILE;
+        v = woff[w] + (l ? __popcll(mask[w] & ((1ull << l) - 1ull)) : 0);
+    }
+    (second ? seg1 : seg0)[s] = v - first;
 }
 
-void exclusive_scan_int(ipc_ctx *c, const int *in, int *out, int n)
+// Exclusive scan of up to SCAN_ONE counts in one workgroup, 4096 at a time,
+// with the total after the last: one launch that needs no zero after the
+// counts, where the library's scan takes a launch to clear that zero and,
+// above one block's worth, one to set up its look-back.  A Newton iteration
+// runs four of these scans and each is a few us of launches.
+constexpr int SCAN_T = 1024, SCAN_ONE = 4 * 4 * SCAN_T;
+__global__ void __launch_bounds__(SCAN_T) k_scan_one(int n, const int *__restrict__ in, int *__restrict__ out)
 {
-    size_t bytes = 0;
-    IPC_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, bytes, in, out, n + 1, c->stream));
-    c->d.sort_tmp.alloc(bytes + 16);
-    IPC_HIP(hipcub::DeviceScan::ExclusiveSum(c->d.sort_tmp.p, bytes, in, out, n + 1, c->stream));
+    __shared__ int wsum[2][SCAN_T / TILE];
+    const int t = threadIdx.x, lane = t & (TILE - 1), w = t / TILE;
+    int before = 0;
+    for (int b0 = 0, turn = 0; b0 < n; b0 += 4 * SCAN_T, turn ^= 1) {   // two rows of sums: one barrier per turn
+        const int i = b0 + 4 * t;
+        int v[4], sum = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = i + q < n ? in[i + q] : 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sum += v[q];
+        int incl = sum;
+#pragma unroll
+        for (int d = 1; d < TILE; d <<= 1) {
+            const int o = __shfl_up(incl, d, TILE);
+            if (lane >= d) incl += o;
+        }
+        if (lane == TILE - 1) wsum[turn][w] = incl;
+        __syncthreads();
+        int at = before + incl - sum;
+#pragma unroll
+        for (int u = 0; u < SCAN_T / TILE; ++u) {
+            const int x = wsum[turn][u];
+            before += x;
+            if (u < w) at += x;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (i + q < n) out[i + q] = at;
+            at += v[q];
+        }
+    }
+    if (t == 0) out[n] = before;
 }
 
-// exclusive scan helper (count[n] -> off[n + 1], off[n] = total)
-static void exclusive_scan(ipc_ctx *c, const int *in, int *out, int n)
+// exclusive scan (in[n] -> out[n + 1], out[n] = total); in has room for n + 1
+void exclusive_scan_int(ipc_ctx *c, int *in, int *out, int n)
 {
+    if (n <= SCAN_ONE) {
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(SCAN_T), 0, c->stream, n, in, out);
+        return;
+    }
+    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, c->stream, 1, in + n, 0);
     size_t bytes = 0;
     IPC_HIP(hipcub::DeviceScan::ExclusiveSum(nullptr, bytes, in, out, n + 1, c->stream));
     c->d.sort_tmp.alloc(bytes + 16);
@@ -667,8 +715,7 @@ static void bvh_query(ipc_ctx *c, int kind, const double *xw0, const double *xw1
     D.bvh_moving.alloc(P + 1); D.bvh_mscan.alloc(P + 1); D.bvh_nmoving.alloc(P);
     hipLaunchKernelGGL(k_seg_leaves, dim3(blocks_for(P)), dim3(BLOCK), 0, st, P, kind, D.mid2.p, D.box.p, D.tri.p, D.edge.p, D.cv_obj.p,
                        D.obj_kind.p, D.bvh_lev.p, D.bvh_moving.p);
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, 1, D.bvh_moving.p + P, 0);
-    exclusive_scan(c, D.bvh_moving.p, D.bvh_mscan.p, P);
+    exclusive_scan_int(c, D.bvh_moving.p, D.bvh_mscan.p, P);
     for (int j0 = 0; j0 + 1 < SL.n; j0 += 8)
         hipLaunchKernelGGL(k_seg_up, dim3(blocks_for(SL.size[j0], 256)), dim3(256), 0, st, SL, j0, D.bvh_lev.p);
     hipLaunchKernelGGL(k_node_box, dim3(blocks_for(P)), dim3(BLOCK), 0, st, P, SL, D.bvh_lev.p, D.bvh_range.p, D.bvh_mscan.p,
@@ -713,8 +760,7 @@ static void bvh_query(ipc_ctx *c, int kind, const double *xw0, const double *xw1
         hipLaunchKernelGGL(k_wide<false>, dim3(std::min(Q, WIDE_GRID)), dim3(WIDE_BLOCK), 0, st, kind, qedge, D.cv_scene.p, D.tri.p,
                            D.edge.p, D.cv_obj.p, D.obj_kind.p, D.excl.p, c->NEX, xw0, xw1, D.sparam.p, pseg_d, rid, rbox, bbox, pobj, grow,
                            ovf.p + 2, wlist, D.qcount.p, nullptr, nullptr, ovf.p, D.qstash.p);
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, 1, D.qcount.p + Q, 0);
-    exclusive_scan(c, D.qcount.p, D.qoff.p, Q);
+    exclusive_scan_int(c, D.qcount.p, D.qoff.p, Q);
     // the candidates' per-scene segments go straight to the device table
     hipLaunchKernelGGL(k_seg_from_scan, dim3(blocks_for(ns + 1)), dim3(BLOCK), 0, st, ns, qseg_d, D.qoff.p, sseg);
     int total = 0, of[2] = {0, 0};
@@ -821,14 +867,18 @@ __device__ __forceinline__ void pair_vertices(int kind, int2 p, const int4 *tri,
     else { int2 a = edge[p.x], b = edge[p.y]; cv[0] = a.x; cv[1] = a.y; cv[2] = b.x; cv[3] = b.y; }
 }
 
+// Both kinds of candidate in one launch: wavefronts [0, nw0) take the n0
+// point-triangle ones, the next the n1 edge-edge ones.
 template <bool WRITE>
-__global__ void k_narrow(int n, int kind, const int2 *__restrict__ cand, const int4 *__restrict__ tri, const int2 *__restrict__ edge,
-                         const int *__restrict__ cv_scene, const double *__restrict__ xw, const double *__restrict__ sparam,
-                         unsigned long long *__restrict__ mask, int *__restrict__ wcount, const int *__restrict__ woff,
-                         int2 *__restrict__ out)
+__global__ void k_narrow(int n0, int n1, const int2 *__restrict__ cand0, const int2 *__restrict__ cand1, const int4 *__restrict__ tri,
+                         const int2 *__restrict__ edge, const int *__restrict__ cv_scene, const double *__restrict__ xw,
+                         const double *__restrict__ sparam, unsigned long long *__restrict__ mask, int *__restrict__ wcount,
+                         const int *__restrict__ woff, int2 *__restrict__ out0, int2 *__restrict__ out1)
 {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    int wave = i / TILE, lane = threadIdx.x & (TILE - 1);
+    const int nw0 = (n0 + TILE - 1) / TILE, nw1 = (n1 + TILE - 1) / TILE;
+    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) / TILE, lane = threadIdx.x & (TILE - 1);
+    const int kind = wave >= nw0, n = kind ? n1 : n0, i = TILE * (kind ? wave - nw0 : wave) + lane;
+    const int2 *cand = kind ? cand1 : cand0;
     if (!WRITE) {
         bool act = false;
         if (i < n) {
@@ -841,65 +891,64 @@ __global__ void k_narrow(int n, int kind, const int2 *__restrict__ cand, const i
             act = d2 < dh * dh;
         }
         unsigned long long m = __ballot(act);
-        if (lane == 0 && wave * TILE < n) { mask[wave] = m; wcount[wave] = __popcll(m); }
+        if (lane == 0 && wave < nw0 + nw1) { mask[wave] = m; wcount[wave] = __popcll(m); }
     } else {
         if (i >= n) return;
         unsigned long long m = mask[wave];
         if ((m >> lane) & 1ull) {
-            int pos = woff[wave] + __popcll(m & ((1ull << lane) - 1ull));
-            out[pos] = cand[i];
+            int pos = woff[wave] - (kind ? woff[nw0] : 0) + __popcll(m & ((1ull << lane) - 1ull));
+            (kind ? out1 : out0)[pos] = cand[i];
         }
     }
 }
 
-static void compact(ipc_ctx *c, int kind, const double *xw, const DBuf<int2> &cand, int64_t ncand, int cseg_region, int pseg_region,
-                    DBuf<int2> &out, int64_t &cap, int64_t &count, std::vector<int> &hseg)
+void narrow_phase(ipc_ctx *c, const double *xw)
 {
     Dev &D = c->d;
     hipStream_t st = c->stream;
-    int ns = c->n_scenes;
-    hseg.assign(ns + 1, 0);
-    count = 0;
-    int *sseg = seg_ptr(c, pseg_region);
-    if (ncand == 0) {
-        hipLaunchKernelGGL(k_fill_int, dim3(blocks_for(ns + 1)), dim3(BLOCK), 0, st, ns + 1, sseg, 0);
+    const int ns = c->n_scenes, n0 = (int)c->n_cand_pt, n1 = (int)c->n_cand_ee;
+    c->h_pt_seg.assign(ns + 1, 0);
+    c->h_ee_seg.assign(ns + 1, 0);
+    c->n_pt = c->n_ee = 0;
+    int *seg0 = seg_ptr(c, R_PT), *seg1 = seg_ptr(c, R_EE);
+    const int nw0 = (n0 + TILE - 1) / TILE, nw = nw0 + (n1 + TILE - 1) / TILE;
+    if (nw == 0) {
+        hipLaunchKernelGGL(k_fill_int, dim3(blocks_for(ns + 1)), dim3(BLOCK), 0, st, ns + 1, seg0, 0);
+        hipLaunchKernelGGL(k_fill_int, dim3(blocks_for(ns + 1)), dim3(BLOCK), 0, st, ns + 1, seg1, 0);
         return;
     }
-    int nw = (int)((ncand + TILE - 1) / TILE);
     DBuf<unsigned long long> &mask = D.mkey;   // scratch reuse
     mask.alloc(nw);
     D.wcount.alloc(nw + 1); D.woff.alloc(nw + 1);
-    hipLaunchKernelGGL(k_narrow<false>, dim3(blocks_for(ncand)), dim3(BLOCK), 0, st, (int)ncand, kind, cand.p, D.tri.p, D.edge.p,
-                       D.cv_scene.p, xw, D.sparam.p, mask.p, D.wcount.p, nullptr, nullptr);
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, 1, D.wcount.p + nw, 0);
-    exclusive_scan(c, D.wcount.p, D.woff.p, nw);
+    hipLaunchKernelGGL(k_narrow<false>, dim3(blocks_for((int64_t)nw * TILE)), dim3(BLOCK), 0, st, n0, n1, D.cand_pt.p, D.cand_ee.p, D.tri.p,
+                       D.edge.p, D.cv_scene.p, xw, D.sparam.p, mask.p, D.wcount.p, nullptr, nullptr, nullptr);
+    exclusive_scan_int(c, D.wcount.p, D.woff.p, nw);
     // candidates are grouped by scene and the order is kept, so each scene's
     // first survivor is the number of survivors before its first candidate
-    hipLaunchKernelGGL(k_compact_seg, dim3(blocks_for(ns + 1)), dim3(BLOCK), 0, st, ns, (int)ncand, seg_ptr(c, cseg_region), mask.p,
-                       D.woff.p, nw, sseg);
-    int total = 0;
+    hipLaunchKernelGGL(k_compact_seg, dim3(blocks_for(2 * (ns + 1))), dim3(BLOCK), 0, st, ns, n0, n1, seg_ptr(c, R_CPT), seg_ptr(c, R_CEE),
+                       mask.p, D.woff.p, seg0, seg1);
+    int total0 = 0, total = 0;
     {
         HostReads r(c);
+        r.add(&total0, D.woff.p + nw0, sizeof(int));
         r.add(&total, D.woff.p + nw, sizeof(int));
-        r.add(hseg.data(), sseg, (ns + 1) * sizeof(int));
+        r.add(c->h_pt_seg.data(), seg0, (ns + 1) * sizeof(int));
+        r.add(c->h_ee_seg.data(), seg1, (ns + 1) * sizeof(int));
         r.wait();
     }
-    if (total > cap) {
+    auto room = [&](int n, const char *what, DBuf<int2> &out, int64_t &cap) {
+        if (n <= cap) return;
         if (c->ws.base)
-            throw Error(IPC_E_CAPACITY, std::to_string(total) + (kind == 0 ? " point-triangle" : " edge-edge") +
-                                            " pairs exceed the planned capacity of " + std::to_string(cap));
-        cap = (int64_t)(total * 1.5) + 1024;
+            throw Error(IPC_E_CAPACITY, std::to_string(n) + what + " pairs exceed the planned capacity of " + std::to_string(cap));
+        cap = (int64_t)(n * 1.5) + 1024;
         out.alloc(cap);
-    }
-    count = total;
-    hipLaunchKernelGGL(k_narrow<true>, dim3(blocks_for(ncand)), dim3(BLOCK), 0, st, (int)ncand, kind, cand.p, D.tri.p, D.edge.p,
-                       D.cv_scene.p, xw, D.sparam.p, mask.p, D.wcount.p, D.woff.p, out.p);
-}
-
-void narrow_phase(ipc_ctx *c, const double *xw)
-{
-    compact(c, 0, xw, c->d.cand_pt, c->n_cand_pt, R_CPT, R_PT, c->d.pt, c->cap_pt, c->n_pt, c->h_pt_seg);
-    compact(c, 1, xw, c->d.cand_ee, c->n_cand_ee, R_CEE, R_EE, c->d.ee, c->cap_ee, c->n_ee, c->h_ee_seg);
+    };
+    room(total0, " point-triangle", D.pt, c->cap_pt);
+    room(total - total0, " edge-edge", D.ee, c->cap_ee);
+    c->n_pt = total0;
+    c->n_ee = total - total0;
+    hipLaunchKernelGGL(k_narrow<true>, dim3(blocks_for((int64_t)nw * TILE)), dim3(BLOCK), 0, st, n0, n1, D.cand_pt.p, D.cand_ee.p, D.tri.p,
+                       D.edge.p, D.cv_scene.p, xw, D.sparam.p, mask.p, D.wcount.p, D.woff.p, D.pt.p, D.ee.p);
 }
 
 // ---------------------------------------------------------------------------
@@ -1514,10 +1563,17 @@ __global__ void __launch_bounds__(64) k_cv_bodies(const int *__restrict__ ptr, c
     for (int q = 0; q < 12; ++q) o[q] += a[q];
 }
 
+__global__ void k_zero_d(int64_t n, double *p)
+{
+    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i < n) p[i] = 0.0;
+}
+
 void contact_grad_begin(ipc_ctx *c)
 {
     c->d.gcv.alloc(3 * (size_t)c->CV + 3);
-    c->d.gcv.zero(c->stream, 3 * (size_t)c->CV + 3);
+    const int64_t n = 3 * (int64_t)c->CV + 3;
+    hipLaunchKernelGGL(k_zero_d, dim3(blocks_for(n)), dim3(BLOCK), 0, c->stream, n, c->d.gcv.p);
 }
 
 void contact_grad_end(ipc_ctx *c, double *g)
@@ -2153,8 +2209,7 @@ void build_dyn_blocks(ipc_ctx *c)
         hipLaunchKernelGGL(k_dyn_count, dim3(blocks_for(n)), dim3(BLOCK), 0, st, (int)nb, (int)nf, D.pair_flag.p, D.lag_flag.p,
                            D.pair_cv.p, D.lag_cv.p, D.cv_node.p, D.cv_body.p, D.cv_x.p, D.body_node0.p, D.dyn_cnt.p, D.tickets.p,
                            D.cv_scene.p, c->assemble_only);
-        hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, 1, D.dyn_cnt.p + n, 0);
-        exclusive_scan(c, D.dyn_cnt.p, D.dyn_off.p, (int)n);
+        exclusive_scan_int(c, D.dyn_cnt.p, D.dyn_off.p, (int)n);
         int hv[2];
         HostReads rd(c);
         rd.add(&hv[0], D.dyn_off.p + n, sizeof(int));
@@ -2186,7 +2241,7 @@ void build_dyn_blocks(ipc_ctx *c)
         IPC_HIP(hipcub::DeviceRadixSort::SortPairs(D.sort_tmp.p, bytes, D.dyn_key64.p, D.dyn_key64b.p, D.dyn_idx.p, D.dyn_idx2.p,
                                                    (int)E, 0, end_bit, st));
         hipLaunchKernelGGL(k_dyn_heads, dim3(blocks_for(E + 1)), dim3(BLOCK), 0, st, (int)E, D.dyn_key64b.p, D.dyn_head.p);
-        exclusive_scan(c, D.dyn_head.p, D.dyn_pos.p, (int)E);
+        exclusive_scan_int(c, D.dyn_head.p, D.dyn_pos.p, (int)E);
         hipLaunchKernelGGL(k_dyn_starts, dim3(blocks_for(E + 1)), dim3(BLOCK), 0, st, (int)E, D.dyn_head.p, D.dyn_pos.p, D.dyn_start.p);
         hipLaunchKernelGGL(k_dyn_merge, dim3(blocks_for(E * TILE)), dim3(BLOCK), 0, st, D.dyn_pos.p + E, D.dyn_key64b.p, D.dyn_idx2.p,
                            D.dyn_start.p, D.dyn_val_coo.p, D.dyn_row.p, D.dyn_col.p, D.dyn_val.p);
@@ -2201,8 +2256,7 @@ void build_dyn_blocks(ipc_ctx *c)
     D.mkey.alloc(nw); D.wcount.alloc(nw + 1); D.woff.alloc(nw + 1); D.long_rows.alloc(N + 1);
     hipLaunchKernelGGL(k_long<false>, dim3(blocks_for(N)), dim3(BLOCK), 0, st, N, D.row_ptr.p, D.dyn_ptr.p, D.mkey.p, D.wcount.p,
                        nullptr, nullptr);
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, st, 1, D.wcount.p + nw, 0);
-    exclusive_scan(c, D.wcount.p, D.woff.p, nw);
+    exclusive_scan_int(c, D.wcount.p, D.woff.p, nw);
     {
         int hv[2] = {0, 0};
         HostReads rd(c);
@@ -2394,7 +2448,7 @@ void reserve_capacity(ipc_ctx *c, int64_t P, int64_t C, int64_t B)
     D.qcount.alloc(Q + 1); D.qoff.alloc(Q + 1); D.qstash.alloc(Q * TRAV_STASH);
     D.qkey.alloc(Q); D.qkey2.alloc(Q); D.qid.alloc(Q); D.qperm.alloc(Q);
     // scratch words shared by the Morton keys, the narrow phase's masks and the long rows' masks
-    const int64_t nw = std::max<int64_t>(C, c->N) / TILE + 1;
+    const int64_t nw = std::max<int64_t>(2 * C, c->N) / TILE + 2;   // both kinds of candidate
     D.mkey.alloc(std::max<int64_t>(Pp, nw)); D.mkey2.alloc(Pp);
     D.wcount.alloc(nw + 1); D.woff.alloc(nw + 1);
     c->cap_cand_pt = c->cap_cand_ee = C;

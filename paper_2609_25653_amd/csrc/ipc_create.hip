@@ -644,7 +644,7 @@ void create_context(ipc_ctx *c, const ipc_scene_desc *scenes, int n, const int64
         const int64_t P = std::max<int64_t>(caps[0], 1), C = std::max<int64_t>(caps[1], 1), B = std::max<int64_t>(caps[2], 1);
         const int64_t N = node, T = tet, NB = std::max(body, 1), NS = std::max(sp, 1), CVn = std::max(cv, 1), NZ = std::max(c->nnzb, 1);
         const int64_t Pp = std::max<int64_t>(std::max(tri, edge), 1), Q = std::max<int64_t>(std::max(cv, edge), 1);
-        const int64_t NW = std::max<int64_t>(C, N) / TILE + 1, PC = std::max(P, C);
+        const int64_t NW = std::max<int64_t>(2 * C, N) / TILE + 2, PC = std::max(P, C);
         const int64_t ndom = N / (CG_AGG * CG_DOM) + 2 * (int64_t)n, ngrp = N / CG_AGG + 2 * (int64_t)n;
         const int64_t MH = std::max<int64_t>(c->M_HS, 1);
         const std::vector<int64_t> nbuf = {

@@ -21,10 +21,12 @@ namespace ipc {
 // nodes: inertia of FEM vertices; initialises g (FEM nodes) and zeroes the rest
 // ---------------------------------------------------------------------------
 __global__ void k_node_inertia(int N, const double *__restrict__ y, const double *__restrict__ xt, const double *__restrict__ mass,
-                               const int *__restrict__ kind, double *__restrict__ g, double *__restrict__ part)
+                               const int *__restrict__ kind, double *__restrict__ g, double *__restrict__ part, int n_scenes,
+                               int *__restrict__ inf_flag)
 {
     int n = blockIdx.x * blockDim.x + threadIdx.x;
     double e = 0.0;
+    if (n < n_scenes) inf_flag[n] = 0;   // for the evaluation that this launch begins
     if (n < N) {
         d3 gv = {0.0, 0.0, 0.0};
         if (kind[n] == 0) {
@@ -358,8 +360,8 @@ __global__ void k_spring(int NS, const int *__restrict__ ka, const int *__restri
 // ---------------------------------------------------------------------------
 void launch_node_inertia(ipc_ctx *c, const double *y, double *g, double *part)
 {
-    hipLaunchKernelGGL(k_node_inertia, dim3(blocks_for(c->N)), dim3(BLOCK), 0, c->stream, c->N, y, c->d.xt.p, c->d.mass.p,
-                       c->d.node_kind.p, g, part);
+    hipLaunchKernelGGL(k_node_inertia, dim3(blocks_for(std::max(c->N, c->n_scenes))), dim3(BLOCK), 0, c->stream, c->N, y, c->d.xt.p, c->d.mass.p,
+                       c->d.node_kind.p, g, part, c->n_scenes, c->d.inf_flag.p);
 }
 
 void launch_fem(ipc_ctx *c, int mode, const double *y, double *g, bool project, double *part, const double *h2s)

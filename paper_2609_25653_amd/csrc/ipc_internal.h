@@ -503,19 +503,21 @@ PcgResident pcg_resident(ipc_ctx *c, double *x, const int *on);
 void pcg_resident_setup(ipc_ctx *c);
 size_t pcg_resident_bytes(int n_scenes, int N, int NB);   // its memory in a workspace
 // exclusive scan of n ints into out[0..n] (out[n] = total), on the context's stream
-void exclusive_scan_int(ipc_ctx *c, const int *in, int *out, int n);
+void exclusive_scan_int(ipc_ctx *c, int *in, int *out, int n);
 void pcg_wginfo(ipc_ctx *c);
 // constant part of the matrix (lumped mass, spring blocks) from the current
 // spring points; h2s: h^2 per scene
 void build_const_part(ipc_ctx *c, const double *h2s);   // refresh the step workgroups' scene records (after the long rows change)
 
-// Several device values to the host with one synchronisation, staged in the
-// context's pinned readback arena (asynchronous copies); reads that do not
-// fit go straight to their destination.  One instance at a time per context.
+// Several device values to the host with one synchronisation, through the
+// context's pinned readback arena: wait() reads them, in one launch for the
+// small ones (nothing may change them between add() and wait()); reads that
+// do not fit go straight to their destination.  One instance at a time per
+// context.
 struct HostReads {
     ipc_ctx *c;
     size_t used = 0;
-    struct Item { void *dst; size_t off, bytes; };
+    struct Item { void *dst; size_t off, bytes; const void *src; };   // src: read by wait()
     std::vector<Item> items;
     explicit HostReads(ipc_ctx *cc);
     void add(void *dst, const void *src, size_t bytes);
