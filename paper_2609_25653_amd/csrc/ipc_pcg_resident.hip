@@ -60,9 +60,10 @@ constexpr int PX_NT = 512;                 // threads: a tile's 64 rows x 8 lane
 constexpr int PX_HALO = 1024;              // nodes of other workgroups a workgroup's short rows may read
 constexpr int PX_HASH = 2048;              // their lookup table (set-up)
 constexpr int PX_BODIES = 16;              // affine bodies among a workgroup's nodes
-constexpr int PX_EXTRA = 1536;             // blocks past the two in registers, over all its short rows: the first 512 in
+constexpr int PX_EXTRA = 3840;             // blocks past the two in registers, over all its short rows: the first 512 in
                                            // registers too, one per thread,
-constexpr int PX_POOL = 128;               // the next ones in LDS, the others read from memory
+constexpr int PX_POOL = 128;               // the next ones in LDS, the others read from memory,
+constexpr int PX_CHUNK = 1024;             // and added to their rows this many at a time
 constexpr int PX_VROWS = (PX_NT - 192) / 8 / 3;   // of these, with a coarse group: one row of 8 lanes per component
 constexpr int PX_LONG = 512;               // long rows per scene (on average)
 constexpr int PX_SPARE = 16;               // workgroups kept free of tiles for them
@@ -165,7 +166,7 @@ struct PxLds {
     double wv[3 * TILE * T];                      // A z of the own rows
     double px[12 * TILE * T];                     // p, x, r and s of the own nodes
     union {                                       // (by turns, with barriers between)
-        double res[3 * (PX_EXTRA + 1)];           // the extra blocks times z, then a zero
+        double res[3 * (PX_CHUNK + 1)];           // a chunk of the extra blocks times z, then a zero
         double rcb[CG_N * PX_VROWS];              // group sums of the own bodies' domains
     };
     double pool[9 * PX_POOL];                     // extra blocks 512 ...
@@ -317,8 +318,8 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
     int tid = tid0, lane = tid & (TILE - 1), wave = tid / TILE;
     // ---- set-up ---------------------------------------------------------------
     if (tid < 3) S.zs[3 * (OWN + PX_HALO) + tid] = 0.0;
-    if (tid < 3) S.res[3 * PX_EXTRA + tid] = 0.0;   // (past rcb)
-    static_assert(3 * PX_EXTRA >= CG_N * PX_VROWS, "the zero stays");
+    if (tid < 3) S.res[3 * PX_CHUNK + tid] = 0.0;   // (past rcb)
+    static_assert(3 * PX_CHUNK >= CG_N * PX_VROWS, "the zero stays");
     if (tid == 0) { S.nhalo = 0; S.nextra = 0; S.nbody = 0; S.nv = 0; S.fit = 0; S.gone[0] = S.gone[1] = S.gone[2] = 0; }
     for (int i = tid; i < PX_HASH; i += PX_NT) S.h.key[i] = -1;
     __syncthreads();
@@ -645,24 +646,35 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
             }
             asm volatile("" : "+v"(zx));
             if (tid < S.nextra) st3(S.res, tid, px_mat3v(Bx, z_at(zx)));
-            for (int e = tid + PX_NT; e < S.nextra; e += PX_NT)
-                st3(S.res, e, px_mat3v(e < PX_NT + PX_POOL ? S.pool + 9 * (e - PX_NT) : extra_at(e), z_at(S.eidx[e])));
-            __syncthreads();
+            for (int lo = 0;;) {
+                const int hi = min(lo + PX_CHUNK, S.nextra);
+                for (int e = max(lo, PX_NT) + tid; e < hi; e += PX_NT)
+                    st3(S.res, e - lo, px_mat3v(e < PX_NT + PX_POOL ? S.pool + 9 * (e - PX_NT) : extra_at(e), z_at(S.eidx[e])));
+                __syncthreads();
 #pragma unroll
-            for (int j0 = 0; j0 < T; j0 += 2) {
-                constexpr int P = T < 2 ? T : 2;
-                int cmax = 0;
+                for (int j0 = 0; j0 < T; j0 += 2) {
+                    constexpr int P = T < 2 ? T : 2;
+                    int x0[P], cnt[P], cmax = 0;   // the sums' entries in the chunk
 #pragma unroll
-                for (int j = j0; j < j0 + P; ++j) cmax = max(cmax, ex[j] >> 16);
-                // (a lane that has none left adds the zero, so that no branch
-                // keeps the sums' reads from overlapping)
-                for (int x = 0; __any(x < cmax); ++x) {
+                    for (int u = 0; u < P; ++u) {
+                        const int f = ex[j0 + u] & 0xffff, l = f + (ex[j0 + u] >> 16);
+                        x0[u] = max(f, lo) - lo;
+                        cnt[u] = max(min(l, hi) - lo - x0[u], 0);
+                        cmax = max(cmax, cnt[u]);
+                    }
+                    // (a lane that has none left adds the zero, so that no branch
+                    // keeps the sums' reads from overlapping)
+                    for (int x = 0; __any(x < cmax); ++x) {
 #pragma unroll
-                    for (int j = j0; j < j0 + P; ++j) {
-                        const d3 r = ld3(S.res, x < (ex[j] >> 16) ? (ex[j] & 0xffff) + x : PX_EXTRA);
-                        p[j][0] += r.x; p[j][1] += r.y; p[j][2] += r.z;
+                        for (int u = 0; u < P; ++u) {
+                            const d3 r = ld3(S.res, x < cnt[u] ? x0[u] + x : PX_CHUNK);
+                            p[j0 + u][0] += r.x; p[j0 + u][1] += r.y; p[j0 + u][2] += r.z;
+                        }
                     }
                 }
+                lo += PX_CHUNK;
+                if (lo >= S.nextra) break;
+                __syncthreads();   // the chunk's products are read before the next one's are written
             }
             // a row's A z (the tree of lane_sum<8>), its z.Az, and the tile's sum over 8 rows (wave_sum)
             auto finish = [&](int q, bool first, d3 w) -> double {

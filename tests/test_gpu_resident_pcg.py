@@ -89,3 +89,33 @@ def test_scenes_of_a_batch_match_iteration_launches(coarse, monkeypatch):
         got.append(out)
     for ((ya, va), sa), ((yb, vb), sb) in zip(*got):
         assert sa == sb and torch.equal(ya, yb) and torch.equal(va, vb)
+
+
+def test_rows_in_contact_past_a_chunk(monkeypatch):
+    """The 200k-tet squeeze after 34 steps: one workgroup's rows have some 2200
+    blocks past those in registers, three chunks of 1024; early on none has
+    more than one."""
+    import torch
+
+    from paper_2609_25653_amd import Sim
+    from paper_2609_25653_amd._lib import Q_PCG_RESIDENT
+    sc = S.contact_rich(n_steps=100)
+    got = []
+    y = v = None
+    for eager in ("0", "1"):
+        monkeypatch.setenv("IPC_NO_GRAPH", eager)
+        sim = Sim(sc)
+        if y is None:
+            for n in range(34):
+                sim.step(n, allow_status=(3,))
+            y, v = sim.state()
+        else:
+            sim.set_state(y, v)
+        sim.begin_step(34)
+        b = torch.randn(sim.ndof, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(6))
+        before = sim._query(Q_PCG_RESIDENT)
+        x, it = sim.pcg(y, b, 1e-6)
+        assert sim._query(Q_PCG_RESIDENT) - before == (1 if eager == "0" else 0)
+        got.append((x.clone(), int(it[0])))
+    assert got[0][1] == got[1][1] > 10
+    assert torch.equal(got[0][0], got[1][0])
