@@ -664,12 +664,16 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
                     }
                     // (a lane that has none left adds the zero, so that no branch
                     // keeps the sums' reads from overlapping)
-                    for (int x = 0; __any(x < cmax); ++x) {
+                    for (int x = 0; __any(x < cmax); x += 2) {
+                        d3 r[2][P];
 #pragma unroll
-                        for (int u = 0; u < P; ++u) {
-                            const d3 r = ld3(S.res, x < cnt[u] ? x0[u] + x : PX_CHUNK);
-                            p[j0 + u][0] += r.x; p[j0 + u][1] += r.y; p[j0 + u][2] += r.z;
-                        }
+                        for (int h = 0; h < 2; ++h)
+#pragma unroll
+                            for (int u = 0; u < P; ++u) r[h][u] = ld3(S.res, x + h < cnt[u] ? x0[u] + x + h : PX_CHUNK);
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+#pragma unroll
+                            for (int u = 0; u < P; ++u) { p[j0 + u][0] += r[h][u].x; p[j0 + u][1] += r[h][u].y; p[j0 + u][2] += r[h][u].z; }
                     }
                 }
                 lo += PX_CHUNK;
