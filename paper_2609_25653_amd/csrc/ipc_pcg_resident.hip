@@ -63,7 +63,7 @@ constexpr int PX_BODIES = 16;              // affine bodies among a workgroup's 
 constexpr int PX_EXTRA = 3840;             // blocks past the two in registers, over all its short rows: the first 512 in
                                            // registers too, one per thread,
 constexpr int PX_POOL = 128;               // the next ones in LDS, the others read from memory,
-constexpr int PX_CHUNK = 1024;             // and added to their rows this many at a time
+constexpr int PX_CHUNK = 2 * PX_NT;        // and added to their rows this many at a time
 constexpr int PX_VROWS = (PX_NT - 192) / 8 / 3;   // of these, with a coarse group: one row of 8 lanes per component
 constexpr int PX_LONG = 512;               // long rows per scene (on average)
 constexpr int PX_SPARE = 16;               // workgroups kept free of tiles for them
@@ -648,8 +648,24 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
             if (tid < S.nextra) st3(S.res, tid, px_mat3v(Bx, z_at(zx)));
             for (int lo = 0;;) {
                 const int hi = min(lo + PX_CHUNK, S.nextra);
-                for (int e = max(lo, PX_NT) + tid; e < hi; e += PX_NT)
-                    st3(S.res, e - lo, px_mat3v(e < PX_NT + PX_POOL ? S.pool + 9 * (e - PX_NT) : extra_at(e), z_at(S.eidx[e])));
+                if constexpr (TWO) {
+                    // 256 rows in contact: a chunk is two rounds of blocks from memory, whose loads go out
+                    // together (260 -> 266 Newton iterations/s on the 200k-tet squeeze; with fewer tiles, which
+                    // rarely have a second round, 1-3 % slower)
+                    if (lo == 0 && tid < min(PX_POOL, hi - PX_NT)) st3(S.res, PX_NT + tid, px_mat3v(S.pool + 9 * tid, z_at(S.eidx[PX_NT + tid])));
+                    const int e0 = max(lo, PX_NT + PX_POOL) + tid, e1 = e0 + PX_NT;
+                    if (e0 < hi) {
+                        const double *const M0 = extra_at(e0), *const M1 = extra_at(min(e1, hi - 1));
+                        double m0[9], m1[9];
+#pragma unroll
+                        for (int q = 0; q < 9; ++q) { m0[q] = M0[q]; m1[q] = M1[q]; }
+                        st3(S.res, e0 - lo, px_mat3v(m0, z_at(S.eidx[e0])));
+                        if (e1 < hi) st3(S.res, e1 - lo, px_mat3v(m1, z_at(S.eidx[e1])));
+                    }
+                } else {
+                    for (int e = max(lo, PX_NT) + tid; e < hi; e += PX_NT)
+                        st3(S.res, e - lo, px_mat3v(e < PX_NT + PX_POOL ? S.pool + 9 * (e - PX_NT) : extra_at(e), z_at(S.eidx[e])));
+                }
                 __syncthreads();
 #pragma unroll
                 for (int j0 = 0; j0 < T; j0 += 2) {
