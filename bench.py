@@ -447,7 +447,7 @@ def bench_dualmesh(args):
     except (OSError, ValueError):
         pass
     roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-            "traffic": traffic, "kernel": "k_dm_apply (W X^c for every frame)", "bytes_per_launch": by, "avg_us": us,
+            "traffic": traffic, "kernel": "k_dm_pairs (W X^c for every frame)", "bytes_per_launch": by, "avg_us": us,
             "launches_timed": 50}
     per_launch = frames.shape[0] * dm.n_fine
     line = {
@@ -484,14 +484,14 @@ def write_dm_traffic(fetch_csv, write_csv):
 
     f, w = per_kernel(fetch_csv), per_kernel(write_csv)
     copy = [k for k in f if "copyBuffer" in k]
-    dmk = [k for k in f if "k_dm_apply" in k]
+    dmk = [k for k in f if "k_dm_pairs" in k]
     kib = 256 * 1024
     fac_f = kib / max(max(f[k]) for k in copy)
     fac_w = kib / max(max(w[k]) for k in copy)
     sf = [v for k in dmk for v in f[k]]
     sw = [v for k in dmk for v in w[k]]
     traffic = 1024.0 * (fac_f * sum(sf) / len(sf) + fac_w * sum(sw) / len(sw))
-    rec = {"kernel": "k_dm_apply", "bytes_per_launch": traffic, "fetch_kib": sum(sf) / len(sf), "write_kib": sum(sw) / len(sw),
+    rec = {"kernel": "k_dm_pairs", "bytes_per_launch": traffic, "fetch_kib": sum(sf) / len(sf), "write_kib": sum(sw) / len(sw),
            "fetch_scale": fac_f, "write_scale": fac_w, "launches": len(sf),
            "source_sha256": hashlib.sha256(open(DM_SRC, "rb").read()).hexdigest(),
            "source": "python bench.py --workload dualmesh --traffic-run under rocprofv3 --pmc"}

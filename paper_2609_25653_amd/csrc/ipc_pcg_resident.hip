@@ -1,13 +1,19 @@
-// The whole PCG solve of a one-scene context in one launch.
+// The whole PCG solve of a context in one launch (a batch's scenes: at most
+// two), each scene to its own end.
 //
-// What bounds the launch-per-iteration form (k_pcg_step + k_spmv) on one
-// scene is not the arithmetic: on the 20k-tet squeeze an iteration moves a
-// few MB, yet takes 12 us, two launches of 5 us that are mostly start-up,
-// dependent loads and drain; on the 200k-tet scene the product also reads the
-// 45 MB matrix again every iteration (11.5 us of 23).  Here every workgroup
-// keeps its rows of the matrix in registers (two blocks per lane) and LDS
-// (the rest) for the whole solve, with its nodes' p, s, x and r, and only the
-// vector z, the dot products' partials and the coarse sums travel.
+// What bounds the launch-per-iteration form (k_pcg_step + k_spmv) is not the
+// arithmetic: on the 20k-tet squeeze an iteration moves a few MB, yet takes 12
+// us, two launches of 5 us that are mostly start-up, dependent loads and drain;
+// on the 200k-tet scene the product also reads the 45 MB matrix again every
+// iteration (11.5 us of 23).  Here every workgroup keeps its rows of the matrix
+// in registers (two blocks per lane) and LDS (the rest) for the whole solve,
+// with its nodes' p, s, x and r, and only the vector z, the dot products'
+// partials and the coarse sums travel.
+//
+// Measured, us per iteration, that form and this one: 625-tet block 8.5 and
+// 3.9, most of it two exchanges; 20k-tet squeeze 12-14 and 6.4 (the body rows' chain: z -> poll -> sum -> partial -> poll);
+// 200k tets, coarse, 22-23 and 12.3, or 16 once a workgroup's rows have 2000
+// contact blocks, most of them read from memory again in every iteration.
 //
 // Exchange.  Workgroups exchange 8-byte words through memory with relaxed
 // agent-scope atomics, which bypass the (per-XCD, mutually incoherent) L2s
