@@ -160,11 +160,17 @@ enum {
                               the environment variable IPC_NO_FUSED_PCG = 1, read
                               at ipc_create, keeps it in a launch of its own).
                               Both forms give the same bits.                  */
-    IPC_Q_PCG_RESIDENT = 16 /* PCG solves of this context so far whose iterations
+    IPC_Q_PCG_RESIDENT = 16, /* PCG solves of this context so far whose iterations
                               all ran inside one launch per group of scenes
                               (every scene fits the chip; also the same bits;
                               IPC_NO_GRAPH = 1 and IPC_NO_FUSED_PCG = 1 keep
                               it off)                                         */
+    IPC_Q_PCG_SKIP = 17    /* PCG solves that this context will take a launch per
+                              iteration before it tries the one-launch form
+                              again: 0 unless that form gave up, when the
+                              solve started again (256: a workgroup's rows did
+                              not fit; 64: a workgroup waited too long for the
+                              others)                                         */
 };
 
 /* Flags of ipc_energy_grad_hess. */

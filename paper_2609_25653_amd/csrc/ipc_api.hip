@@ -688,6 +688,7 @@ extern "C" int ipc_query(const ipc_ctx *c, int what, int64_t *v)
     case IPC_Q_SPMV_LANES: *v = c->spmv_lanes; return IPC_OK;
     case IPC_Q_FEM_BLOCKS: *v = ((int64_t)c->fem_block << 32) | ((int64_t)c->asm_block << 16) | c->grad_block; return IPC_OK;
     case IPC_Q_PCG_RESIDENT: *v = c->resident_solves; return IPC_OK;
+    case IPC_Q_PCG_SKIP: *v = c->resident_skip; return IPC_OK;
     case IPC_Q_PCG_FUSED: *v = c->cg_fusable && c->coarse_on && c->pcg_fused && c->n_cdom > 0 ? 1 : 0; return IPC_OK;
     }
     return IPC_E_INVALID;

@@ -102,6 +102,10 @@ __host__ __device__ inline int px_dlen(int ntile, int nlong, int ncd, int nb) { 
 __device__ __forceinline__ u64 px_ld(const u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void px_st(u64 *p, u64 v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void px_put(u64 *p, double v) { px_st(p, (u64)__double_as_longlong(v)); }
+// The abort word (ctl[0]): 0, 1 a wait was given up, 2 the rows of a workgroup
+// do not fit.  It only grows: workgroups that leave because the word is up
+// raise it too, and must not turn a 2 into a 1.
+__device__ __forceinline__ void px_abort(int *ctl, int why) { (void)__hip_atomic_fetch_max(ctl, why, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // Poll the words ld(0) .. ld(K - 1) until none that is needed is empty.
 // Every wait ends: after PX_WAIT, or once any workgroup has given up
@@ -121,7 +125,7 @@ __device__ __forceinline__ void px_poll(Ld ld, Need need, double (&v)[K], int *c
         if ((tries & 31) == 31) {
             const long long t = (long long)wall_clock64();
             if (t0 == 0) t0 = t;
-            if (t - t0 > PX_WAIT) __hip_atomic_store(ctl, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (t - t0 > PX_WAIT) px_abort(ctl, 1);
             if (t - t0 > PX_WAIT || __hip_atomic_load(ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
                 *gone = 1;
                 break;
@@ -480,7 +484,7 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
     }
     __syncthreads();
     if (S.fit) {   // does not fit: everybody leaves
-        if (tid == 0) __hip_atomic_store(A.ctl, S.fit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) px_abort(A.ctl, S.fit);
         return;
     }
 
@@ -815,7 +819,7 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
     }
     // ---- the end: x, and this workgroup's vote that it has reached it ----
     if (gone) {
-        if (tid0 == 0) __hip_atomic_store(A.ctl, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid0 == 0) px_abort(A.ctl, 1);
         return;
     }
     if (own && kd0 != 2) st3(A.x, n, ld3(S.px, OWN + tid0));

@@ -1,0 +1,92 @@
+"""When the PCG solve in one launch gives up (ipc_pcg_resident.hip): the solve
+starts again in the launch-per-iteration form, with that form's bits, and the
+context leaves the one-launch form alone for a while."""
+import numpy as np
+import pytest
+
+import ipcscenes as S
+
+pytestmark = pytest.mark.gpu
+
+
+def _block(n, z=0.3):
+    """n^3 cells of 1 cm, away from the ground."""
+    sc = S.block_drop(n_steps=2)
+    g = np.stack(np.meshgrid(*[np.arange(n + 1)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    X = 0.01 * g + [0.1, 0.1, z]
+    T = S.hex_tets(n, n, n)
+    e = X[T[:, 1:]] - X[T[:, :1]]
+    neg = np.linalg.det(e) < 0
+    T[neg, 1], T[neg, 2] = T[neg, 2].copy(), T[neg, 1].copy()
+    nt = len(T)
+    sc.update(X=X, V=np.zeros_like(X), tets=np.ascontiguousarray(T), tet_E=np.full(nt, 1e5), tet_nu=np.full(nt, 0.45),
+              tet_rho=np.full(nt, 1000.0), vobj=np.zeros(len(X), np.int32))
+    return sc
+
+
+def _crossed(n=12, per=40, seed=0):
+    """The block with weak springs from every vertex to 40 random ones: rows of
+    at most 64 blocks, 64 of which read more vertices of other rows than a
+    workgroup has places for (1024)."""
+    sc = _block(n)
+    rng = np.random.default_rng(seed)
+    nv = len(sc["X"])
+    a = np.tile(np.arange(nv), per // 2)
+    b = np.concatenate([rng.permutation(nv) for _ in range(per // 2)])
+    a, b = a[a != b], b[a != b]
+    ns = len(a)
+    sc.update(sp_ka=np.zeros(ns, np.int32), sp_ia=a.astype(np.int32), sp_xa=np.zeros((ns, 3)), sp_kb=np.zeros(ns, np.int32),
+              sp_ib=b.astype(np.int32), sp_xb=np.zeros((ns, 3)), sp_k=np.full(ns, 1.0))
+    return sc
+
+
+def test_crossed_block_has_short_rows_that_do_not_fit():
+    """(the input of the tests below, on the host: a tile's 64 rows are
+    vertices near each other)"""
+    sc = _crossed()
+    X = sc["X"]
+    adj = [set() for _ in range(len(X))]
+    for t in sc["tets"]:
+        for i in t:
+            adj[i].update(int(j) for j in t)
+    for i, j in zip(sc["sp_ia"], sc["sp_ib"]):
+        adj[i].add(int(j))
+        adj[j].add(int(i))
+    assert max(len(a) for a in adj) <= 64 and len(X) <= 64 * 240
+    for k in range(0, len(X), 200):
+        own = set(np.argsort(np.abs(X - X[k]).max(1), kind="stable")[:64].tolist())
+        assert len(set().union(*(adj[i] for i in own)) - own) > 1024
+
+
+def _solve(sc, b_seed, eta=1e-8):
+    import torch
+    from paper_2609_25653_amd import Sim
+    sim = Sim(sc)
+    y, _ = sim.state()
+    sim.begin_step(0)
+    b = torch.randn(sim.ndof, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(b_seed))
+    return sim, y, b
+
+
+@pytest.mark.parametrize("with_others", [False, True])
+def test_rows_that_do_not_fit(with_others, monkeypatch):
+    """One workgroup's set-up refuses, the others wait for it and leave: the
+    verdict stays "does not fit", whatever the order in which they leave."""
+    import torch
+    from paper_2609_25653_amd._lib import Q_PCG_RESIDENT, Q_PCG_SKIP
+    monkeypatch.setenv("IPC_PCG_COARSE", "0")
+    sc = _crossed()
+    if with_others:   # scenes that fit, of which the first ends before the refusal is seen
+        sc = [S.tiny_scene("tet", h=0.01, n_steps=2), sc, _block(6)]
+    got = []
+    for eager in ("1", "0"):
+        monkeypatch.setenv("IPC_NO_GRAPH", eager)
+        sim, y, b = _solve(sc, 3)
+        x, it = sim.pcg(y, b, 1e-8)
+        assert sim._query(Q_PCG_RESIDENT) == 0
+        assert sim._query(Q_PCG_SKIP) == (0 if eager == "1" else 256)
+        x2, it2 = sim.pcg(y, b, 1e-8)
+        assert torch.equal(x, x2) and np.array_equal(it, it2)
+        assert sim._query(Q_PCG_SKIP) == (0 if eager == "1" else 255)
+        got.append((x.clone(), it.copy()))
+    assert torch.equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1]) and got[0][1].max() > 10
