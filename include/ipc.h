@@ -170,7 +170,9 @@ enum {
                               again: 0 unless that form gave up, when the
                               solve started again (256: a workgroup's rows did
                               not fit; 64: a workgroup waited too long for the
-                              others)                                         */
+                              others, which the environment variable
+                              IPC_PCG_GIVE_UP = 1, read at ipc_create, makes
+                              every such solve report, for tests)             */
 };
 
 /* Flags of ipc_energy_grad_hess. */

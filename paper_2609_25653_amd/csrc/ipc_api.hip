@@ -531,6 +531,8 @@ static void read_options(ipc_ctx *c)
     c->coarse_forced = nc && nc[0] == '1';
     const char *nfp = std::getenv("IPC_NO_FUSED_PCG");   // 1: the coarse correction in a launch of its own
     c->pcg_fused = !(nfp && nfp[0] == '1');
+    const char *gu = std::getenv("IPC_PCG_GIVE_UP");   // 1: every one-launch solve gives up, as if its workgroups had waited too long
+    c->resident_give_up = gu && gu[0] == '1';
     const char *nf = std::getenv("IPC_NO_FLOOR_STOP");   // 1: no stop at the energy's rounding floor
     c->floor_stop = !(nf && nf[0] == '1');
     const char *tr = std::getenv("IPC_TRACE_NEWTON");   // a scene index: its Newton iterations on stderr

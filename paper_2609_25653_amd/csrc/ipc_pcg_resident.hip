@@ -832,11 +832,12 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
     }
 }
 
-// empties the exchange words and clears the control words
-__global__ void __launch_bounds__(BLOCK) k_pcgx_fill(int64_t n, u64 *__restrict__ p, int *__restrict__ ctl)
+// empties the exchange words and clears the control words (abort: the first
+// one's value)
+__global__ void __launch_bounds__(BLOCK) k_pcgx_fill(int64_t n, u64 *__restrict__ p, int *__restrict__ ctl, int abort)
 {
     for (int64_t i = blockIdx.x * (int64_t)BLOCK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLOCK) p[i] = PX_EMPTY;
-    if (blockIdx.x == 0 && threadIdx.x < 2) ctl[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 2) ctl[threadIdx.x] = threadIdx.x == 0 ? abort : 0;
 }
 
 // after the solve: 1 when every workgroup reached its end, 2 when one ran
@@ -1017,7 +1018,8 @@ PcgResident pcg_resident(ipc_ctx *c, double *x, const int *on)
     A.x = x; A.scal = D.scal.p; A.iters = D.pcg_iters.p; A.ctl = D.px_ctl.p;
     A.D = D.px_words.p; A.Z = A.D + nd; A.RC = A.Z + nz;
     upload_async(c, D.px_wg.p, wg.data(), wgs * sizeof(PxPart));
-    hipLaunchKernelGGL(k_pcgx_fill, dim3(std::min(blocks_for(nd + nz + nr), 1024)), dim3(BLOCK), 0, st, nd + nz + nr, A.D, A.ctl);
+    hipLaunchKernelGGL(k_pcgx_fill, dim3(std::min(blocks_for(nd + nz + nr), 1024)), dim3(BLOCK), 0, st, nd + nz + nr, A.D, A.ctl,
+                       c->resident_give_up ? 1 : 0);
     for (size_t k = 0; k + 1 < round.size(); ++k) {
         const int w = round[k + 1] - round[k];
         A.wg = (const PxPart *)D.px_wg.p + round[k];

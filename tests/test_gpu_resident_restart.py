@@ -90,3 +90,81 @@ def test_rows_that_do_not_fit(with_others, monkeypatch):
         assert sim._query(Q_PCG_SKIP) == (0 if eager == "1" else 255)
         got.append((x.clone(), it.copy()))
     assert torch.equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1]) and got[0][1].max() > 10
+
+
+@pytest.mark.parametrize("coarse", ["0", "1"])
+@pytest.mark.parametrize("name", ["one_tile", "squeeze", "batch"])
+def test_restart_after_giving_up(name, coarse, monkeypatch):
+    """The abort word is up from the start: workgroups that need not wait
+    (scenes of one tile) run to their end and write their solutions and
+    counts, the others leave at the first wait; then the solve starts again.
+    Steps and counts are those of the launch-per-iteration form."""
+    import torch
+    from paper_2609_25653_amd import Sim
+    from paper_2609_25653_amd._lib import Q_PCG_RESIDENT, Q_PCG_SKIP
+    if name == "one_tile":
+        sc = S.tiny_scene("cube", h=0.01, n_steps=3)
+    elif name == "squeeze":
+        sc = S.gripper_squeeze(n_steps=3, pad_cells=(4, 2, 3))
+    else:
+        sc = [S.tiny_scene("cube", h=0.005, n_steps=3), S.gripper_squeeze(n_steps=3, pad_cells=(6, 3, 3)), S.block_drop(n_steps=3),
+              S.tiny_scene("free_body", h=0.005, n_steps=3)]
+    monkeypatch.setenv("IPC_PCG_COARSE", coarse)
+    got = []
+    for eager in ("1", "0"):
+        monkeypatch.setenv("IPC_NO_GRAPH", eager)
+        monkeypatch.setenv("IPC_PCG_GIVE_UP", "1")
+        sim = Sim(sc)
+        out = []
+        for _ in range(3):
+            _, st = sim.step(allow_status=(3,))
+            out.append((sim.state(), [(q["newton_iters"], q["pcg_iters_total"], q["status"]) for q in st]))
+        assert sim._query(Q_PCG_RESIDENT) == 0
+        assert (sim._query(Q_PCG_SKIP) > 0) == (eager == "0")
+        got.append(out)
+    for ((ya, va), sa), ((yb, vb), sb) in zip(*got):
+        assert sa == sb and torch.equal(ya, yb) and torch.equal(va, vb)
+
+
+def test_two_contexts_on_two_streams(monkeypatch):
+    """Two threads solve at the same time, each with its context on its own
+    stream: one launch holds the device at a time, the other context takes
+    the launch-per-iteration form meanwhile.  Solutions are those of a
+    context alone, whichever form each solve took."""
+    import threading
+
+    import torch
+    from paper_2609_25653_amd import Sim
+    from paper_2609_25653_amd._lib import Q_PCG_RESIDENT
+    scenes = [S.gripper_squeeze(n_steps=1, pad_cells=(12, 6, 6)), _block(9)]
+    N = 40
+
+    def solves(sc, n):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            sim = Sim(sc)
+            y, _ = sim.state()
+            sim.begin_step(0)
+            b = torch.randn(sim.ndof, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(7))
+            torch.cuda.current_stream().synchronize()
+            xs = [sim.pcg(y, b, 1e-8) for _ in range(n)]
+            torch.cuda.current_stream().synchronize()
+            return [(x.cpu(), int(it[0])) for x, it in xs], sim._query(Q_PCG_RESIDENT)
+
+    alone = [solves(sc, 1) for sc in scenes]
+    assert all(a[1] == 1 for a in alone)
+    got = [None, None]
+
+    def run(k):
+        got[k] = solves(scenes[k], N)
+
+    ts = [threading.Thread(target=run, args=(k,)) for k in range(2)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for k in range(2):
+        out, taken = got[k]
+        assert 0 <= taken <= N
+        for x, it in out:
+            assert it == alone[k][0][0][1] and torch.equal(x, alone[k][0][0][0])
+    assert got[0][1] + got[1][1] > 0
