@@ -869,6 +869,17 @@ static int px_wgs(const ipc_ctx *c, int s, int T)
     return px_coarse(c) ? std::max(w, CG_SPLIT * (c->seg_cdom[s + 1] - c->seg_cdom[s])) : w;
 }
 
+// Whether no workgroup of T tiles gets more bodies than it has places for,
+// with the coarse correction rows for their groups.  A scene's bodies follow
+// each other, 4 nodes each, from bnode0 on.
+static bool px_bodies_fit(const ipc_ctx *c, int s, int T)
+{
+    const SceneInfo &S = c->sc[s];
+    const int own = TILE * T, room = (own - (S.bnode0 - S.node0) % own) / 4;   // places in the first workgroup
+    const int most = std::max(std::min(S.nb, room), std::min(S.nb - room, own / 4));
+    return most <= (px_coarse(c) ? std::min(PX_BODIES, PX_VROWS) : PX_BODIES);
+}
+
 // Tiles per workgroup for this context, 0: not for this context.
 static int px_tiles(const ipc_ctx *c)
 {
@@ -882,7 +893,11 @@ static int px_tiles(const ipc_ctx *c)
         total += c->sc[s].nnode_pad / TILE;
     }
     for (int i = px_coarse(c) ? 2 : 0; i < 3; ++i)
-        if (largest[i] <= std::min(room, BLOCK) && (i == 2 || total + c->n_scenes <= Ts[i] * room)) return Ts[i];
+        if (largest[i] <= std::min(room, BLOCK) && (i == 2 || total + c->n_scenes <= Ts[i] * room)) {
+            for (int s = 0; s < c->n_scenes; ++s)
+                if (!px_bodies_fit(c, s, Ts[i])) return 0;   // (with more tiles each workgroup has more of them)
+            return Ts[i];
+        }
     return 0;
 }
 

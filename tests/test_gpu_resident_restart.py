@@ -168,3 +168,40 @@ def test_two_contexts_on_two_streams(monkeypatch):
         for x, it in out:
             assert it == alone[k][0][0][1] and torch.equal(x, alone[k][0][0][0])
     assert got[0][1] + got[1][1] > 0
+
+
+def _with_bodies(cells, nb):
+    """The block and nb free boxes above it, whose nodes follow each other."""
+    from ipcscenes import scenes as M
+    blk = _block(cells)
+    b = M._Builder()
+    b.add_fem(blk["X"], blk["tets"], 1e5, 0.45, 1000.0)
+    for k in range(nb):
+        b.add_body((0.1 * (k % 8), 0.1 * (k // 8), 0.9), (0.02, 0.03, 0.04), 0.05)
+    return b.finish(M._params(h=0.01, n_steps=1), np.zeros((1, 0, 12)))
+
+
+@pytest.mark.parametrize("cells,coarse,nb,taken", [
+    (9, "0", 40, True),      # 64 nodes per workgroup: 16 bodies fill them
+    (25, "0", 16, True),     # 128 per workgroup: as many bodies as it has places for
+    (25, "0", 40, False),
+    (9, "1", 13, True),      # 256 per workgroup, rows for 13 bodies' coarse groups
+    (9, "1", 30, False),
+])
+def test_bodies_in_one_workgroup(cells, coarse, nb, taken, monkeypatch):
+    """More bodies side by side than a workgroup has places for: the context
+    keeps to the launch-per-iteration form from the start (nothing is thrown
+    away: the skip count stays 0); up to there the forms agree bit for bit."""
+    import torch
+    from paper_2609_25653_amd._lib import Q_PCG_RESIDENT, Q_PCG_SKIP
+    monkeypatch.setenv("IPC_PCG_COARSE", coarse)
+    sc = _with_bodies(cells, nb)
+    got = []
+    for eager in ("1", "0"):
+        monkeypatch.setenv("IPC_NO_GRAPH", eager)
+        sim, y, b = _solve(sc, 4)
+        x, it = sim.pcg(y, b, 1e-8)
+        assert sim._query(Q_PCG_SKIP) == 0
+        assert sim._query(Q_PCG_RESIDENT) == (1 if eager == "0" and taken else 0)
+        got.append((x.clone(), int(it[0])))
+    assert torch.equal(got[0][0], got[1][0]) and got[0][1] == got[1][1] > 5
