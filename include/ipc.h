@@ -383,10 +383,10 @@ int ipc_time_kernel(ipc_ctx *ctx, int kernel, int reps, double *avg_us, double *
  * (nullable) the choice.  The default before any call is 8 lanes; the
  * environment variable IPC_SPMV_LANES (1, 2, 4, 8 or 16), read at
  * ipc_create, fixes the count instead: the autotuner still times every
- * count but keeps that one.  A context that takes its PCG
- * solves in one launch (IPC_Q_PCG_RESIDENT) keeps 8 lanes, whose sums that
- * launch forms, unless the variable fixes another count.  Otherwise the choice is also kept for the
- * process, keyed by the context's size bucket (the powers of two of the
+ * count but keeps that one.  A context that takes its PCG solves in one
+ * launch (IPC_Q_PCG_RESIDENT) forms the sums of 8 lanes in its solves
+ * whatever the choice, unless the variable fixes another count.  Otherwise
+ * the choice is also kept for the process, keyed by the context's size bucket (the powers of two of the
  * static pattern's block count and of the node count, and whether it holds
  * several scenes); a context created later in the same bucket starts with
  * it (IPC_Q_SPMV_LANES).  The same call then times the three kernels of the

@@ -1524,8 +1524,7 @@ extern "C" int ipc_autotune(ipc_ctx *c, int reps, double *us_host, int32_t *lane
         c->prof = false;
         int keep = c->spmv_lanes;
         autotune_spmv(c, reps, us_host);
-        // (the one-launch PCG solve sums as 8 lanes per row do)
-        if (c->spmv_lanes_forced || c->resident_lanes) c->spmv_lanes = keep;
+        if (c->spmv_lanes_forced) c->spmv_lanes = keep;
         autotune_fem(c, reps);
         {
             std::lock_guard<std::mutex> lk(g_tune_mu);

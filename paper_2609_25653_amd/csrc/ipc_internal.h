@@ -426,7 +426,7 @@ struct ipc_ctx {
     unsigned long long *h_peek_dev = nullptr;   // its device address
     unsigned int peek_seq = 0;
     bool resident_ok = false;             // the one-launch solve has its memory (ipc_pcg_resident.hip)
-    bool resident_lanes = false;          // and all scenes take it: the product's lanes stay at 8
+    bool resident_lanes = false;          // and all scenes take it: the PCG's products use 8 lanes
     int64_t resident_solves = 0;          // solves it has done
     bool resident_give_up = false;        // every one-launch solve gives up (for tests of the restart)
     int resident_skip = 0;                // solves to take in the launch-per-iteration form before it is tried again

@@ -970,8 +970,8 @@ void pcg_resident_setup(ipc_ctx *c)
         return;
     c->n_cu = std::min(cu, PX_WGMAX);
     if (!px_allow<1, false>() || !px_allow<2, false>() || !px_allow<4, false>() || !px_allow<4, true>()) return;
-    // Its sums are those of 8 lanes per row: the lanes stay at 8, unless a
-    // count is forced or the scenes take too many launches together (then it
+    // Its sums are those of 8 lanes per row: the PCG's products take 8, unless
+    // a count is forced or the scenes take too many launches together (then it
     // serves a Newton iteration's last scenes while the lanes are 8).
     const int lanes = c->spmv_lanes;
     c->spmv_lanes = 8;
@@ -981,7 +981,7 @@ void pcg_resident_setup(ipc_ctx *c)
     std::vector<PxPart> wg;
     std::vector<int> first;
     c->resident_lanes = c->resident_ok && !c->spmv_lanes_forced && px_plan(c, T, nullptr, wg, first);
-    if (!c->resident_lanes) c->spmv_lanes = lanes;
+    c->spmv_lanes = lanes;
     if (!c->resident_ok) return;
     std::vector<int> tab;
     for (int s = 0; s < ns; ++s) {

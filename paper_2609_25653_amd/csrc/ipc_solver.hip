@@ -998,8 +998,19 @@ int pcg_await(ipc_ctx *c, int slot, unsigned int seq, int n)
     return most;
 }
 
+// The lanes per row of a solve's products: 8 in a context whose solves run in
+// one launch, which sums as 8 lanes do, so that a solve that has to take the
+// launch-per-iteration form has the same bits; else the context's count.
+struct PcgLanes {
+    ipc_ctx *c;
+    const int keep;
+    explicit PcgLanes(ipc_ctx *cc) : c(cc), keep(cc->spmv_lanes) { if (c->resident_lanes) c->spmv_lanes = 8; }
+    ~PcgLanes() { c->spmv_lanes = keep; }
+};
+
 void pcg_solve(ipc_ctx *c, const double *b, double *x, double eta, const int *want, const int *on)
 {
+    const PcgLanes lanes(c);
     Dev &D = c->d;
     hipStream_t st = c->stream;
     const int ns = c->n_scenes, ntile = c->N / TILE;
