@@ -507,9 +507,12 @@ hipError_t upload(ipc_dualmesh *m)
 {
     if (m->d_w) return hipSuccess;
     const Layout L = owned(m);
-    hipError_t e = hipMalloc(&m->d_w, L.total);
-    if (e == hipSuccess) e = copy_in(m, L, m->d_w);
+    unsigned char *p = nullptr;
+    hipError_t e = hipMalloc(&p, L.total);
+    if (e == hipSuccess) e = copy_in(m, L, p);
     if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
+    if (e == hipSuccess) m->d_w = p;   // only a W that has arrived is taken for one by the next call
+    else if (p) (void)hipFree(p);
     return e;
 }
 
