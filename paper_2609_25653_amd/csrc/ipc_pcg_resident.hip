@@ -200,7 +200,7 @@ struct PxLds {
     unsigned char kind[TILE * T], bslot[TILE * T];   // own node: 0 FEM, 1 body, 2 none, 3 stands for a body's node; its body's place
     int nhalo, nextra, nbody, nv;
     int fit;                                      // raised in the set-up: the rows do not fit
-    int gone[3];                                  // raised by a poll that gave up: phases scalars and long rows, coarse, halo
+    int gone[4];                                  // raised by a poll that gave up: phases scalars, coarse, halo, long rows
 };
 
 static_assert(sizeof(PxLds<4>) <= 160 * 1024 && sizeof(PxLds<1>) > 80 * 1024, "one workgroup per compute unit");
@@ -330,7 +330,7 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
     if (tid < 3) S.zs[3 * (OWN + PX_HALO) + tid] = 0.0;
     if (tid < 3) S.res[3 * PX_CHUNK + tid] = 0.0;   // (past rcb)
     static_assert(3 * PX_CHUNK >= CG_N * PX_VROWS, "the zero stays");
-    if (tid == 0) { S.nhalo = 0; S.nextra = 0; S.nbody = 0; S.nv = 0; S.fit = 0; S.gone[0] = S.gone[1] = S.gone[2] = 0; }
+    if (tid == 0) { S.nhalo = 0; S.nextra = 0; S.nbody = 0; S.nv = 0; S.fit = 0; S.gone[0] = S.gone[1] = S.gone[2] = S.gone[3] = 0; }
     for (int i = tid; i < PX_HASH; i += PX_NT) S.h.key[i] = -1;
     __syncthreads();
     // the own nodes (threads 0 .. OWN - 1): n
@@ -492,9 +492,9 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
     PxState st;
     st.a = A.act[0];
     st.eta = A.st[2];
-    // Why a workgroup's threads leave together: a flag is raised only before
-    // its phase's barrier (the long rows' polls share the next scalars') and
-    // read only after it.
+    // Why a workgroup's threads leave together: each phase has a flag of its
+    // own, raised only before the phase's barrier and read only after it, and
+    // another barrier lies between the reads and the phase's next polls.
     bool gone = false;
     for (int k = 0; tiles && st.a; ++k) {
         // the thread's number anew in every iteration: what is derived from it
@@ -781,12 +781,12 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
                 double ax = 0.0, ay = 0.0, az = 0.0;
                 d3 zr;
                 auto rest = [&](int q, int end, const int *col, const double *val) {
-                    for (; q < end; q += PX_NT) px_acc(val + 9 * (size_t)q, px_poll3(z, col[q], A.ctl, &S.gone[0]), ax, ay, az);
+                    for (; q < end; q += PX_NT) px_acc(val + 9 * (size_t)q, px_poll3(z, col[q], A.ctl, &S.gone[3]), ax, ay, az);
                 };
                 if (i == me.spare) {   // the first blocks' z and the row's own in one poll
                     const u64 *const p = z + 3u * (unsigned)c0, *const pd = z + 3u * (unsigned)c1, *const pr = z + 3u * (unsigned)r;
                     double v[9];
-                    px_poll<9>([&](int i) { return i < 3 ? p + i : i < 6 ? pd + (i - 3) : pr + (i - 6); }, [](int) { return true; }, v, A.ctl, &S.gone[0]);
+                    px_poll<9>([&](int i) { return i < 3 ? p + i : i < 6 ? pd + (i - 3) : pr + (i - 6); }, [](int) { return true; }, v, A.ctl, &S.gone[3]);
                     zr = {v[6], v[7], v[8]};
                     if (e0 < e1) px_acc(B[0][0], {v[0], v[1], v[2]}, ax, ay, az);
                     rest(e0 + PX_NT, e1, A.col, A.val);
@@ -794,14 +794,15 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
                     rest(f0 + PX_NT, f1, A.dcol, A.dval);
                 } else {
                     r = A.long_rows[i];
-                    zr = px_poll3(z, r, A.ctl, &S.gone[0]);
+                    zr = px_poll3(z, r, A.ctl, &S.gone[3]);
                     rest(A.row_ptr[r] + tid, A.row_ptr[r + 1], A.col, A.val);
                     rest(A.dptr[r] + tid, A.dptr[r + 1], A.dcol, A.dval);
                 }
                 ax = wave_sum(ax); ay = wave_sum(ay); az = wave_sum(az);
                 if (lane == 0) { S.shl[0][wave] = ax; S.shl[1][wave] = ay; S.shl[2][wave] = az; }
                 __syncthreads();
-                if (tid == 0) {
+                gone = S.gone[3] != 0;
+                if (tid == 0 && !gone) {
                     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the emptying stores have completed
                     for (int q = 1; q < 8; ++q) { ax += S.shl[0][q]; ay += S.shl[1][q]; az += S.shl[2][q]; }
                     u64 *p = Dn + oWL + 3 * i;
@@ -814,7 +815,9 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
                     px_put(Dn + oZL + i, px_dt(zr, {ax, ay, az}));
                 }
                 __syncthreads();
+                if (gone) break;
             }
+            if (gone) break;
         }
     }
     // ---- the end: x, and this workgroup's vote that it has reached it ----
