@@ -169,8 +169,9 @@ enum {
                               iteration before it tries the one-launch form
                               again: 0 unless that form gave up, when the
                               solve started again (256: a workgroup's rows did
-                              not fit; 64: a workgroup waited too long for the
-                              others, which the environment variable
+                              not fit; 64, and twice as many each further time
+                              in a row up to 4096: a workgroup waited too long
+                              for the others, which the environment variable
                               IPC_PCG_GIVE_UP = 1, read at ipc_create, makes
                               every such solve report, for tests)             */
 };

@@ -428,6 +428,7 @@ struct ipc_ctx {
     bool resident_ok = false;             // the one-launch solve has its memory (ipc_pcg_resident.hip)
     bool resident_lanes = false;          // and all scenes take it: the PCG's products use 8 lanes
     int64_t resident_solves = 0;          // solves it has done
+    int resident_waits = 0;               // solves in a row that gave up waiting
     bool resident_give_up = false;        // every one-launch solve gives up (for tests of the restart)
     int resident_skip = 0;                // solves to take in the launch-per-iteration form before it is tried again
     int device = 0, n_cu = 0;             // the context's device and its compute units

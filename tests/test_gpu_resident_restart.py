@@ -205,3 +205,15 @@ def test_bodies_in_one_workgroup(cells, coarse, nb, taken, monkeypatch):
         assert sim._query(Q_PCG_RESIDENT) == (1 if eager == "0" and taken else 0)
         got.append((x.clone(), int(it[0])))
     assert torch.equal(got[0][0], got[1][0]) and got[0][1] == got[1][1] > 5
+
+
+def test_waits_that_run_out_again_lengthen_the_pause(monkeypatch):
+    from paper_2609_25653_amd._lib import Q_PCG_RESIDENT, Q_PCG_SKIP
+    monkeypatch.setenv("IPC_PCG_GIVE_UP", "1")
+    sim, y, b = _solve(S.tiny_scene("tet", h=0.01, n_steps=1), 5)
+    for pause in (64, 128, 256):
+        sim.pcg(y, b, 1e-8)
+        assert sim._query(Q_PCG_SKIP) == pause
+        for _ in range(pause):
+            sim.pcg(y, b, 1e-8)
+        assert sim._query(Q_PCG_SKIP) == 0 and sim._query(Q_PCG_RESIDENT) == 0
