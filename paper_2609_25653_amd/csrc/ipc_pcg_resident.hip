@@ -971,6 +971,15 @@ void pcg_resident_setup(ipc_ctx *c)
     int cu = 0;
     if (hipGetDevice(&c->device) != hipSuccess || hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess)
         return;
+    // a stream may be restricted to some of the compute units
+    unsigned int mask[64] = {};
+    if (hipExtStreamGetCUMask(c->stream, 64, mask) == hipSuccess) {
+        int units = 0;
+        for (unsigned int m : mask) units += __builtin_popcount(m);
+        if (units > 0) cu = std::min(cu, units);
+    } else {
+        (void)hipGetLastError();
+    }
     c->n_cu = std::min(cu, PX_WGMAX);
     if (!px_allow<1, false>() || !px_allow<2, false>() || !px_allow<4, false>() || !px_allow<4, true>()) return;
     // Its sums are those of 8 lanes per row: the PCG's products take 8, unless

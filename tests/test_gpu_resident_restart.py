@@ -217,3 +217,37 @@ def test_waits_that_run_out_again_lengthen_the_pause(monkeypatch):
         for _ in range(pause):
             sim.pcg(y, b, 1e-8)
         assert sim._query(Q_PCG_SKIP) == 0 and sim._query(Q_PCG_RESIDENT) == 0
+
+
+@pytest.mark.parametrize("cells", [9, 25])
+def test_stream_with_half_of_the_compute_units(cells, monkeypatch):
+    """On a stream that may use half of the compute units the launch is cut
+    for these: 17.6k nodes (25 cells), 138 workgroups of two tiles on the whole
+    chip, take more tiles each.  No wait runs out, and the bits are the same."""
+    import ctypes
+
+    import torch
+    from paper_2609_25653_amd._lib import Q_PCG_RESIDENT, Q_PCG_SKIP
+    monkeypatch.setenv("IPC_PCG_COARSE", "0")
+    sc = _block(cells)
+    sim, y, b = _solve(sc, 6)
+    want = sim.pcg(y, b, 1e-8)
+    assert sim._query(Q_PCG_RESIDENT) == 1
+    torch.cuda.synchronize()
+    path = [ln.split()[-1] for ln in open("/proc/self/maps") if "libamdhip64" in ln][0]
+    hip = ctypes.CDLL(path)
+    p = ctypes.c_void_p()
+    n = torch.cuda.get_device_properties(0).multi_processor_count // 32
+    mask = (ctypes.c_uint32 * n)(*[0xFFFFFFFF if k < n // 2 else 0 for k in range(n)])
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(p), n, mask) == 0
+    try:
+        with torch.cuda.stream(torch.cuda.ExternalStream(p.value)):
+            sim, y, b = _solve(sc, 6)
+            x, it = sim.pcg(y, b, 1e-8)
+            assert sim._query(Q_PCG_SKIP) == 0 and sim._query(Q_PCG_RESIDENT) == 1
+            torch.cuda.current_stream().synchronize()
+        assert torch.equal(x, want[0]) and it[0] == want[1][0]
+        del sim, y, b, x
+        torch.cuda.synchronize()
+    finally:
+        hip.hipStreamDestroy(p)
