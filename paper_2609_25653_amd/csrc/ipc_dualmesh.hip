@@ -24,7 +24,7 @@
 
 struct ipc_dualmesh {
     hipStream_t stream = nullptr;
-    int n_coarse = 0, n_fine = 0, max_row = 0;
+    int n_coarse = 0, n_fine = 0, max_row = 0, max_group = 0;   // columns of the widest row, of the widest group
     int64_t nnz = 0;
     std::vector<int> row_ptr, col, tri_fine;
     std::vector<double> val;
@@ -377,12 +377,12 @@ __global__ void __launch_bounds__(DM_T) k_dm_pairs(int nf, int nc, int frames, i
             for (int k = 0; k < KMAX; ++k) {
                 const double px = sx[c[k]], py = sx[c[k] + 1], pz = sx[c[k] + 2];
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    if (w[j][k] != 0.0) {   // the weights of a row are all positive
-                        a[j][0] += w[j][k] * px;
-                        a[j][1] += w[j][k] * py;
-                        a[j][2] += w[j][k] * pz;
-                    }
+                for (int j = 0; j < 2; ++j) {
+                    const bool in = w[j][k] != 0.0;   // the weights of a row are all positive
+                    a[j][0] = in ? __builtin_fma(w[j][k], px, a[j][0]) : a[j][0];
+                    a[j][1] = in ? __builtin_fma(w[j][k], py, a[j][1]) : a[j][1];
+                    a[j][2] = in ? __builtin_fma(w[j][k], pz, a[j][2]) : a[j][2];
+                }
             }
         }
         // the wavefront's own part of so: no barrier
@@ -406,6 +406,139 @@ __global__ void __launch_bounds__(DM_T) k_dm_pairs(int nf, int nc, int frames, i
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// One frame per workgroup, for the launches whose frames are split to single
+// ones: no loop, no prefetch, and the threads' own sums tell whether a staged
+// position is not finite (0 * x is then not 0, and a sum that took one in is
+// not finite either; such a thread sums again with the other row's columns
+// left out).
+//
+// What bounds it: three dependent trips to memory, then, with few blocks, the
+// loads of one CU: a thread reads up to 48 words of its group.  So NT threads
+// take a part of a block's groups, each part staging the block's vertices for
+// itself: with 128 threads two CUs share a block as long as there are CUs for
+// the halves.  One frame, us, k_dm_pairs / 256 threads / 128: torus of 24 x
+// 16, level 1, 3.9 / 3.4 / 3.1; level 2, 4.2 / 3.9 / 3.5; cylinder of 6602
+// vertices, level 1 (73 blocks), 4.7 / 4.4 / 3.9, level 3 (885 blocks) 12.4 /
+// 12.0 / 12.4.
+template <int KMAX, int NT>
+__global__ void __launch_bounds__(NT) k_dm_frame(int nf, int nc, const int *__restrict__ grp_row,
+                                                 const ipc_dualmesh::Block *__restrict__ blk, const int *__restrict__ blk_cols,
+                                                 const uint16_t *__restrict__ grp_col, const double *__restrict__ grp_val,
+                                                 const double *__restrict__ xc, double *__restrict__ xf)
+{
+    typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
+    constexpr int PER = DM_STAGE / NT;     // staged vertices per thread, at most
+    __shared__ double sx[3 * DM_STAGE];
+    __shared__ double so[6 * NT];
+    const int tid = threadIdx.x, t = tid + NT * blockIdx.z, lane = tid & 63;
+    const size_t f = blockIdx.y;
+    const ipc_dualmesh::Block B = blk[blockIdx.x];
+    const int ng = B.ng, nk = B.nk;
+    if (NT * blockIdx.z >= ng) return;
+    int src[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) src[q] = tid + q * NT < B.nu ? blk_cols[B.u0 + tid + q * NT] : -1;
+    const bool on = t < ng;
+    const int ti = min(t, ng - 1);
+    const int r0 = grp_row[B.g0 + ti], r1 = grp_row[B.g0 + ti + 1], rows = on ? r1 - r0 : 0;
+    int c[KMAX];
+    double w[2][KMAX];
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k) {
+        c[k] = 0;
+        w[0][k] = w[1][k] = 0.0;
+    }
+    auto load = [&](int k0, int k1) {      // nothing looks at them before the last loads are out
+#pragma unroll
+        for (int k = k0; k < k1; ++k) {
+            const size_t o = (size_t)B.w0 + (size_t)min(k, nk - 1) * ng + ti;
+            const size_t v = 2 * o - ti;
+            c[k] = grp_col[o];
+            w[0][k] = grp_val[v];
+            w[1][k] = grp_val[v + ng];
+        }
+    };
+    load(0, 2);
+    if (nk > 2) load(2, 6);
+    if (nk > 6) load(6, KMAX < 10 ? KMAX : 10);
+    if (KMAX > 10 && nk > 10) load(10, 14);
+    if (KMAX > 14 && nk > 14) load(14, KMAX);
+    const double *const x = xc + f * nc * 3;
+    double px[PER][3];
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (src[q] >= 0)
+            for (int m = 0; m < 3; ++m) px[q][m] = x[3 * (size_t)src[q] + m];
+    int words = 0;                         // of the wavefront's rows, which start at wr0
+    const int wr0 = __builtin_amdgcn_readfirstlane(r0), first = __builtin_amdgcn_readfirstlane(t);
+    if (first < ng) words = 3 * (__builtin_amdgcn_readlane(r1, min(63, ng - 1 - first)) - wr0);
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if (src[q] >= 0)
+            for (int m = 0; m < 3; ++m) sx[3 * (tid + q * NT) + m] = px[q][m];
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k) {
+        const bool in = k < nk && on;
+        c[k] = in ? c[k] : 0;
+        w[0][k] = in ? w[0][k] : 0.0;
+        w[1][k] = in ? w[1][k] : 0.0;
+    }
+    __syncthreads();
+    double a[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
+    auto sum = [&](int k0, int k1) {
+#pragma unroll
+        for (int k = k0; k < k1; ++k) {
+            const double qx = sx[c[k]], qy = sx[c[k] + 1], qz = sx[c[k] + 2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                a[j][0] += w[j][k] * qx;
+                a[j][1] += w[j][k] * qy;
+                a[j][2] += w[j][k] * qz;
+            }
+        }
+    };
+    sum(0, 2);
+    if (nk > 2) sum(2, 6);
+    if (nk > 6) sum(6, KMAX < 10 ? KMAX : 10);
+    if (KMAX > 10 && nk > 10) sum(10, 14);
+    if (KMAX > 14 && nk > 14) sum(14, KMAX);
+    const double z = (a[0][0] * 0.0 + a[0][1] * 0.0 + a[0][2] * 0.0) + (a[1][0] * 0.0 + a[1][1] * 0.0 + a[1][2] * 0.0);
+    if (!(z == 0.0)) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) a[j][0] = a[j][1] = a[j][2] = 0.0;
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) {
+            const double qx = sx[c[k]], qy = sx[c[k] + 1], qz = sx[c[k] + 2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const bool in = w[j][k] != 0.0;   // the weights of a row are all positive
+                a[j][0] = in ? __builtin_fma(w[j][k], qx, a[j][0]) : a[j][0];
+                a[j][1] = in ? __builtin_fma(w[j][k], qy, a[j][1]) : a[j][1];
+                a[j][2] = in ? __builtin_fma(w[j][k], qz, a[j][2]) : a[j][2];
+            }
+        }
+    }
+    // the wavefront's own part of so: no barrier
+    double *const out = so + 6 * (tid - lane);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+        if (j < rows) {
+            double *o = out + 3 * (r0 - wr0 + j);
+            o[0] = a[j][0];
+            o[1] = a[j][1];
+            o[2] = a[j][2];
+        }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    double *const o = xf + (f * nf + wr0) * 3;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int e = 2 * (64 * q + lane);
+        if (e + 1 < words) __builtin_nontemporal_store((d2u){out[e], out[e + 1]}, (d2u *)(o + e));
+        else if (e < words) __builtin_nontemporal_store(out[e], o + e);
     }
 }
 
@@ -456,6 +589,7 @@ void group_rows(ipc_dualmesh *m)
         for (int j : u)
             if (place[j] < 0) { place[j] = 0; cols.push_back(j); }
         nk = std::max(nk, (int)u.size());
+        m->max_group = std::max(m->max_group, nk);
         ucol.insert(ucol.end(), u.begin(), u.end());
         uptr.push_back((int)ucol.size());
         m->grp_row.push_back(end);
@@ -533,12 +667,21 @@ hipError_t launch(ipc_dualmesh *m, const Layout &L, const unsigned char *base, c
         const int nb = (int)m->blk.size();
         const int parts = std::max({1, std::min(4 * DM_CUS / nb, frames), std::min((16 * DM_CUS + nb - 1) / nb, frames / 16)});
         const int per = (frames + parts - 1) / parts;
-        auto go = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3(nb, (frames + per - 1) / per), dim3(DM_T), 0, m->stream, m->n_fine, m->n_coarse, frames, per, row,
-                               (const ipc_dualmesh::Block *)(base + L.blk), (const int *)(base + L.cols),
-                               (const uint16_t *)(base + L.col), val, xc, xf);
+        const auto *blk = (const ipc_dualmesh::Block *)(base + L.blk);
+        const int *cols = (const int *)(base + L.cols);
+        const uint16_t *col = (const uint16_t *)(base + L.col);
+        auto one = [&](auto kern, int nt) {
+            hipLaunchKernelGGL(kern, dim3(nb, frames, DM_T / nt), dim3(nt), 0, m->stream, m->n_fine, m->n_coarse, row, blk, cols, col, val, xc, xf);
         };
-        if (R <= 14) go(k_dm_pairs<14>);   // 128 registers: four blocks per CU; regular meshes have rows of at most 14
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(nb, (frames + per - 1) / per), dim3(DM_T), 0, m->stream, m->n_fine, m->n_coarse, frames, per, row, blk,
+                               cols, col, val, xc, xf);
+        };
+        if (per == 1) {   // at most 1024 frames, or one: blocks halved while every half has a CU (52 blocks: 2 frames 4.4 us whole, 4.0 halved, 4 frames 4.5 and 4.7)
+            const bool half = (int64_t)2 * nb * frames <= DM_CUS, narrow = m->max_group <= 8;   // (regular meshes of one level: groups of at most 8)
+            if (half) narrow ? one(k_dm_frame<8, DM_T / 2>, DM_T / 2) : one(k_dm_frame<16, DM_T / 2>, DM_T / 2);
+            else narrow ? one(k_dm_frame<8, DM_T>, DM_T) : one(k_dm_frame<16, DM_T>, DM_T);
+        } else if (R <= 14) go(k_dm_pairs<14>);   // 128 registers: four blocks per CU; regular meshes have rows of at most 14
         else go(k_dm_pairs<16>);
         return hipGetLastError();
     }

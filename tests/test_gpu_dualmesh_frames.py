@@ -1,0 +1,56 @@
+"""Frames of the dual-mesh map taken one per workgroup (k_dm_frame: few blocks
+or a single frame; whole blocks or halves) and several per workgroup
+(k_dm_pairs): the same bits, for rows that pair and rows that do not, at the
+counts where the launch changes, and positions that are not finite reach
+exactly the fine vertices whose row of W names them in either kernel."""
+import numpy as np
+import pytest
+
+from test_gpu_dualmesh import fan
+from test_gpu_dualmesh_pairs import _host, _shuffled
+
+torch = pytest.importorskip("torch")
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a ROCm GPU")]
+
+
+def _torus(nu, nv):
+    u, v = np.meshgrid(np.arange(nu), np.arange(nv), indexing="ij")
+    a, b = 2 * np.pi * u / nu, 2 * np.pi * v / nv
+    V = np.stack([(1 + 0.3 * np.cos(b)) * np.cos(a), (1 + 0.3 * np.cos(b)) * np.sin(a), 0.3 * np.sin(b)], -1).reshape(-1, 3)
+    i = lambda x, y: (x % nu) * nv + y % nv
+    F = np.stack([i(u, v), i(u + 1, v), i(u + 1, v + 1), i(u, v), i(u + 1, v + 1), i(u, v + 1)], -1).reshape(-1, 3)
+    return V, F
+
+
+def _mesh(name):
+    if name == "unpaired":                 # rows of 16 next to rows of 4; a single block of under 128 groups
+        return fan(15, seed=2) + (1,)
+    if name == "one level":                # groups of at most 8 columns, one block of over 128 groups and a short one
+        return _torus(13, 11) + (1,)
+    if name == "many blocks":              # more than 64: 50 frames are several per workgroup
+        return _shuffled(20, 24, 3) + (2,)
+    return _torus(31, 20) + (3,)           # 78 blocks: one frame in whole blocks and in none halved
+
+
+@pytest.mark.parametrize("name", ["unpaired", "one level", "many blocks", "three levels"])
+def test_single_frames_and_runs_of_frames_agree(name):
+    from paper_2609_25653_amd.dualmesh import DualMesh
+    V, F, levels = _mesh(name)
+    rng = np.random.default_rng(1)
+    X = V[None] + 0.1 * rng.standard_normal((50,) + V.shape)
+    X[7, 2, 1] = np.inf
+    X[31, len(V) - 1, 0] = np.nan
+    dm = DualMesh(F, len(V), levels)
+    x = torch.as_tensor(X, device="cuda")
+    all_at_once = dm.apply(x).cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        ref = _host(dm, X)
+    fin = np.isfinite(ref)
+    assert not fin[7].all() and not fin[31].all() and fin[:7].all()
+    assert np.array_equal(all_at_once[~fin], ref[~fin], equal_nan=True)
+    assert np.abs(all_at_once[fin] - ref[fin]).max() <= 1e-13 * np.abs(X[np.isfinite(X)]).max()
+    for frames in (1, 2, 3, 5, 20):
+        for f in (0, 7, 30):
+            part = x[f:f + frames].contiguous()
+            assert np.array_equal(dm.apply(part).cpu().numpy(), all_at_once[f:f + len(part)], equal_nan=True), (frames, f)
