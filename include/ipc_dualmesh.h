@@ -75,10 +75,9 @@ int ipc_dualmesh_apply(ipc_dualmesh *m, const double *xc_dev, double *xf_dev, in
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * this entry point calls no hipMalloc, hipFree or other allocating routine.
  * W is staged in a fixed device array of 16 MiB per GPU that the library
- * holds until the process ends; a W that needs more (its CSR arrays, plus
- * the per-block column lists when every block fits the staged kernel, each
- * rounded up to 256 bytes) is rejected with IPC_E_CAPACITY.  Every call on
- * one GPU shares that array: it keeps the W of the last call (a call with the
+ * holds until the process ends; a W that needs more even as its CSR arrays
+ * (12 bytes per nonzero and 4 per row, each rounded up to 256) is rejected
+ * with IPC_E_CAPACITY.  Every call on one GPU shares that array: it keeps the W of the last call (a call with the
  * same handle copies nothing, another handle's call copies its W from host
  * memory first), so calls that overlap on one GPU, from several host threads
  * or on different streams, race.  Arguments, results and errors are those of

@@ -44,6 +44,11 @@ struct ipc_dualmesh {
     std::vector<Block> blk;
     std::vector<uint16_t> grp_col;
     std::vector<double> grp_val;
+    // W for k_dm_rows (if the no-alloc path needs it): blocks of DM_T rows, block b with
+    // its distinct columns row_cols[row_off[b] .. row_off[b + 1]), and every
+    // nonzero's column's place in that list (times 3)
+    std::vector<int> row_off, row_cols;
+    std::vector<uint16_t> row_place;
     uint64_t id = 0;   // unique per handle: names the W that the no-alloc path last staged
     unsigned char *d_w = nullptr;   // the arrays of W, at layout()'s offsets
     std::string err;
@@ -59,6 +64,7 @@ std::string g_dm_create_error;
 
 constexpr int DM_T = 256;        // groups of rows per workgroup of k_dm_pairs, at most
 constexpr int DM_STAGE = 512;    // coarse vertices a block stages in LDS, at most (12 KiB)
+constexpr int DM_ROWSTAGE = 1024;   // the same of k_dm_rows (24 KiB)
 constexpr int DM_K = 16;         // columns of a group, at most
 constexpr int DM_CUS = 256;
 
@@ -542,6 +548,77 @@ __global__ void __launch_bounds__(NT) k_dm_frame(int nf, int nc, const int *__re
     }
 }
 
+// Workgroup b takes rows [DM_T b, DM_T b + DM_T), a row per thread from W's
+// own rows, and the frames of its part, staging positions as k_dm_pairs does.
+// For a W whose pairs, padded to a block's widest group, do not fit the
+// no-alloc path's array while its rows do (rows of one or two levels share
+// fewer columns).  Cylinder of 8706 vertices, two levels, 139266 rows, 20 and
+// 100 frames: 45 and 114 us, k_dm_apply 70 and 349; one level, 237602 rows:
+// 56 and 259, 70 and 330.
+template <int K>
+__global__ void __launch_bounds__(DM_T) k_dm_rows(int nf, int nc, int frames, int per, const int *__restrict__ rp,
+                                                  const uint16_t *__restrict__ place, const double *__restrict__ val,
+                                                  const int *__restrict__ off, const int *__restrict__ cols,
+                                                  const double *__restrict__ xc, double *__restrict__ xf)
+{
+    constexpr int PER = DM_ROWSTAGE / DM_T;   // staged vertices per thread, at most
+    __shared__ double sx[3 * DM_ROWSTAGE];
+    const int t = threadIdx.x, r = blockIdx.x * DM_T + t, f0 = blockIdx.y * per, f1 = min(frames, f0 + per);
+    const int u0 = off[blockIdx.x], U = off[blockIdx.x + 1] - u0;
+    int src[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) src[q] = t + q * DM_T < U ? cols[u0 + t + q * DM_T] : -1;
+    int c[K];
+    double w[K];
+    int n = 0;
+    if (r < nf) {
+        const int k0 = rp[r];
+        n = rp[r + 1] - k0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const bool in = k < n;
+            c[k] = in ? place[k0 + k] : 0;
+            w[k] = in ? val[k0 + k] : 0.0;
+        }
+    }
+    double pf[PER][3];
+    auto fetch = [&](int f) {
+        const double *x = xc + (size_t)f * nc * 3;
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (src[q] >= 0) {
+                pf[q][0] = x[3 * (size_t)src[q]];
+                pf[q][1] = x[3 * (size_t)src[q] + 1];
+                pf[q][2] = x[3 * (size_t)src[q] + 2];
+            }
+    };
+    if (f0 < f1) fetch(f0);
+    for (int f = f0; f < f1; ++f) {
+        if (f > f0) __syncthreads();   // the previous frame's reads of sx are done
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (src[q] >= 0) {
+                const int u = 3 * (t + q * DM_T);
+                sx[u] = pf[q][0];
+                sx[u + 1] = pf[q][1];
+                sx[u + 2] = pf[q][2];
+            }
+        if (f + 1 < f1) fetch(f + 1);
+        __syncthreads();
+        if (r < nf) {
+            double ax = 0.0, ay = 0.0, az = 0.0;
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if (k < n) {
+                    ax += w[k] * sx[c[k]];
+                    ay += w[k] * sx[c[k] + 1];
+                    az += w[k] * sx[c[k] + 2];
+                }
+            st_stream(xf + ((size_t)f * nf + r) * 3, ax, ay, az);
+        }
+    }
+}
+
 // Groups and blocks of k_dm_pairs (host side of its layout).
 void group_rows(ipc_dualmesh *m)
 {
@@ -598,24 +675,46 @@ void group_rows(ipc_dualmesh *m)
     close((int)m->grp_row.size() - 1);
 }
 
+// Blocks of k_dm_rows; none if a block has too many columns.
+void list_rows(ipc_dualmesh *m)
+{
+    if (m->max_row > DM_K) return;
+    const int *rp = m->row_ptr.data(), n = m->n_fine;
+    std::vector<int> at(m->n_coarse, -1), cols;
+    m->row_place.resize(m->col.size());
+    m->row_off.push_back(0);
+    for (int b0 = 0; b0 < n; b0 += DM_T) {
+        const int k0 = rp[b0], k1 = rp[std::min(n, b0 + DM_T)];
+        cols.assign(m->col.begin() + k0, m->col.begin() + k1);
+        std::sort(cols.begin(), cols.end());
+        cols.erase(std::unique(cols.begin(), cols.end()), cols.end());
+        if ((int)cols.size() > DM_ROWSTAGE) { m->row_off.clear(); m->row_cols.clear(); m->row_place.clear(); return; }
+        for (size_t u = 0; u < cols.size(); ++u) at[cols[u]] = (int)u;
+        for (int k = k0; k < k1; ++k) m->row_place[k] = (uint16_t)(3 * at[m->col[k]]);
+        m->row_cols.insert(m->row_cols.end(), cols.begin(), cols.end());
+        m->row_off.push_back((int)m->row_cols.size());
+    }
+}
+
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// byte offsets of W's arrays on the device, of k_dm_pairs (pairs) or k_dm_apply; the total
+// byte offsets of W's arrays on the device, for the kernel of its form; the total
+enum Form { PAIRS, ROWS, CSR };   // k_dm_pairs and k_dm_frame; k_dm_rows; k_dm_apply
 struct Layout {
-    bool pairs = false;
+    Form form = CSR;
     size_t row = 0, col = 0, val = 0, blk = 0, cols = 0, total = 0;
 };
-Layout layout(const ipc_dualmesh *m, bool pairs)
+Layout layout(const ipc_dualmesh *m, Form form)
 {
     Layout L;
     auto put = [&](size_t bytes) { const size_t o = L.total; L.total += align256(std::max<size_t>(bytes, 1)); return o; };
-    L.pairs = pairs;
-    L.row = put(sizeof(int) * (pairs ? m->grp_row : m->row_ptr).size());
-    L.val = put(sizeof(double) * (pairs ? m->grp_val : m->val).size());
-    L.col = put(pairs ? sizeof(uint16_t) * m->grp_col.size() : sizeof(int) * m->col.size());
-    if (pairs) {
-        L.blk = put(sizeof(ipc_dualmesh::Block) * m->blk.size());
-        L.cols = put(sizeof(int) * m->blk_cols.size());
+    L.form = form;
+    L.row = put(sizeof(int) * (form == PAIRS ? m->grp_row : m->row_ptr).size());
+    L.val = put(sizeof(double) * (form == PAIRS ? m->grp_val : m->val).size());
+    L.col = put(form == PAIRS ? sizeof(uint16_t) * m->grp_col.size() : form == ROWS ? sizeof(uint16_t) * m->row_place.size() : sizeof(int) * m->col.size());
+    if (form != CSR) {
+        L.blk = put(form == PAIRS ? sizeof(ipc_dualmesh::Block) * m->blk.size() : sizeof(int) * m->row_off.size());
+        L.cols = put(sizeof(int) * (form == PAIRS ? m->blk_cols : m->row_cols).size());
     }
     return L;
 }
@@ -626,16 +725,22 @@ hipError_t copy_in(const ipc_dualmesh *m, const Layout &L, unsigned char *base)
     auto put = [&](size_t off, const auto &v) {
         if (e == hipSuccess && !v.empty()) e = hipMemcpyAsync(base + off, v.data(), sizeof(v[0]) * v.size(), hipMemcpyHostToDevice, m->stream);
     };
-    if (L.pairs) {
+    switch (L.form) {
+    case PAIRS:
         put(L.row, m->grp_row); put(L.val, m->grp_val); put(L.col, m->grp_col);
         put(L.blk, m->blk); put(L.cols, m->blk_cols);
-    } else {
+        break;
+    case ROWS:
+        put(L.row, m->row_ptr); put(L.val, m->val); put(L.col, m->row_place);
+        put(L.blk, m->row_off); put(L.cols, m->row_cols);
+        break;
+    case CSR:
         put(L.row, m->row_ptr); put(L.val, m->val); put(L.col, m->col);
     }
     return e;
 }
 
-Layout owned(const ipc_dualmesh *m) { return layout(m, !m->grp_row.empty()); }
+Layout owned(const ipc_dualmesh *m) { return layout(m, m->grp_row.empty() ? CSR : PAIRS); }
 
 hipError_t upload(ipc_dualmesh *m)
 {
@@ -655,18 +760,22 @@ hipError_t launch(ipc_dualmesh *m, const Layout &L, const unsigned char *base, c
     const int *row = (const int *)(base + L.row);
     const double *val = (const double *)(base + L.val);
     const int R = m->max_row;
-    if (L.pairs) {
-        // Frames are split over blocks: as long as all of the blocks run at
-        // once (four per CU), to single frames, which then take as long as
-        // one; beyond, to about four rounds of blocks, so that the last,
-        // partly empty one weighs little, and at least 16 frames each: a
-        // block's set-up reads the weights, as many bytes as five frames
-        // write.  885 blocks by 100 frames: one part 304 us, two 270, three
-        // 264, four 259, six 255.  13 blocks
-        // by 20: one part 28 us, twenty 6.
-        const int nb = (int)m->blk.size();
-        const int parts = std::max({1, std::min(4 * DM_CUS / nb, frames), std::min((16 * DM_CUS + nb - 1) / nb, frames / 16)});
-        const int per = (frames + parts - 1) / parts;
+    // Frames are split over blocks: as long as all of the blocks run at once
+    // (four per CU), to single frames, which then take as long as one; beyond,
+    // to about four rounds of blocks, so that the last, partly empty one
+    // weighs little, and at least 16 frames each: a block's set-up reads the
+    // weights, as many bytes as five frames write.  k_dm_pairs, 885 blocks by
+    // 100 frames: one part 304 us, two 270, three 264, four 259, six 255.  13
+    // blocks by 20: one part 28 us, twenty 6.
+    const int nb = L.form == PAIRS ? (int)m->blk.size() : (m->n_fine + DM_T - 1) / DM_T;
+    const int parts = std::max({1, std::min(4 * DM_CUS / nb, frames), std::min((16 * DM_CUS + nb - 1) / nb, frames / 16)});
+    const int per = (frames + parts - 1) / parts;
+    if (L.form == ROWS) {
+        hipLaunchKernelGGL(k_dm_rows<DM_K>, dim3(nb, (frames + per - 1) / per), dim3(DM_T), 0, m->stream, m->n_fine, m->n_coarse, frames, per,
+                           row, (const uint16_t *)(base + L.col), val, (const int *)(base + L.blk), (const int *)(base + L.cols), xc, xf);
+        return hipGetLastError();
+    }
+    if (L.form == PAIRS) {
         const auto *blk = (const ipc_dualmesh::Block *)(base + L.blk);
         const int *cols = (const int *)(base + L.cols);
         const uint16_t *col = (const uint16_t *)(base + L.col);
@@ -715,11 +824,14 @@ std::mutex g_scratch_mu;
 ScratchSlot g_scratch[DM_MAX_DEVICES];
 uint64_t g_dm_next_id = 1;
 
-// W as the array holds it: for k_dm_pairs if that fits, else in its own rows
+// W as the array holds it: for k_dm_pairs if that fits, else in its own rows,
+// staged if they can be and that fits
 Layout scratch_layout(const ipc_dualmesh *m)
 {
-    const Layout L = owned(m);
-    return L.total <= DM_SCRATCH_BYTES ? L : layout(m, false);
+    Layout L = owned(m);
+    if (L.total <= DM_SCRATCH_BYTES) return L;
+    if (!m->row_off.empty() && (L = layout(m, ROWS)).total <= DM_SCRATCH_BYTES) return L;
+    return layout(m, CSR);
 }
 
 } // namespace
@@ -767,6 +879,7 @@ extern "C" int ipc_dualmesh_create(const int32_t *tri_host, int32_t n_tri, int32
         for (int r = 0; r < n; ++r) m->max_row = std::max(m->max_row, m->row_ptr[r + 1] - m->row_ptr[r]);
         m->tri_fine = std::move(tri);
         group_rows(m);
+        if (owned(m).total > DM_SCRATCH_BYTES && layout(m, CSR).total <= DM_SCRATCH_BYTES) list_rows(m);   // for the no-alloc path
         *out = own.release();
         return IPC_OK;
     } catch (const Invalid &e) {

@@ -54,3 +54,38 @@ def test_single_frames_and_runs_of_frames_agree(name):
         for f in (0, 7, 30):
             part = x[f:f + frames].contiguous()
             assert np.array_equal(dm.apply(part).cpu().numpy(), all_at_once[f:f + len(part)], equal_nan=True), (frames, f)
+
+
+def _large(name):
+    V, F = _torus(328 if name == "rows staged" else 300, 200)
+    if name == "rows staged":
+        return V, F
+    rng = np.random.default_rng(6)         # rows next to each other share no columns: blocks of more than 1024
+    perm = rng.permutation(len(V))
+    W = np.empty_like(V)
+    W[perm] = V
+    return W, perm[F][rng.permutation(len(F))]
+
+
+@pytest.mark.parametrize("name", ["rows staged", "rows not staged"])
+def test_the_forms_that_fit_the_fixed_array(name):
+    """One level, 262400 and 240000 rows: W's pairs take more than the no-alloc
+    path's 16 MiB, its own rows (at most 12 bytes per nonzero and 4 per row)
+    less.  The same bits as through the library's own memory, for frames in
+    one part and in several, also around positions that are not finite."""
+    from paper_2609_25653_amd.dualmesh import DualMesh
+    V, F = _large(name)
+    dm = DualMesh(F, len(V), 1)
+    assert 12 * dm.nnz + 4 * (dm.n_fine + 1) <= 16 << 20
+    rng = np.random.default_rng(3)
+    for frames in (1, 3, 40):
+        X = V[None] + 0.1 * rng.standard_normal((frames,) + V.shape)
+        X[0, 5, 1] = np.inf
+        X[-1, len(V) - 2, 0] = np.nan
+        xc = torch.as_tensor(X, device="cuda")
+        a = dm.apply(xc)
+        b = torch.full_like(a, 7.0)
+        dm.apply_noalloc(xc, b)
+        torch.cuda.synchronize()
+        assert torch.equal(torch.isnan(a), torch.isnan(b))
+        assert torch.equal(a.nan_to_num(nan=-9.0), b.nan_to_num(nan=-9.0)) and not torch.isfinite(a).all()
