@@ -44,17 +44,19 @@ struct ipc_dualmesh {
     std::vector<Block> blk;
     std::vector<uint16_t> grp_col;
     std::vector<double> grp_val;
-    // W for k_dm_rows (if the no-alloc path needs it): blocks of DM_T rows, block b with
+    // W for k_dm_rows (if the no-alloc path or few frames take it): blocks of DM_T rows, block b with
     // its distinct columns row_cols[row_off[b] .. row_off[b + 1]), and every
     // nonzero's column's place in that list (times 3)
     std::vector<int> row_off, row_cols;
     std::vector<uint16_t> row_place;
     uint64_t id = 0;   // unique per handle: names the W that the no-alloc path last staged
     unsigned char *d_w = nullptr;   // the arrays of W, at layout()'s offsets
+    unsigned char *d_rows = nullptr;   // and for few frames, row by row
     std::string err;
     ~ipc_dualmesh()
     {
         if (d_w) (void)hipFree(d_w);
+        if (d_rows) (void)hipFree(d_rows);
     }
 };
 
@@ -742,16 +744,42 @@ hipError_t copy_in(const ipc_dualmesh *m, const Layout &L, unsigned char *base)
 
 Layout owned(const ipc_dualmesh *m) { return layout(m, m->grp_row.empty() ? CSR : PAIRS); }
 
-hipError_t upload(ipc_dualmesh *m)
+// Whether a few frames (DM_FEW at most) go row by row: what they cost is to
+// read W, and where rows are short, of one level, pairs share few columns and
+// padded to a block's widest group are the larger form.  Rows of 4.75 columns,
+// 1, 2, 4, 8 and 20 frames, by pairs and by rows, us: torus, 240000 rows (712
+// blocks), 6.4 / 8.3 / 12.9 / 20.7 / 44 and 5.5 / 7.1 / 11.8 / 20.5 / 46;
+// cylinder, 237602 (837), 8.3 / 11.0 / 15.6 / 24.5 / 51 and 5.9 / 8.3 / 13.9 /
+// 23.8 / 55; torus, 1200000 (3560, more than run in two rounds), 23.3 / 33.7 /
+// 53 / 94 and 22.6 / 34.1 / 56 / 100; with fewer than two blocks per CU
+// latency decides (73 blocks: 4.0 and 3.8, 107: 3.7 and 3.8).  Two levels (8.7
+// columns, 357 blocks) 6.0 and 6.0, three (11.2) 12.1 and 19.0; none (one
+// column), 586 blocks, 4.2 and 4.9.
+constexpr int DM_FEW = 4;
+bool few_by_rows(const ipc_dualmesh *m)
 {
-    if (m->d_w) return hipSuccess;
-    const Layout L = owned(m);
+    const int nb = (int)m->blk.size();
+    return nb >= 2 * DM_CUS && nb <= 8 * DM_CUS && m->nnz > 2 * (int64_t)m->n_fine && m->nnz < 6 * (int64_t)m->n_fine;
+}
+
+// W on the device in one form
+hipError_t upload(ipc_dualmesh *m, const Layout &L, unsigned char *&dev)
+{
+    if (dev) return hipSuccess;
     unsigned char *p = nullptr;
     hipError_t e = hipMalloc(&p, L.total);
     if (e == hipSuccess) e = copy_in(m, L, p);
     if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
-    if (e == hipSuccess) m->d_w = p;   // only a W that has arrived is taken for one by the next call
+    if (e == hipSuccess) dev = p;   // only a W that has arrived is taken for one by the next call
     else if (p) (void)hipFree(p);
+    return e;
+}
+bool by_rows(const ipc_dualmesh *m) { return few_by_rows(m) && !m->row_off.empty(); }
+// every form that a call may take, with the first one (so that later calls, under capture too, only launch)
+hipError_t upload(ipc_dualmesh *m)
+{
+    hipError_t e = upload(m, owned(m), m->d_w);
+    if (e == hipSuccess && by_rows(m)) e = upload(m, layout(m, ROWS), m->d_rows);
     return e;
 }
 
@@ -804,6 +832,12 @@ hipError_t launch(ipc_dualmesh *m, const Layout &L, const unsigned char *base, c
     else IPC_DM(0);
 #undef IPC_DM
     return hipGetLastError();
+}
+
+// the product from the library's own memory
+hipError_t launch_owned(ipc_dualmesh *m, const double *xc, double *xf, int frames)
+{
+    return frames <= DM_FEW && by_rows(m) ? launch(m, layout(m, ROWS), m->d_rows, xc, xf, frames) : launch(m, owned(m), m->d_w, xc, xf, frames);
 }
 
 // ---- the variant that allocates nothing ------------------------------------
@@ -879,7 +913,8 @@ extern "C" int ipc_dualmesh_create(const int32_t *tri_host, int32_t n_tri, int32
         for (int r = 0; r < n; ++r) m->max_row = std::max(m->max_row, m->row_ptr[r + 1] - m->row_ptr[r]);
         m->tri_fine = std::move(tri);
         group_rows(m);
-        if (owned(m).total > DM_SCRATCH_BYTES && layout(m, CSR).total <= DM_SCRATCH_BYTES) list_rows(m);   // for the no-alloc path
+        const bool noalloc = owned(m).total > DM_SCRATCH_BYTES && layout(m, CSR).total <= DM_SCRATCH_BYTES;
+        if (noalloc || few_by_rows(m)) list_rows(m);
         *out = own.release();
         return IPC_OK;
     } catch (const Invalid &e) {
@@ -929,7 +964,7 @@ extern "C" int ipc_dualmesh_apply(ipc_dualmesh *m, const double *xc_dev, double 
     if (!m) return IPC_E_INVALID;
     if (!xc_dev || !xf_dev || n_frames < 1) { m->err = "need device arrays and at least one frame"; return IPC_E_INVALID; }
     hipError_t e = upload(m);
-    if (e == hipSuccess) e = launch(m, owned(m), m->d_w, xc_dev, xf_dev, n_frames);
+    if (e == hipSuccess) e = launch_owned(m, xc_dev, xf_dev, n_frames);
     if (e != hipSuccess) { m->err = std::string("HIP: ") + hipGetErrorString(e); return IPC_E_DEVICE; }
     return IPC_OK;
 }
@@ -967,11 +1002,11 @@ extern "C" int ipc_dualmesh_time(ipc_dualmesh *m, const double *xc_dev, double *
     if (!xc_dev || !xf_dev || n_frames < 1 || reps < 1 || !avg_us) { m->err = "invalid timing arguments"; return IPC_E_INVALID; }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = upload(m);
-    if (e == hipSuccess) e = launch(m, owned(m), m->d_w, xc_dev, xf_dev, n_frames);   // warm
+    if (e == hipSuccess) e = launch_owned(m, xc_dev, xf_dev, n_frames);   // warm
     if (e == hipSuccess) e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
     if (e == hipSuccess) e = hipEventRecord(e0, m->stream);
-    for (int k = 0; k < reps && e == hipSuccess; ++k) e = launch(m, owned(m), m->d_w, xc_dev, xf_dev, n_frames);
+    for (int k = 0; k < reps && e == hipSuccess; ++k) e = launch_owned(m, xc_dev, xf_dev, n_frames);
     if (e == hipSuccess) e = hipEventRecord(e1, m->stream);
     if (e == hipSuccess) e = hipEventSynchronize(e1);
     float ms = 0.0f;

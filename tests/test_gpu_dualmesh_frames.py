@@ -89,3 +89,21 @@ def test_the_forms_that_fit_the_fixed_array(name):
         torch.cuda.synchronize()
         assert torch.equal(torch.isnan(a), torch.isnan(b))
         assert torch.equal(a.nan_to_num(nan=-9.0), b.nan_to_num(nan=-9.0)) and not torch.isfinite(a).all()
+
+
+def test_few_frames_of_a_large_mesh_of_one_level():
+    """Up to 4 frames go row by row from a copy of W's rows, more by pairs;
+    the same bits, whichever call comes first on a handle."""
+    from paper_2609_25653_amd.dualmesh import DualMesh
+    V, F = _torus(300, 200)
+    rng = np.random.default_rng(4)
+    X = V[None] + 0.1 * rng.standard_normal((9,) + V.shape)
+    X[2, 11, 2] = -np.inf
+    x = torch.as_tensor(X, device="cuda")
+    few, many = DualMesh(F, len(V), 1), DualMesh(F, len(V), 1)
+    a = torch.cat([few.apply(x[f:f + 1].contiguous()) for f in range(5)] + [few.apply(x[5:9].contiguous())])
+    b = many.apply(x)
+    c = torch.cat([many.apply(x[:4].contiguous()), many.apply(x[4:].contiguous())])
+    for q in (a, c):
+        assert torch.equal(torch.isnan(q), torch.isnan(b)) and torch.equal(q.nan_to_num(nan=-9.0), b.nan_to_num(nan=-9.0))
+    assert not torch.isfinite(b[2]).all() and torch.isfinite(b[3:]).all()
