@@ -621,7 +621,9 @@ __global__ void __launch_bounds__(DM_T) k_dm_rows(int nf, int nc, int frames, in
     }
 }
 
-// Groups and blocks of k_dm_pairs (host side of its layout).
+// Groups and blocks of k_dm_pairs (host side of its layout); none for rows of
+// more than DM_K columns, nor if the padded groups would not fit the kernel's
+// indices (W's own rows do: they go row by row then).
 void group_rows(ipc_dualmesh *m)
 {
     if (m->max_row > DM_K) return;
@@ -630,13 +632,14 @@ void group_rows(ipc_dualmesh *m)
     std::vector<int> place(m->n_coarse, -1), cols;      // of the block being filled
     std::vector<int> ucol, uptr{0};                     // each group's columns, ascending
     int g0 = 0, nk = 1;
+    bool fits = true;
     auto close = [&](int g1) {
         std::sort(cols.begin(), cols.end());
         for (size_t u = 0; u < cols.size(); ++u) place[cols[u]] = (int)u;
         m->blk_cols.insert(m->blk_cols.end(), cols.begin(), cols.end());
         const int ng = g1 - g0;
         const size_t w0 = m->grp_col.size(), size = w0 + (size_t)nk * ng;
-        if (size > (size_t)INT32_MAX) throw Invalid("too many nonzeros");
+        if (size > (size_t)INT32_MAX) { fits = false; return; }
         m->grp_col.resize(size, 0);
         m->grp_val.resize(2 * size, 0.0);
         for (int g = g0; g < g1; ++g) {
@@ -655,7 +658,7 @@ void group_rows(ipc_dualmesh *m)
         nk = 1;
     };
     m->grp_row.push_back(0);
-    for (int r = 0; r < n;) {
+    for (int r = 0; r < n && fits;) {
         std::vector<int> u;
         int end = r + 1;
         if (end < n) std::set_union(col + rp[r], col + rp[r + 1], col + rp[r + 1], col + rp[r + 2], std::back_inserter(u));
@@ -674,7 +677,11 @@ void group_rows(ipc_dualmesh *m)
         m->grp_row.push_back(end);
         r = end;
     }
-    close((int)m->grp_row.size() - 1);
+    if (fits) close((int)m->grp_row.size() - 1);
+    if (!fits) {
+        m->grp_row.clear(); m->blk_cols.clear(); m->blk.clear(); m->grp_col.clear(); m->grp_val.clear();
+        m->max_group = 0;
+    }
 }
 
 // Blocks of k_dm_rows; none if a block has too many columns.
@@ -742,7 +749,7 @@ hipError_t copy_in(const ipc_dualmesh *m, const Layout &L, unsigned char *base)
     return e;
 }
 
-Layout owned(const ipc_dualmesh *m) { return layout(m, m->grp_row.empty() ? CSR : PAIRS); }
+Layout owned(const ipc_dualmesh *m) { return layout(m, !m->grp_row.empty() ? PAIRS : !m->row_off.empty() ? ROWS : CSR); }
 
 // Whether a few frames (DM_FEW at most) go row by row: what they cost is to
 // read W, and where rows are short, of one level, pairs share few columns and
@@ -914,7 +921,7 @@ extern "C" int ipc_dualmesh_create(const int32_t *tri_host, int32_t n_tri, int32
         m->tri_fine = std::move(tri);
         group_rows(m);
         const bool noalloc = owned(m).total > DM_SCRATCH_BYTES && layout(m, CSR).total <= DM_SCRATCH_BYTES;
-        if (noalloc || few_by_rows(m)) list_rows(m);
+        if (m->grp_row.empty() || noalloc || few_by_rows(m)) list_rows(m);
         *out = own.release();
         return IPC_OK;
     } catch (const Invalid &e) {
