@@ -494,7 +494,9 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
     st.eta = A.st[2];
     // Why a workgroup's threads leave together: each phase has a flag of its
     // own, raised only before the phase's barrier and read only after it, and
-    // another barrier lies between the reads and the phase's next polls.
+    // another barrier lies between the reads and the phase's next polls.  (The
+    // long rows' flag is handed on to the scalars' phase, after the rows'
+    // barriers and before that phase's.)
     bool gone = false;
     for (int k = 0; tiles && st.a; ++k) {
         // the thread's number anew in every iteration: what is derived from it
@@ -801,8 +803,7 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
                 ax = wave_sum(ax); ay = wave_sum(ay); az = wave_sum(az);
                 if (lane == 0) { S.shl[0][wave] = ax; S.shl[1][wave] = ay; S.shl[2][wave] = az; }
                 __syncthreads();
-                gone = S.gone[3] != 0;
-                if (tid == 0 && !gone) {
+                if (tid == 0) {
                     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the emptying stores have completed
                     for (int q = 1; q < 8; ++q) { ax += S.shl[0][q]; ay += S.shl[1][q]; az += S.shl[2][q]; }
                     u64 *p = Dn + oWL + 3 * i;
@@ -815,9 +816,8 @@ __global__ void __launch_bounds__(PX_NT) k_pcg_resident(PxArgs A)
                     px_put(Dn + oZL + i, px_dt(zr, {ax, ay, az}));
                 }
                 __syncthreads();
-                if (gone) break;
             }
-            if (gone) break;
+            if (tid == 0 && S.gone[3]) S.gone[0] = 1;   // the workgroup leaves in the next scalars' phase
         }
     }
     // ---- the end: x, and this workgroup's vote that it has reached it ----
