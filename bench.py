@@ -8,9 +8,11 @@ Timed: K full steps (every Newton iteration with assembly, PCG, CCD, line
 search), after W untimed warm-up steps, between device synchronisations; by
 default steps 2-100 of the scene (K = 99, W = 1): the squeeze and the lift.  The
 JSON line reports Newton iterations per second as ``value`` plus steps per
-second, the roofline object of the dominant kernel (durations from HIP events
-the library records on its own stream during the timed steps) and the oracle's
-CPU throughput on a bounded sample of the same workload.
+second, the roofline object of the Hessian product as a launch of its own
+(durations from HIP events the library records on its own stream during one
+more step after the timed ones; the timed steps' PCG iterations run inside one
+launch per solve) and the oracle's CPU throughput on a bounded sample of the
+same workload.
 """
 import argparse
 import ctypes
@@ -175,9 +177,14 @@ def copy_bandwidth():
 
 def product_roofline(sim, lib, traffic=None):
     """The Hessian product's roofline: algorithmic bytes per launch over its
-    average duration inside PCG during the last timed step (HIP events that
-    each dispatch records; the step ran with ipc_profile on), and, as a
-    secondary figure, over 200 back-to-back launches on the last matrix."""
+    average duration inside PCG (HIP events that each dispatch records) during
+    one more step after the timed ones, towards the last one's targets, with
+    ipc_profile on, which keeps to a launch per PCG iteration step; and, as a
+    secondary figure, over 200 back-to-back launches on the last matrix.  The
+    timed steps launch the product once per solve: their PCG iterations hold
+    the matrix in registers and LDS (k_pcg_resident)."""
+    sim._check(lib().ipc_profile(sim._h, 1))
+    sim.step_targets(sim.targets(sim.step_index - 1), allow_status=(3, 4))
     tot, nl, by = ctypes.c_double(), ctypes.c_int64(), ctypes.c_double()
     sim._check(lib().ipc_kernel_time(sim._h, K_SPMV, ctypes.byref(tot), ctypes.byref(nl), ctypes.byref(by)))
     sim._check(lib().ipc_profile(sim._h, 0))
@@ -193,7 +200,8 @@ def product_roofline(sim, lib, traffic=None):
                            "note": "a plain 1 GiB device copy (read + write), best of 6: the measured bandwidth ceiling"},
             "traffic": traffic, "kernel": "k_spmv (Hessian product: block CSR + row-sorted pair-local blocks)",
             "bytes_per_launch": bytes_launch, "avg_us": us_pcg, "launches_timed": int(nl.value),
-            "timing": "HIP events stamped by each product launch inside PCG during the last timed step",
+            "timing": "HIP events stamped by each product launch inside PCG during one more step after the timed ones, "
+                      "taken with a launch per PCG iteration step",
             "back_to_back": {"avg_us": us.value, "achieved": by2.value / (us.value * 1e-6) / 1e9,
                              "frac": by2.value / (us.value * 1e-6) / 1e9 / HBM_PEAK_GBS, "launches_timed": 200,
                              "timing": "200 back-to-back launches on the last matrix between two HIP events"},
@@ -227,10 +235,6 @@ def bench_batched(args):
     newton = []
     t0 = time.perf_counter()
     for k in range(args.steps):
-        if k == args.steps - 1:
-            # the product's launches inside PCG stamp HIP events in the last
-            # timed step, as in the contact workload
-            sim._check(lib().ipc_profile(sim._h, 1))
         rc, st = sim.step(allow_status=ok_codes)
         for i, s in enumerate(st):
             status[s["status"]] = status.get(s["status"], 0) + 1
@@ -585,11 +589,6 @@ def main():
     status = {}
     t0 = time.perf_counter()
     for k in range(args.steps):
-        if k == args.steps - 1:
-            # the last timed step runs with the library's kernel timing on:
-            # every product launch inside PCG stamps HIP events at its own
-            # start and end (eager launches for this step only)
-            sim._check(lib().ipc_profile(sim._h, 1))
         rc, st = sim.step(allow_status=(3, 4))
         status[st[0]["status"]] = status.get(st[0]["status"], 0) + 1
         newton += st[0]["newton_iters"]
@@ -600,7 +599,7 @@ def main():
               f"pairs={pairs[-1]} pair_local={nloc} cand_max={st[0]['n_cand_max']} alpha_min={st[0]['alpha_min']:.3g}", file=sys.stderr, flush=True)
     torch.cuda.synchronize()
     t = time.perf_counter() - t0
-    # Dominant kernel: the Hessian product inside PCG (see product_roofline).
+    # the Hessian product inside PCG, as a launch of its own (see product_roofline)
     roof = product_roofline(sim, lib, product_traffic())
     line = {
         "metric": METRIC, "value": newton / t, "unit": "Newton iters/s", "n_gpus": 1, "steps": args.steps,

@@ -387,10 +387,10 @@ int ipc_time_kernel(ipc_ctx *ctx, int kernel, int reps, double *avg_us, double *
  * count but keeps that one.  A context that takes its PCG solves in one
  * launch (IPC_Q_PCG_RESIDENT) forms the sums of 8 lanes in its solves
  * whatever the choice, unless the variable fixes another count.  Otherwise
- * the choice is also kept for the process, keyed by the context's size bucket (the powers of two of the
- * static pattern's block count and of the node count, and whether it holds
- * several scenes); a context created later in the same bucket starts with
- * it (IPC_Q_SPMV_LANES).  The same call then times the three kernels of the
+ * the choice is also kept for the process, keyed by the context's size
+ * bucket (the powers of two of the static pattern's block count and of the
+ * node count, and whether it holds several scenes); a context created later
+ * in the same bucket starts with it (IPC_Q_SPMV_LANES).  The same call then times the three kernels of the
  * FEM assembly (element blocks and gradients, matrix-slot gather, node
  * gradient gather) alone with 64, 128 and 256 threads per workgroup on the
  * current state and keeps the fastest of each (256 unless another is more

@@ -5,7 +5,9 @@
 // The application is HBM-bound: W is read once per launch and every frame
 // writes 24 B per fine vertex, while the coarse frames (24 B per coarse
 // vertex) stay in L2.  A thread keeps its rows of W in registers and loops
-// over the frames (k_dm_pairs; k_dm_apply for long rows).
+// over the frames (k_dm_pairs; k_dm_frame where a workgroup has one frame;
+// k_dm_rows where W's own rows are the smaller form; k_dm_apply for long
+// rows).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -270,7 +272,7 @@ __global__ void __launch_bounds__(256) k_dm_apply(int nf, int nc, int frames, co
 // straight from two-row threads, 48 B apart,
 // 633-1270; three or four rows per thread 289-305 (registers).  One frame
 // (118786 fine vertices): 8.4 us with CSR rows, which each thread reads for
-// itself, 5.1 with the weights side by side.
+// itself, 5.1 with the weights side by side (4.7 in k_dm_frame).
 //
 // The sums run over a row's own columns in ascending order; the other row's
 // columns add 0 * x, which changes nothing unless x is infinite or NaN: a

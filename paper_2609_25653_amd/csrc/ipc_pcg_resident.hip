@@ -34,12 +34,14 @@
 //      (k & 1), emptied in k + 1 by the same argument.
 //
 // Residency.  Every workgroup has to be running for the exchange to finish.
-// The grid is at most the number of compute units, one workgroup fits on
-// each, and one such launch per device runs at a time in this process.  A
-// poll that waits longer than PX_WAIT (another process holding compute units)
-// raises the abort word, every workgroup leaves, and the caller takes the
-// launch-per-iteration form instead: the kernel writes nothing that form
-// reads before its successful end.
+// The grid is at most the number of compute units that the stream may use,
+// one workgroup fits on each, and one such launch per device runs at a time in
+// this process.  A poll that waits longer than PX_WAIT (another process
+// holding compute units) raises the abort word, every workgroup leaves, and
+// the solve starts again in the launch-per-iteration form, which sets again
+// all that this kernel writes.  Two contexts stepping the 20k-tet squeeze at
+// once, ms a step each, that form and this one: threads of one process 26.0
+// and 20.8, processes 25.2 and 15.9 (no wait ran out), alone 23.2 and 13.9.
 //
 // Bits.  Every sum runs in the order of k_spmv<8> and k_pcg_step<> (the same
 // tiles, lanes, wavefront sums and partials), so both forms give the same
@@ -48,8 +50,10 @@
 // Split: T tiles of 64 rows per workgroup of 512 threads.  T = 1 as long as the tiles do not outnumber the compute
 // units (more units share the LDS and register traffic), else 2, else 4; the
 // coarse correction takes T = 4, which makes a workgroup one slice of a
-// coarse domain.  T = 4 is what registers hold: 8 blocks per lane are 144 of
-// the 256 registers.  Rows of more than LONG_ROW blocks go to workgroups of
+// coarse domain.  T = 4 is the most that the registers take: 8 blocks per lane
+// are 144 of the 256, and 12 more (6 with the coarse correction) are spilled, 28
+// bytes of scratch memory per lane; T = 1 and 2 take 146 and 172 registers.  The arguments and what follows from them do not fit the
+// scalar registers (115 to 212 of them are kept in lanes of vector registers).  Rows of more than LONG_ROW blocks go to workgroups of
 // their own, as in k_spmv.
 #include <mutex>
 
