@@ -51,10 +51,11 @@
 // units (more units share the LDS and register traffic), else 2, else 4; the
 // coarse correction takes T = 4, which makes a workgroup one slice of a
 // coarse domain.  T = 4 is the most that the registers take: 8 blocks per lane
-// are 144 of the 256, and 12 more (6 with the coarse correction) are spilled, 28
-// bytes of scratch memory per lane; T = 1 and 2 take 146 and 172 registers.  The arguments and what follows from them do not fit the
-// scalar registers (115 to 212 of them are kept in lanes of vector registers).  Rows of more than LONG_ROW blocks go to workgroups of
-// their own, as in k_spmv.
+// are 144 of the 256, and 12 more (6 with the coarse correction) are spilled,
+// 28 bytes of scratch memory per lane; T = 1 and 2 take 146 and 172 registers.
+// The arguments and what follows from them do not fit the scalar registers
+// (115 to 212 of them are kept in lanes of vector registers).  Rows of more
+// than LONG_ROW blocks go to workgroups of their own, as in k_spmv.
 #include <mutex>
 
 #include "ipc_device.h"
